@@ -509,12 +509,17 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
       hipLaunchKernelGGL(kv_desc_fill_kernel, dim3(1), dim3(512), 0, st, p->na_dev, at, m, pack);
     }
     HIPCHK(p, hipGetLastError());
-    MoveArgs a;
-    int u = 1;
-    const int grid = build_move_args(p, 2, (size_t)n, nullptr, 0, false, &a, &u);
-    a.desc = p->na_dev;
     (void)hipGetLastError();
-    launch_move<2>(u, grid, 0, st, a);
+    int grid;
+    if (hbm_kernels(p)) {
+      grid = launch_hbm(p, 2, p->na_dev, nullptr, (size_t)n, nullptr, false, st);
+    } else {
+      MoveArgs a;
+      int u = 1;
+      grid = build_move_args(p, 2, (size_t)n, nullptr, 0, &a, &u);
+      a.desc = p->na_dev;
+      launch_move<2>(u, grid, 0, st, a);
+    }
     HIPCHK(p, hipGetLastError());
     p->plan_stats.launches = 1;
     p->plan_stats.grid = grid;

@@ -1,0 +1,67 @@
+"""The kernels for launches with both ends in HBM, at the sizes where one form hands over to the next: chunks of whole
+KiB, chunks of whole 128-byte lines, ragged chunks, blocks of less than a wavefront, with and without scales, layer-
+major and padded pools.  Gather, scatter (in both job orders) and move against the oracle, byte for byte."""
+import numpy as np
+import pytest
+
+from adapters import GpuAdapter
+from hostpool import HostPool
+from oracle import kv_oracle as ko
+from paper_2510_02758_amd import kvswap as kv
+from paper_2510_02758_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+GEOMS = {
+    "1KiB": W.Geometry(3, 1, 64, 8, "bf16", 96),                       # one full wavefront per chunk
+    "9KiB": W.Geometry(2, 4, 72, 16, "f16", 80),
+    "1152B": W.Geometry(3, 1, 72, 8, "bf16", 96),                      # whole lines, no whole KiB; 432 vectors: lane per vector
+    "2560B": W.Geometry(2, 2, 80, 8, "bf16", 96),                      # 640 vectors per block: the last job is full
+    "128B": W.Geometry(5, 1, 16, 4, "bf16", 300),                      # 80 vectors per block
+    "1040B": W.Geometry(5, 1, 65, 8, "bf16", 300),                     # ragged: no whole line
+    "20528B": W.Geometry(3, 1, 5132, 2, "bf16", 40),                   # ragged and longer than 4 KiB: both orders of the scatter
+    "16B": W.Geometry(1, 1, 8, 1, "bf16", 2000),                       # blocks of 32 bytes
+    "fp8_1KiB": W.Geometry(2, 2, 64, 8, "fp8_e4m3", 96, scales=True),
+    "fp8_4KiB_wide": W.Geometry(5, 32, 16, 8, "fp8_e4m3", 64, scales=True),     # 320 scale words: a full side job and a short one
+    "fp8_640B": W.Geometry(6, 10, 16, 4, "fp8_e4m3", 96, scales=True),          # 480 vectors, a head count that is no power of two
+    "fp8_256B": W.Geometry(2, 2, 16, 8, "fp8_e4m3", 200, scales=True),          # a block is exactly one wavefront
+    "fp8_48B": W.Geometry(2, 2, 8, 3, "fp8_e4m3", 300, scales=True),
+}
+
+
+@pytest.mark.parametrize("layout", ["layer", "padded"])
+@pytest.mark.parametrize("name", list(GEOMS))
+def test_gather_scatter_move(gpu, name, layout):
+    g = GEOMS[name]
+    rng = np.random.default_rng(sum(map(ord, name)))
+    for n, order in ((1, 0), (8, 0), (9, 0), (g.N // 3, 0), (g.N // 3, 2)):
+        perm = rng.permutation(g.N).astype(np.int32)
+        src, dst, mid = perm[:n], perm[n:2 * n], perm[2 * n:3 * n]
+        tune = ((kv.KV_TUNE_SCATTER_ORDER, order),) if order else ()
+        a, b = (HostPool(g, 0xB0B + n, layout, slots=n + 1) for _ in range(2))
+        ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE, tune=tune)
+        for lib in (ora, gpu_lib):
+            assert lib.swap_out([7], [0, n], src, [n * g.B]) == ko.OK
+            assert lib.swap_in([7], [0, n], dst) == ko.OK
+            assert lib.move_blocks(dst, mid) == ko.OK
+        assert np.array_equal(a.staging, b.staging), (name, n, "gather")
+        assert np.array_equal(a.pool, b.pool), (name, n, "scatter or move")
+        if g.scales:
+            assert np.array_equal(a.scale, b.scale), (name, n, "scales")
+        gpu_lib.close()
+
+
+@pytest.mark.parametrize("name", ["9KiB", "1040B", "fp8_1KiB", "fp8_48B"])
+def test_bounce_buffer(gpu, name):
+    """The copy-engine path's gather and scatter run the same kernels between the pool and the bounce buffer."""
+    g = GEOMS[name]
+    n = 21
+    perm = np.random.default_rng(3).permutation(g.N).astype(np.int32)
+    a, b = (HostPool(g, 0xB0C, "padded", slots=n) for _ in range(2))
+    ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_PATH_DMA, bounce_slots=10)
+    for lib in (ora, gpu_lib):
+        assert lib.swap_out([1, 2], [0, 4, n], perm[:n], [4 * g.B, (n - 4) * g.B]) == ko.OK
+        assert lib.swap_in([2, 1], [0, n - 4, n], perm[n:2 * n]) == ko.OK
+    assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
+    assert not g.scales or np.array_equal(a.scale, b.scale)
+    gpu_lib.close()
