@@ -243,9 +243,10 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
 
 /* kv_move_blocks for callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, same result in the pool, same kernel.  The call makes no hipMalloc,
- * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: its descriptors travel inside the
- * arguments of small fill launches (448 per launch) into a fixed device array that is part of the library's code
- * object (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB per GPU, held until the process ends).
+ * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: up to 448 descriptors travel inside
+ * the arguments of the move kernel, longer lists inside the arguments of small fill launches (448 per launch) into a
+ * fixed device array that is part of the library's code object (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB
+ * per GPU, held until the process ends).
  *   - n > KV_NOALLOC_MAX_BLOCKS returns KV_E2BIG and does nothing; split the list.
  *   - Runs on the evict stream after everything enqueued on either stream of this handle before it; load-stream
  *     calls made while it is unfinished wait for it as a whole (it keeps no per-block marks).

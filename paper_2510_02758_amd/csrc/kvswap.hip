@@ -202,6 +202,7 @@ int kv_pool_create(const kv_pool_config* cfg, kv_pool** out) {
         }
       }
     }
+    hbm_setup(p);
     if (!rc) rc = grow_ring(p, ring_entries_for(cfg->num_blocks));
     if (!rc) {
       p->blk_reader.assign((size_t)cfg->num_blocks, BlkMark{0, -1});
@@ -455,8 +456,8 @@ KV_CATCH(p)
 
 // kv_move_blocks for callers that cannot allocate.  Uses only what kv_pool_create set up: no hipMalloc, hipFree,
 // hipHostMalloc, event or stream creation, and no host heap either (the descriptors travel inside kernel
-// arguments, duplicates are found with the handle's bitmap).  The kernel is the one kv_move_blocks launches; it
-// reads its descriptors from the library's fixed device array instead of the growable ring.
+// arguments, duplicates are found with the handle's bitmap).  The kernel is the one kv_move_blocks launches; a list
+// that its arguments do not hold is read from the library's fixed device array instead of the growable ring.
 int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t* dst_ids, void* wait_event) try {
   if (!p) return KV_EINVAL;
   KV_ENTER(p);
@@ -498,26 +499,30 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   hipEvent_t callers = (hipEvent_t)wait_event;
   if (callers) HIPCHK(p, hipStreamWaitEvent(st, callers, 0));
   if (n > 0) {
-    // The descriptors go into the fixed array in batches that travel as kernel arguments: nothing on the host has to
-    // outlive this call, so it never waits for an earlier one.  The array keeps the previous call's descriptors:
-    // [0, n) is overwritten here, in stream order behind the previous call's kernel, and nothing beyond n is read.
+    // Up to kInlineDescMax descriptors travel inside the arguments of the move itself.  More go into the fixed array
+    // in batches that travel as kernel arguments: nothing on the host has to outlive this call, so it never waits for
+    // an earlier one.  The array keeps the previous call's descriptors: [0, n) is overwritten here, in stream order
+    // behind the previous call's kernel, and nothing beyond n is read.
+    const bool inline_desc = n <= kInlineDescMax;
     (void)hipGetLastError();
     DescPack pack;
     for (int64_t at = 0; at < n; at += kDescPack) {
       const int m = (int)std::min<int64_t>(kDescPack, n - at);
       for (int i = 0; i < m; i++) pack.d[i] = {src_ids[at + i], dst_ids[at + i]};
-      hipLaunchKernelGGL(kv_desc_fill_kernel, dim3(1), dim3(512), 0, st, p->na_dev, at, m, pack);
+      if (!inline_desc) hipLaunchKernelGGL(kv_desc_fill_kernel, dim3(1), dim3(512), 0, st, p->na_dev, at, m, pack);
     }
     HIPCHK(p, hipGetLastError());
     (void)hipGetLastError();
     int grid;
     if (hbm_kernels(p)) {
-      grid = launch_hbm(p, 2, p->na_dev, nullptr, (size_t)n, nullptr, false, st);
+      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, false, st);
     } else {
       MoveArgs a;
       int u = 1;
       grid = build_move_args(p, 2, (size_t)n, nullptr, 0, &a, &u);
       a.desc = p->na_dev;
+      a.use_inl = inline_desc ? 1 : 0;
+      if (inline_desc) std::memcpy(a.inl, pack.d, (size_t)n * sizeof(Desc));
       launch_move<2>(u, grid, 0, st, a);
     }
     HIPCHK(p, hipGetLastError());
