@@ -1,6 +1,7 @@
-"""The kernels for launches with both ends in HBM, at the sizes where one form hands over to the next: chunks of whole
-KiB, chunks of whole 128-byte lines, ragged chunks, blocks of less than a wavefront, with and without scales, layer-
-major and padded pools.  Gather, scatter (in both job orders) and move against the oracle, byte for byte."""
+"""The kernels for launches with both ends in HBM and for the host arena, at the sizes where one form hands over to the
+next: chunks of whole KiB, chunks of whole 128-byte lines, ragged chunks, blocks of less than a wavefront, slots of
+whole and of ragged jobs, with and without scales, layer-major and padded pools, descriptor lists inside and outside the
+kernel arguments.  Gather, scatter (in both job orders) and move against the oracle, byte for byte."""
 import numpy as np
 import pytest
 
@@ -65,3 +66,50 @@ def test_bounce_buffer(gpu, name):
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     assert not g.scales or np.array_equal(a.scale, b.scale)
     gpu_lib.close()
+
+
+@pytest.mark.parametrize("layout", ["layer", "padded"])
+@pytest.mark.parametrize("name", list(GEOMS))
+def test_host_arena(gpu, name, layout):
+    """One block, a ragged list, and both directions in flight at once (the wider launches)."""
+    g = GEOMS[name]
+    rng = np.random.default_rng(1 + sum(map(ord, name)))
+    for n in (1, g.N // 3):
+        perm = rng.permutation(g.N).astype(np.int32)
+        src, dst, more = perm[:n], perm[n:2 * n], perm[2 * n:2 * n + 1]
+        a, b = (HostPool(g, 0xB0D + n, layout, slots=n + 2) for _ in range(2))
+        ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_PATH_ZEROCOPY)
+        assert ora.swap_out([7], [0, n], src, [n * g.B]) == ko.OK
+        assert ora.swap_in([7], [0, n], dst) == ko.OK
+        assert ora.swap_out([8], [0, 1], more, [g.B]) == ko.OK
+        gpu_lib._push()
+        kp = gpu_lib.kp
+        assert kp.swap_out([7], [0, n], src, [n * g.B]) == kv.KV_OK
+        assert kp.swap_in([7], [0, n], dst) == kv.KV_OK
+        assert kp.swap_out([8], [0, 1], more, [g.B]) == kv.KV_OK
+        gpu_lib._pull()
+        assert np.array_equal(a.staging, b.staging), (name, n, "gather")
+        assert np.array_equal(a.pool, b.pool), (name, n, "scatter")
+        if g.scales:
+            assert np.array_equal(a.scale, b.scale), (name, n, "scales")
+        gpu_lib.close()
+
+
+def test_lists_longer_than_the_kernel_arguments(gpu):
+    """448 descriptors travel inside the arguments, 449 do not."""
+    g = W.Geometry(1, 1, 16, 4, "bf16", 1400)
+    perm = np.random.default_rng(9).permutation(g.N).astype(np.int32)
+    for n in (448, 449):
+        for flags in (kv.KV_STAGING_DEVICE, kv.KV_PATH_ZEROCOPY, kv.KV_PATH_DMA):
+            a, b = (HostPool(g, 0xB0E, "layer", slots=n) for _ in range(2))
+            ora, gpu_lib = a.oracle(), GpuAdapter(b, flags, bounce_slots=n)
+            for lib in (ora, gpu_lib):
+                assert lib.swap_out([1], [0, n], perm[:n], [n * g.B]) == ko.OK
+                assert lib.swap_in([1], [0, n], perm[n:2 * n]) == ko.OK
+            assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), (n, flags)
+            assert ora.move_blocks(perm[n:2 * n], perm[2 * n:3 * n]) == ko.OK
+            gpu_lib._push()
+            assert gpu_lib.kp.move_blocks_noalloc(perm[n:2 * n], perm[2 * n:3 * n]) == kv.KV_OK
+            gpu_lib._pull()
+            assert np.array_equal(a.pool, b.pool), (n, flags, "move")
+            gpu_lib.close()
