@@ -220,9 +220,9 @@ int kv_swap_in(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* of
  * to the load).  The result is that of kv_swap_out(first set) followed by kv_swap_in(second set); the destination
  * blocks of the load may be blocks of the requests being evicted.  The call is all-or-nothing as a whole: the load is
  * checked before the eviction changes anything.  A request id may appear in one set only (KV_EINVAL).  On the
- * zero-copy path the two transfers are cut into phases of KV_TUNE_PHASE_BYTES (256 MiB) and interleaved on the two
- * streams so that one eviction kernel and one load kernel always start together, each load phase waiting only for
- * the eviction phase that frees its blocks; per-request completion (kv_req_poll / kv_req_wait) follows the phases.
+ * zero-copy path the two transfers are cut into phases (KV_TUNE_PHASE_BYTES) and run beside each other on the two
+ * streams, each load phase waiting only for the eviction phase that frees its blocks; per-request completion
+ * (kv_req_poll / kv_req_wait) follows the phases.
  * On the copy-engine path and under KV_PLAN_ONLY it is the two calls one after the other.  kv_last_stats and
  * kv_last_plan afterwards report the load.
  * Errors: those of kv_swap_out and kv_swap_in. */
@@ -361,26 +361,24 @@ int kv_swap_out_delta_timed(kv_pool* p, int32_t n, const uint64_t* req_ids, cons
 /* Launch-shape knobs: value 0 restores the default. */
 enum {
   KV_TUNE_MAX_WGS_DEVICE = 1, /* workgroup cap when both ends are in HBM */
-  KV_TUNE_MAX_WGS_LINK = 2,   /* workgroup cap when one end is host memory (CU budget; default 64, which saturates the
-                                 link in one direction; a caller that keeps both directions busy with separate calls
-                                 gains 5-7 % aggregate with 128-160) */
+  KV_TUNE_MAX_WGS_LINK = 2,   /* workgroup cap when one end is host memory (CU budget; default 60 out, 48 in: either
+                                 saturates the link in its direction, and the two share it when both are busy) */
   KV_TUNE_KERNEL_VARIANT = 3, /* 0 default; other values select experimental kernels */
   KV_TUNE_DMA_SLICE_BLOCKS = 4, /* blocks per gather+copy slice on the DMA path */
   KV_TUNE_SEGMENT_BYTES = 5,    /* smallest segment under KV_REQ_EVENTS (default 32 MiB) */
-  KV_TUNE_SCALE_LDS = 6,        /* scale side band: 0 default (LDS for the scatter), 1 word by word, 2 LDS both ways */
+  KV_TUNE_SCALE_LDS = 6,        /* scale side band of launches on the host arena: 0 default, 1 word by word, 2 through LDS */
   KV_TUNE_SCATTER_ORDER = 8,    /* scatter of 1024 blocks and more with both ends in HBM: 0 default (the handle times
                                    both job orders on its first two such calls and keeps the faster), 1 always block
                                    by block, 2 plane by plane over descriptors sorted by destination block, whatever the size */
-  KV_TUNE_PHASE_BYTES = 9,      /* kv_evict_and_load: bytes of one phase per direction (default 256 MiB) */
-  KV_TUNE_PHASE_WGS_OUT = 10,   /* kv_evict_and_load: workgroups of an eviction phase (default 128) */
-  KV_TUNE_PHASE_WGS_IN = 11,    /* kv_evict_and_load: workgroups of a load phase (default 128: with both directions of
-                                   the link busy each kernel needs more requests in flight than alone, and the two do
-                                   best with equal counts) */
+  KV_TUNE_PHASE_BYTES = 9,      /* kv_evict_and_load: bytes of one phase per direction (default an eighth of the larger
+                                   transfer, between 16 and 64 MiB) */
+  KV_TUNE_PHASE_WGS_OUT = 10,   /* kv_evict_and_load: workgroups of an eviction phase (default 36) */
+  KV_TUNE_PHASE_WGS_IN = 11,    /* kv_evict_and_load: workgroups of a load phase (default 36: the two directions do best
+                                   with equal counts) */
   KV_TUNE_LINK_IN_WGS = 14,     /* workgroups of the scatter out of the host arena alone (0: as KV_TUNE_MAX_WGS_LINK) */
   KV_TUNE_LINK_IN_UNROLL = 15,  /* 16-byte loads in flight per lane of that scatter: 1, 2, 4, 8 (0: by chunk size) */
-  KV_TUNE_HOST_STORES = 13,     /* zero-copy gather into the host arena: 0 (default) each lane writes 64 consecutive bytes with
-                                   ordinary stores that L2 merges into full lines; 1 whole 128-byte lines per store instruction,
-                                   non-temporal */
+  KV_TUNE_HOST_STORES = 13,     /* zero-copy gather into the host arena: 0 (default) whole 128-byte lines per store instruction that
+                                   go straight through L2; 1 the same lines with the non-temporal hint only */
   KV_TUNE_KERNEL_EVENTS = 12,   /* 1: every data kernel is bracketed by its own pair of events, so that kv_stats.ms_kernel
                                    is the kernel alone also for a call that is a single launch (otherwise such a call
                                    reports its whole stream time, descriptor upload included); for measurements */

@@ -52,6 +52,57 @@ hipError_t scratch_on_current_device(Desc** out, int* dev_out) {
 }
 }  // namespace
 
+// ---- the job counters of the host-arena launches ----
+// 64 words per handle (a cache line per direction), part of the code object like `scratch` and zero from its loading on:
+// every launch leaves them zero, so a handle needs no allocation, no copy and no wait to get its own.  A handle
+// gives its slot back when it is destroyed with its streams drained; one whose streams failed keeps it.  Handles beyond
+// kTicketSlots on one GPU at a time allocate their own.
+namespace {
+constexpr int kTicketSlots = 1024, kTicketWords = 64;
+}
+static __device__ __align__(256) uint32_t ticket_words[kTicketSlots * kTicketWords];
+
+namespace {
+std::mutex g_ticket_mu;
+uint32_t* kTicketsOn[kMaxDevices] = {};
+uint64_t g_ticket_taken[kMaxDevices][kTicketSlots / 64] = {};
+
+int tickets_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
+  {
+    std::lock_guard<std::mutex> g(g_ticket_mu);
+    if (!kTicketsOn[p->device]) {
+      uint32_t* at = nullptr;
+      HIPCHK(p, hipGetSymbolAddress((void**)&at, HIP_SYMBOL(ticket_words)));
+      kTicketsOn[p->device] = at;
+    }
+    uint64_t* taken = g_ticket_taken[p->device];
+    for (int s = 0; s < kTicketSlots; s++)
+      if (!(taken[s >> 6] >> (s & 63) & 1)) {
+        taken[s >> 6] |= 1ull << (s & 63);
+        p->ticket_slot = s;
+        p->tickets = kTicketsOn[p->device] + s * kTicketWords;
+        return KV_OK;
+      }
+  }
+  constexpr size_t bytes = kTicketWords * sizeof(uint32_t);
+  HIPCHK(p, hipMalloc((void**)&p->tickets, bytes));
+  std::memset(p->ring_host, 0, bytes);  // the ring is empty: its first words serve as the source
+  HIPCHK(p, hipMemcpyAsync(p->tickets, p->ring_host, bytes, hipMemcpyHostToDevice, p->stream[kEvict]));
+  HIPCHK(p, hipStreamSynchronize(p->stream[kEvict]));
+  return KV_OK;
+}
+
+void tickets_give_back(kv_pool* p, bool drained) {
+  if (p->ticket_slot >= 0) {
+    std::lock_guard<std::mutex> g(g_ticket_mu);
+    if (drained) g_ticket_taken[p->device][p->ticket_slot >> 6] &= ~(1ull << (p->ticket_slot & 63));
+  } else if (p->tickets) {
+    (void)hipFree(p->tickets);
+  }
+  p->tickets = nullptr;
+}
+}  // namespace
+
 // Everything kv_move_blocks_noalloc will need, taken once when the handle is created: the address of the
 // descriptor array on this GPU, two events and the duplicate bitmap.
 static int noalloc_setup(kv_pool* p) {
@@ -209,6 +260,7 @@ int kv_pool_create(const kv_pool_config* cfg, kv_pool** out) {
       p->blk_writer.assign((size_t)cfg->num_blocks, BlkMark{0, -1});
     }
     if (!rc) rc = noalloc_setup(p);
+    if (!rc && !p->dev_staging) rc = tickets_setup(p);
     if (rc) {
       kv_pool_destroy(p);
       return rc;
@@ -231,6 +283,7 @@ int kv_pool_destroy(kv_pool* p) try {
     for (auto ev : p->ev_free) (void)hipEventDestroy(ev);
     if (p->ring_host) (void)hipHostFree(p->ring_host);
     if (p->ring_dev) (void)hipFree(p->ring_dev);
+    tickets_give_back(p, rc == KV_OK && !p->broken);
     if (p->na_fence_ev) (void)hipEventDestroy(p->na_fence_ev);
     if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
     for (int s = 0; s < 2; s++)
@@ -938,7 +991,7 @@ int kv_pool_tune(kv_pool* p, int32_t what, int64_t value) try {
       p->kernel_events = value ? 1 : 0;
       return KV_OK;
     case KV_TUNE_PHASE_BYTES:
-      p->phase_bytes = value ? value : 256ll << 20;
+      p->phase_bytes = value;
       return KV_OK;
     case KV_TUNE_PHASE_WGS_OUT:
       p->phase_wgs_out = value;
