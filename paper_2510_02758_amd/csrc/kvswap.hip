@@ -297,11 +297,11 @@ catch (...) {
 }
 
 static int swap_out_common(kv_pool* p, int op, Plan& plan, double t0, void* wait_event) {
-  p->last_plan = plan.desc;
   const double t1 = now_us();
   if (p->plan_only) {
     p->plan_stats = kv_stats{};
     fill_plan_stats(p, &p->plan_stats, op, plan.desc.size(), t1 - t0);
+    keep_plan(p, &plan);
     return KV_OK;
   }
   // slots this call writes may still be read by an unfinished swap-in
@@ -317,6 +317,7 @@ static int swap_out_common(kv_pool* p, int op, Plan& plan, double t0, void* wait
     p->plan_stats = kv_stats{};
     fill_plan_stats(p, &p->plan_stats, op, 0, t1 - t0);
     p->last_instant = true;
+    keep_plan(p, &plan);
     return KV_OK;
   }
   Call* c = nullptr;
@@ -329,6 +330,7 @@ static int swap_out_common(kv_pool* p, int op, Plan& plan, double t0, void* wait
   if (rc) return rc;
   for (uint64_t id : plan.touched)
     if (kvswap::Req* r = p->planner.find_mut(id)) r->out_seq = c->seq;
+  keep_plan(p, &plan);
   c->st.enqueue_us = now_us() - t1;
   return KV_OK;
 }
@@ -339,6 +341,7 @@ int kv_swap_out(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* o
   KV_ENTER(p);
   const double t0 = now_us();
   Plan plan;
+  take_plan_buffer(p, &plan);
   int rc = p->planner.plan_swap_out(n, req_ids, offsets, block_ids, num_tokens, &plan);
   if (rc) return rc;
   for (int32_t i = 0; i < n; i++) p->wq.erase(req_ids[i]);  // a swapped-out request has nothing left to write through
@@ -353,6 +356,7 @@ int kv_swap_out_delta(kv_pool* p, int32_t n, const uint64_t* req_ids, const int3
   KV_ENTER(p);
   const double t0 = now_us();
   Plan plan;
+  take_plan_buffer(p, &plan);
   int rc = p->planner.plan_delta(n, req_ids, offsets, block_ids, num_tokens, block_budget, flags, blocks_moved,
                                  &plan);
   if (rc) return rc;
@@ -366,14 +370,15 @@ int kv_swap_in(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* of
   KV_ENTER(p);
   const double t0 = now_us();
   Plan plan;
+  take_plan_buffer(p, &plan);
   int rc = p->planner.plan_swap_in(n, req_ids, offsets, new_block_ids, flags, &plan);
   if (rc) return rc;
   for (int32_t i = 0; i < n; i++) p->wq.erase(req_ids[i]);  // their tables have just changed
-  p->last_plan = plan.desc;
   const double t1 = now_us();
   if (p->plan_only) {
     p->plan_stats = kv_stats{};
     fill_plan_stats(p, &p->plan_stats, 3, plan.desc.size(), t1 - t0);
+    keep_plan(p, &plan);
     return KV_OK;
   }
   const uint64_t dep = cross_stream(p, kLoad, plan.wait_out_seq);
@@ -381,6 +386,7 @@ int kv_swap_in(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* of
     p->plan_stats = kv_stats{};
     fill_plan_stats(p, &p->plan_stats, 3, 0, t1 - t0);
     p->last_instant = true;
+    keep_plan(p, &plan);
     return KV_OK;
   }
   Call* c = nullptr;
@@ -394,6 +400,7 @@ int kv_swap_in(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* of
   for (uint64_t id : plan.touched)
     if (kvswap::Req* r = p->planner.find_mut(id)) r->in_seq = c->seq;
   for (auto& f : plan.freed) p->pending.push_back({f.first, f.first + f.second, c->seq});
+  keep_plan(p, &plan);
   c->st.enqueue_us = now_us() - t1;
   return KV_OK;
 }
@@ -482,14 +489,15 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
   KV_ENTER(p);
   const double t0 = now_us();
   Plan plan;
+  take_plan_buffer(p, &plan);
   int rc = p->planner.plan_move(n, src_ids, dst_ids, &plan);
   if (rc) return rc;
-  p->last_plan = plan.desc;
   const double t1 = now_us();
   if (p->plan_only || (plan.desc.empty() && !wait_event)) {
     p->plan_stats = kv_stats{};
     fill_plan_stats(p, &p->plan_stats, 4, plan.desc.size(), t1 - t0);
     p->last_instant = true;
+    keep_plan(p, &plan);
     return KV_OK;
   }
   Call* c = nullptr;
@@ -502,6 +510,7 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
   mark_blocks(p, *c, 2, plan.desc.data(), plan.desc.size(), -1);
   rc = close_call(p, *c);
   if (rc) return rc;
+  keep_plan(p, &plan);
   c->st.enqueue_us = now_us() - t1;
   return KV_OK;
 }

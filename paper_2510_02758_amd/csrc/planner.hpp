@@ -151,6 +151,7 @@ class Planner {
     if (rc || n == 0) return rc;
     if (!ntok) return KV_EINVAL;
     begin();
+    out->desc.reserve((size_t)((int64_t)off[n] - off[0]));
     for (int32_t i = 0; i < n && !rc; i++) {
       int64_t len = ntok[i], row = (int64_t)off[i + 1] - off[i];
       if (len < 0 || row != (len + B_ - 1) / B_) { rc = KV_EINVAL; break; }
@@ -233,6 +234,7 @@ class Planner {
                    Plan* out) {
     int rc = check_swap_in(n, ids, off, blk);
     if (rc || n == 0) return rc;
+    out->desc.reserve((size_t)((int64_t)off[n] - off[0]));
     for (int32_t i = 0; i < n; i++) {
       Req* r = find_mut(ids[i]);
       for (int64_t j = 0; j < r->staged; j++) out->desc.push_back({blk[off[i] + j], (int32_t)(r->base + j)});
@@ -273,6 +275,7 @@ class Planner {
       for (int64_t i = 0; i < n; i++)
         if (mark_[(size_t)(dst[i] >> 6)] >> (dst[i] & 63) & 1) return KV_EDUP;
     }
+    out->desc.reserve((size_t)n);
     for (int64_t i = 0; i < n; i++) out->desc.push_back({src[i], dst[i]});
     return KV_OK;
   }
@@ -285,10 +288,14 @@ class Planner {
     for (int32_t i = 0; i < n; i++)
       if (off[i + 1] < off[i]) return KV_EINVAL;
     if (off[n] > off[0] && !blk) return KV_EINVAL;
-    seen_.clear();
-    seen_.reserve((size_t)n * 2);
-    for (int32_t i = 0; i < n; i++)
-      if (!seen_.emplace(ids[i], 0).second) return KV_EINVAL;
+    // a repeated id: callers mostly hand ids in ascending order, which a single pass proves distinct; others are sorted
+    bool ascending = true;
+    for (int32_t i = 1; i < n && ascending; i++) ascending = ids[i - 1] < ids[i];
+    if (!ascending) {
+      ids_.assign(ids, ids + n);
+      std::sort(ids_.begin(), ids_.end());
+      if (std::adjacent_find(ids_.begin(), ids_.end()) != ids_.end()) return KV_EINVAL;
+    }
     for (int64_t k = off[0]; k < off[n]; k++)
       if (blk[k] < 0 || blk[k] >= N_) return KV_ERANGE;
     return KV_OK;
@@ -360,7 +367,7 @@ class Planner {
   int64_t N_ = 0, B_ = 1;
   ExtentAlloc alloc_;
   std::unordered_map<uint64_t, Req> reqs_;
-  std::unordered_map<uint64_t, int> seen_;
+  std::vector<uint64_t> ids_;
   std::vector<Undo> undo_;
   std::vector<int32_t> moved_;
   std::vector<uint64_t> mark_;

@@ -121,14 +121,21 @@ for _name, (_res, _args) in _sig.items():
 
 
 def _p(a):
-    return None if a is None else a.ctypes.data_as(_vp)
+    return None if a is None else a.ctypes.data
+
+
+_I32, _U64 = np.dtype(np.int32), np.dtype(np.uint64)
 
 
 def _i32a(a):
+    if type(a) is np.ndarray and a.dtype == _I32 and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
 def _u64a(a):
+    if type(a) is np.ndarray and a.dtype == _U64 and a.flags.c_contiguous:
+        return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.uint64))
 
 
@@ -137,6 +144,17 @@ def _csr_ok(n, offsets, block_ids, *per_request):
     if len(offsets) != n + 1 or any(len(a) != n for a in per_request):
         return False
     return n == 0 or int(offsets.max()) <= len(block_ids)
+
+
+def _rows_ok(n, offsets, block_ids, *per_request):
+    """_csr_ok for the calls that refuse offsets which go down before they read a block id: the last one is then the
+    largest."""
+    if len(offsets) != n + 1:
+        return False
+    for a in per_request:
+        if len(a) != n:
+            return False
+    return n == 0 or offsets[n] <= len(block_ids)
 
 
 def kv_strerror(code):
@@ -157,7 +175,7 @@ def kv_pool_destroy(h):
 
 def kv_swap_out(h, req_ids, offsets, block_ids, num_tokens, wait_event=None):
     r, o, b, t = _u64a(req_ids), _i32a(offsets), _i32a(block_ids), _i32a(num_tokens)
-    if not _csr_ok(len(r), o, b, t):
+    if not _rows_ok(len(r), o, b, t):
         return KV_EINVAL
     return _lib.kv_swap_out(h, len(r), _p(r), _p(o), _p(b), _p(t), wait_event)
 
@@ -166,7 +184,7 @@ def kv_swap_out_delta(h, req_ids, offsets, block_ids, num_tokens, block_budget=0
     """-> (rc, blocks_moved int32[n])"""
     r, o, b, t = _u64a(req_ids), _i32a(offsets), _i32a(block_ids), _i32a(num_tokens)
     moved = np.zeros(len(r), dtype=np.int32)
-    if not _csr_ok(len(r), o, b, t):
+    if not _rows_ok(len(r), o, b, t):
         return KV_EINVAL, moved
     rc = _lib.kv_swap_out_delta(h, len(r), _p(r), _p(o), _p(b), _p(t), int(block_budget), int(flags),
                                 _p(moved), wait_event)
@@ -216,7 +234,7 @@ def kv_wq_pending(h):
 
 def kv_swap_in(h, req_ids, offsets, new_block_ids, flags=0, wait_event=None):
     r, o, b = _u64a(req_ids), _i32a(offsets), _i32a(new_block_ids)
-    if not _csr_ok(len(r), o, b):
+    if not _rows_ok(len(r), o, b):
         return KV_EINVAL
     return _lib.kv_swap_in(h, len(r), _p(r), _p(o), _p(b), int(flags), wait_event)
 
@@ -225,7 +243,7 @@ def kv_evict_and_load(h, out_ids, out_offsets, out_block_ids, out_tokens, in_ids
                       wait_event=None):
     r, o, b, t = _u64a(out_ids), _i32a(out_offsets), _i32a(out_block_ids), _i32a(out_tokens)
     r2, o2, b2 = _u64a(in_ids), _i32a(in_offsets), _i32a(in_block_ids)
-    if not _csr_ok(len(r), o, b, t) or not _csr_ok(len(r2), o2, b2):
+    if not _rows_ok(len(r), o, b, t) or not _rows_ok(len(r2), o2, b2):
         return KV_EINVAL
     return _lib.kv_evict_and_load(h, len(r), _p(r), _p(o), _p(b), _p(t), len(r2), _p(r2), _p(o2), _p(b2), int(in_flags),
                                   wait_event)
