@@ -505,7 +505,13 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
   if (rc) return rc;
   fill_plan_stats(p, &c->st, 4, plan.desc.size(), t1 - t0);
   c->st.path = KV_PATH_ZEROCOPY;
-  rc = enqueue_kernel(p, *c, 2, plan.desc.data(), plan.desc.size(), nullptr, 0, /*sole=*/true);
+  const bool pm = plane_by_plane_move(p, plan.desc.size());
+  std::vector<Desc> kd;
+  if (pm) {
+    kd = plan.desc;
+    sort_desc(p, &kd, &Desc::b, p->cfg.num_blocks);
+  }
+  rc = enqueue_kernel(p, *c, 2, pm ? kd.data() : plan.desc.data(), plan.desc.size(), nullptr, 0, /*sole=*/true, pm);
   if (rc) return rc;
   mark_blocks(p, *c, 2, plan.desc.data(), plan.desc.size(), -1);
   rc = close_call(p, *c);
@@ -577,7 +583,9 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     (void)hipGetLastError();
     int grid;
     if (hbm_kernels(p)) {
-      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, false, st);
+      const bool pm = inline_desc && plane_by_plane_move(p, (size_t)n);  // (a longer list would need a buffer to be sorted in)
+      if (pm) std::sort(pack.d, pack.d + n, [](const Desc& x, const Desc& y) { return x.b < y.b; });
+      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, pm, st);
     } else {
       MoveArgs a;
       int u = 1;

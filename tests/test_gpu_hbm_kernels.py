@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 
 GEOMS = {
     "1KiB": W.Geometry(3, 1, 64, 8, "bf16", 96),                       # one full wavefront per chunk
+    "1KiB_many": W.Geometry(1, 1, 64, 8, "bf16", 1800),                 # lists of 600 of 1800: sorted by digits, plane by plane
     "9KiB": W.Geometry(2, 4, 72, 16, "f16", 80),
     "1152B": W.Geometry(3, 1, 72, 8, "bf16", 96),                      # whole lines, no whole KiB; 432 vectors: lane per vector
     "2560B": W.Geometry(2, 2, 80, 8, "bf16", 96),                      # 640 vectors per block: the last job is full
