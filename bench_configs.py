@@ -24,9 +24,8 @@ oracle itself stays single-threaded).
      scheduling call for its Python scheduler, Section 7.5), and a simulated burst (Section 7.3 shape: 80
      requests, long inputs and outputs) served with real KV blocks on the GPU under the buffer-aware policy and
      under run-to-completion FCFS.
-  8  the general builds of the move kernel with both ends in HBM: the fp8 + scales shape (scale jobs, LDS
-     scatter), a one-KV-head shard of the 70B shape (4 KiB chunks) and a token-level pool (256-byte chunks,
-     several chunks per workgroup), each against the 8 TB/s peak and a scrambled plain copy of the same run length.
+  8  other pool shapes with both ends in HBM: the fp8 + scales shape (scale jobs), a one-KV-head shard of the 70B
+     shape (4 KiB chunks) and a token-level pool (256-byte chunks), each against the 8 TB/s peak and a scrambled plain copy of the same run length.
 """
 import argparse
 import json
@@ -815,24 +814,24 @@ def config7(kv, W, torch, dev, args, arena=None, streams=None):
 
 
 def config8(kv, W, torch, dev, args, arena=None, streams=None):
-    """The general builds of the move kernel with both ends in HBM (device arena): gather and scatter of one
+    """Other pool shapes with both ends in HBM (device arena): gather and scatter of one
     batch of random blocks, HIP events around each kernel, against the 8 TB/s peak and against a plain copy of
     the same size whose source / destination is visited in scrambled runs of the pool's chunk length."""
     streams = streams or Streams(torch)
     skw = streams.kw()
     shapes = [
-        ("fp8_scales", "configs[4] shape: fp8 + fp32 scales, L32 H32 D128 B32 (128 KiB chunks, 128-byte scale pieces): two launches, the "
-                       "lean build over the data and the general build over the scale jobs (scatter of the side band through LDS)", W.Geometry(32, 32, 128, 32, "fp8_e4m3", 6144, scales=True), 2048),
-        ("one_kv_head_4KiB_chunks", "a tensor-parallel shard of the 70B shape: bf16 L80 H1 D128 B16 (4 KiB chunks, one piece each: the lean build at its smallest chunk)",
+        ("fp8_scales", "configs[4] shape: fp8 + fp32 scales, L32 H32 D128 B32 (128 KiB chunks, 128-byte scale pieces), the "
+                       "scale jobs at the end of the same launch", W.Geometry(32, 32, 128, 32, "fp8_e4m3", 6144, scales=True), 2048),
+        ("one_kv_head_4KiB_chunks", "a tensor-parallel shard of the 70B shape: bf16 L80 H1 D128 B16 (4 KiB chunks)",
          W.Geometry(80, 1, 128, 16, "bf16", 98304), 24576),
-        ("token_level_256B_chunks", "a token-level pool: bf16 L32 H1 D128 B1 (256-byte chunks, four groups of 16 chunks per workgroup: the small-chunk kernel)",
+        ("token_level_256B_chunks", "a token-level pool: bf16 L32 H1 D128 B1 (256-byte chunks, each lane works out its own)",
          W.Geometry(32, 1, 128, 1, "bf16", 1 << 20), 1 << 18),
     ]
     out = {"config": 8, "peak_gbps": HBM_PEAK_GBS, "kernels": {}}
     warm = torch.empty(8 << 30, dtype=torch.uint8, device=dev)
     kv.kv_bench_copy(warm[4 << 30:].data_ptr(), warm.data_ptr(), 4 << 30, 0, 40)     # memory clocks up
-    builds = {"fp8_scales": "kv_move_kernel<%d,1,0,true,false> + kv_move_kernel<%d,1,0,false,false> (scale jobs)",
-              "one_kv_head_4KiB_chunks": "kv_move_kernel<%d,1,0,true,false>", "token_level_256B_chunks": "kv_move_small_kernel<%d,4,0>"}
+    builds = {"fp8_scales": "kv_wave_kernel<%d,false,true,false>",
+              "one_kv_head_4KiB_chunks": "kv_wave_kernel<%d,false,false,false>", "token_level_256B_chunks": "kv_lane_kernel<%d,false,false>"}
     for name, what, g, nblk in shapes:
         build = builds[name]
         pool = torch.empty(g.pool_bytes, dtype=torch.uint8, device=dev)
