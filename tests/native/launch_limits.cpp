@@ -1,0 +1,192 @@
+// The limits of one launch, checked on the CPU for geometries and list lengths that no test pool could hold.
+//
+// The real launch code (runtime.hip.inc) is compiled with launches that are recorded instead of queued.  For a sweep of
+// geometries it is given lists longer than one launch may carry; every recorded launch must hold what its kernel's
+// 32-bit arithmetic assumes: counts that equal their 64-bit value, divisions by multiplication (FastDiv) that
+// equal plain division up to the largest number the launch divides, a grid whose thread count fits 32 bits, and the
+// launches together exactly the list.  No memory is touched: descriptor pointers are only counted with.
+//
+// usage: launch_limits   (prints "launches ok" and the number of launches looked at)
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#undef hipLaunchKernelGGL
+#define hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, ...) record((grid), (block), __VA_ARGS__)
+
+struct Launch;
+template <class Args>
+void record(dim3 grid, dim3 block, const Args& a);
+
+#include "runtime.hip.inc"
+
+struct Launch {
+  uint64_t grid, threads;
+  HbmArgs a;
+};
+static std::vector<Launch> launches;
+template <class Args>
+void take(uint64_t grid, uint64_t threads, const Args& a) {
+  launches.push_back({grid, threads, a});
+}
+void take(uint64_t, uint64_t, const MoveArgs&) {}
+void take(uint64_t, uint64_t, const DescPack&) {}
+template <class Args>
+void record(dim3 grid, dim3 block, const Args& a) {
+  take(grid.x, block.x, a);
+}
+
+namespace {
+
+long looked_at = 0;
+
+[[noreturn]] void die(const char* what, const kv_pool& p, uint64_t a, uint64_t b) {
+  std::printf("FAILED: %s: %llu, expected %llu (L %d H %d D %d B %d chunk %lld S %lld)\n", what, (unsigned long long)a,
+              (unsigned long long)b, p.cfg.num_layers, p.cfg.num_kv_heads, p.cfg.head_dim, p.cfg.block_size, (long long)p.chunk,
+              (long long)p.S);
+  std::exit(1);
+}
+
+// f divides as plain division does at the largest numbers up to `top` (where the error of the multiplication is largest: the
+// last multiple of d, its neighbour below, and top itself) and at a few others
+void divides(const kv_pool& p, const char* what, const FastDiv& f, uint64_t d, uint64_t top) {
+  const uint64_t last = top / d * d;
+  for (uint64_t n : {top, last, last ? last - 1 : 0, last >= d ? last - d : 0, last > d ? last - d - 1 : 0, top / 2, (uint64_t)0})
+    if ((uint64_t)((uint32_t)n / f) != n / d) die(what, p, (uint32_t)n / f, n / d);
+}
+
+const Desc* const kBase = (const Desc*)(uintptr_t)4096;
+
+void hbm(kv_pool& p, int mode, uint64_t n, bool pm) {
+  launches.clear();
+  launch_hbm(&p, mode, kBase, nullptr, (size_t)n, nullptr, pm, nullptr);
+  const uint64_t L2 = 2 * (uint64_t)p.cfg.num_layers, vpb = (uint64_t)p.block_bytes / 16;
+  uint64_t at = 0;
+  for (size_t i = 0; i < launches.size(); i++) {
+    const HbmArgs& a = launches[i].a;
+    if ((uint64_t)(a.desc - kBase) != at) die("first descriptor of a launch", p, (uint64_t)(a.desc - kBase), at);
+    const uint64_t end = i + 1 < launches.size() ? (uint64_t)(launches[i + 1].a.desc - kBase) : n, m = end - at;
+    uint64_t data;
+    if (pm && mode != 0) {
+      data = L2 * a.ppc * m;
+      if (a.n_plane != m * a.ppc) die("jobs per plane", p, a.n_plane, m * a.ppc);
+      divides(p, "plane of a job", a.per_plane, m * a.ppc, data - 1);
+      divides(p, "chunk of a piece", a.by_ppc, a.ppc, m * a.ppc - 1);
+    } else if (p.hbm_all) {
+      data = (m * vpb + 255) / 256;
+      if (a.n_vec != m * vpb) die("vectors of a launch", p, a.n_vec, m * vpb);
+      divides(p, "block of a vector", a.by_vpb, vpb, m * vpb - 1);
+      divides(p, "chunk of a vector", a.by_vpc, (uint64_t)p.chunk / 16, vpb - 1);
+    } else {
+      data = m * a.ppb;
+      divides(p, "block of a job", a.by_ppb, a.ppb, data - 1);
+      if (p.hbm_wave)
+        divides(p, "chunk of a piece", a.by_ppc, a.ppc, a.ppb - 1);
+      else
+        divides(p, "chunk of a vector", a.by_vpc, (uint64_t)p.chunk / 16, vpb - 1);
+    }
+    if (a.n_data_jobs != data) die("data jobs", p, a.n_data_jobs, data);
+    if (a.n_jobs != data + m * a.side_ppb) die("jobs", p, a.n_jobs, data + m * a.side_ppb);
+    if (a.side_ppb) {
+      divides(p, "block of a side job", a.by_side, a.side_ppb, m * a.side_ppb - 1);
+      divides(p, "head of a scale word", a.by_H, a.H, (uint64_t)a.side_ppb * 256 - 1);
+    }
+    if (launches[i].grid != a.n_jobs && !(pm && mode == 1 && p.max_wgs_device)) die("grid", p, launches[i].grid, a.n_jobs);
+    if (launches[i].grid * launches[i].threads >> 32) die("threads of a launch", p, launches[i].grid * launches[i].threads, 0);
+    at = end;
+    looked_at++;
+  }
+  if (at != n) die("descriptors launched", p, at, n);
+}
+
+void link(kv_pool& p, int mode, uint64_t n, int64_t wgs) {
+  launches.clear();
+  launch_link(&p, mode, kBase, nullptr, (size_t)n, nullptr, wgs, nullptr);
+  const uint64_t vps = (uint64_t)p.S / 16;
+  uint64_t at = 0;
+  for (size_t i = 0; i < launches.size(); i++) {
+    const HbmArgs& a = launches[i].a;
+    if ((uint64_t)(a.desc - kBase) != at) die("first descriptor of a link launch", p, (uint64_t)(a.desc - kBase), at);
+    const uint64_t end = i + 1 < launches.size() ? (uint64_t)(launches[i + 1].a.desc - kBase) : n, m = end - at;
+    uint64_t jobs;
+    if (p.link_all) {
+      jobs = (m * vps + 255) / 256;
+      if (a.n_vec != m * vps) die("vectors of a link launch", p, a.n_vec, m * vps);
+      divides(p, "slot of a vector", a.by_vps, vps, m * vps - 1);
+    } else {
+      jobs = m * ((vps + 255) / 256);
+      divides(p, "slot of a link job", a.by_link, a.link_ppb, jobs - 1);
+    }
+    if (a.n_jobs != jobs) die("link jobs", p, a.n_jobs, jobs);
+    if ((a.n_jobs + launches[i].grid) >> 32) die("numbers the counter hands out", p, a.n_jobs + launches[i].grid, 0);
+    divides(p, "chunk of a vector", a.by_vpc, (uint64_t)p.chunk / 16, vps - 1);
+    if (a.scale_words) divides(p, "head of a scale word", a.by_H, a.H, a.scale_words - 1);
+    if (launches[i].grid < 1 || launches[i].grid > a.n_jobs) die("link grid", p, launches[i].grid, a.n_jobs);
+    if (launches[i].grid * launches[i].threads >> 32) die("threads of a link launch", p, launches[i].grid * launches[i].threads, 0);
+    at = end;
+    looked_at++;
+  }
+  if (at != n) die("descriptors launched on the link", p, at, n);
+}
+
+void geometry(int L, int H, int D, int B, int e, bool scales) {
+  const int64_t chunk = (int64_t)B * H * D * e;
+  if (chunk % 16 || chunk > (1 << 30) || (scales && 2ll * L * H * 4 % 16)) return;  // kv_pool_create refuses these
+  kv_pool p;
+  p.cfg.num_layers = L;
+  p.cfg.num_kv_heads = H;
+  p.cfg.head_dim = D;
+  p.cfg.block_size = B;
+  p.cfg.num_blocks = INT32_MAX;
+  p.chunk = chunk;
+  p.block_bytes = 2 * (int64_t)L * chunk;
+  p.cfg.block_stride = chunk;
+  p.cfg.kv_stride = p.cfg.layer_stride = INT64_MAX / 4;
+  if (scales) {
+    p.cfg.scale_dev = (void*)(uintptr_t)4096;
+    p.block_scale_bytes = 2ll * L * H * 4;
+  }
+  p.S = p.block_bytes + p.block_scale_bytes;
+  static uint32_t counters[64];
+  p.tickets = counters;
+  hbm_setup(&p);
+  auto list = [&](size_t most) { return std::min<uint64_t>(INT32_MAX, 2 * (uint64_t)most + 3); };
+  if (hbm_kernels(&p))
+    for (int mode = 0; mode < 3; mode++) {
+      hbm(p, mode, list(p.hbm_most), false);
+      hbm(p, mode, 1, false);
+      if (mode && p.hbm_wave) hbm(p, mode, list(p.hbm_most), true);
+    }
+  if (p.S < ((int64_t)1 << 34))
+    for (int mode = 0; mode < 2; mode++)
+      for (int64_t wgs : {(int64_t)0, (int64_t)1}) {
+        link(p, mode, list(p.link_most), wgs);
+        link(p, mode, 1, wgs);
+      }
+}
+
+}  // namespace
+
+int main() {
+  {  // the division itself, over its whole range
+    kv_pool none;
+    const uint64_t top = (1ull << 31) - 1;
+    for (uint64_t d = 1; d <= 200000; d++) divides(none, "division", fast_div((uint32_t)d), d, top);
+    for (uint64_t d = 200000; d < (1ull << 30); d += d / 5000 + 1) divides(none, "division", fast_div((uint32_t)d), d, top);
+    for (int b = 1; b <= 30; b++)
+      for (uint64_t d : {(1ull << b) - 1, 1ull << b, (1ull << b) + 1}) divides(none, "division", fast_div((uint32_t)d), d, top);
+  }
+  for (int L : {1, 2, 3, 16, 24, 28, 32, 40, 80, 96})
+    for (int H : {1, 2, 3, 4, 5, 8, 9, 10, 32, 128})
+      for (int D : {8, 16, 64, 65, 72, 80, 96, 112, 120, 128, 192, 256})
+        for (int B : {1, 2, 3, 4, 8, 16, 32, 256})
+          for (int e : {1, 2}) {
+            geometry(L, H, D, B, e, false);
+            if (e == 1) geometry(L, H, D, B, e, true);
+          }
+  geometry(80, 128, 256, 4096, 1, true);    // blocks of 20 GiB
+  geometry(40, 128, 256, 4096, 1, false);   // 10 GiB
+  geometry(64, 129, 257, 2048, 1, true);    // 8.1 GiB, ragged
+  std::printf("launches ok: %ld\n", looked_at);
+  return 0;
+}

@@ -105,6 +105,18 @@ def _build_on_mock(out_dir, name, csrc_dir, flags):
     return exe
 
 
+def test_limits_of_one_launch(tmp_path):
+    """Lists longer than one launch may carry, over geometries that no test pool could hold: what the launch code hands
+    the kernels stays inside their 32-bit arithmetic (see tests/native/launch_limits.cpp)."""
+    if not os.path.exists(CLANGXX):
+        pytest.skip("no host clang++ for the kernel source")
+    exe = str(tmp_path / "launch_limits")
+    subprocess.check_call([CLANGXX, "-std=c++17", "-O2", "-pthread", "-Wno-unused-function", "-I", MOCK, "-I", os.path.join(ROOT, "include"),
+                           "-I", CSRC, "-o", exe, os.path.join(HERE, "native", "launch_limits.cpp"), os.path.join(MOCK, "mockhip.cpp")])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "launches ok" in r.stdout, r.stdout + r.stderr
+
+
 @pytest.fixture(scope="module")
 def mock_driver(tmp_path_factory):
     if not os.path.exists(CLANGXX):
