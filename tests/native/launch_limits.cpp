@@ -159,7 +159,7 @@ void geometry(int L, int H, int D, int B, int e, bool scales) {
     }
   if (p.S < ((int64_t)1 << 34))
     for (int mode = 0; mode < 2; mode++)
-      for (int64_t wgs : {(int64_t)0, (int64_t)1}) {
+      for (int64_t wgs : {(int64_t)0, (int64_t)1, (int64_t)1 << 30, INT64_MAX}) {
         link(p, mode, list(p.link_most), wgs);
         link(p, mode, 1, wgs);
       }
