@@ -589,7 +589,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     } else {
       MoveArgs a;
       int u = 1;
-      grid = build_move_args(p, 2, (size_t)n, nullptr, 0, &a, &u);
+      grid = build_move_args(p, 2, (size_t)n, nullptr, 0, false, &a, &u);
       a.desc = p->na_dev;
       a.use_inl = inline_desc ? 1 : 0;
       if (inline_desc) std::memcpy(a.inl, pack.d, (size_t)n * sizeof(Desc));

@@ -29,7 +29,12 @@ template <class Args>
 void take(uint64_t grid, uint64_t threads, const Args& a) {
   launches.push_back({grid, threads, a});
 }
-void take(uint64_t, uint64_t, const MoveArgs&) {}
+struct MoveLaunch {
+  uint64_t grid, threads;
+  MoveArgs a;
+};
+static std::vector<MoveLaunch> move_launches;
+void take(uint64_t grid, uint64_t threads, const MoveArgs& a) { move_launches.push_back({grid, threads, a}); }
 void take(uint64_t, uint64_t, const DescPack&) {}
 template <class Args>
 void record(dim3 grid, dim3 block, const Args& a) {
@@ -129,6 +134,35 @@ void link(kv_pool& p, int mode, uint64_t n, int64_t wgs) {
   if (at != n) die("descriptors launched on the link", p, at, n);
 }
 
+// A handle under a workgroup cap: launches of 256 lanes within the cap, the data jobs (in either order of the scatter) with
+// the build that has nothing else in it, the scale jobs behind them.
+void capped(kv_pool& p, int64_t cap) {
+  p.max_wgs_device = cap;
+  p.dev_staging = true;
+  if (!p.stream[kEvict]) (void)hipStreamCreateWithFlags(&p.stream[kEvict], hipStreamNonBlocking);
+  const Desc list[3] = {{0, 0}, {1, 1}, {2, 2}};
+  for (int mode = 0; mode < 3; mode++)
+    for (int pm = 0; pm < (mode == 1 && p.chunk >= 4096 ? 2 : 1); pm++) {
+      launches.clear();
+      move_launches.clear();
+      Call c;
+      if (enqueue_kernel(&p, c, mode, list, 3, nullptr, 0, /*sole=*/true, pm == 1) != KV_OK) die("capped launch", p, 0, 0);
+      if (!launches.empty()) die("launches of one-wavefront workgroups under a cap", p, launches.size(), 0);
+      if (move_launches.size() != (p.cfg.scale_dev ? 2u : 1u)) die("launches under a cap", p, move_launches.size(), 1);
+      int64_t at = 0;
+      for (const MoveLaunch& l : move_launches) {
+        if (l.threads != 256 || l.grid > (uint64_t)cap) die("workgroups under a cap", p, l.grid, (uint64_t)cap);
+        if (l.a.first_job != at) die("first job of a capped launch", p, (uint64_t)l.a.first_job, (uint64_t)at);
+        if (&l == &move_launches[0] && (l.a.scale_words || l.a.n_jobs != l.a.n_data_jobs || (l.a.jobs_per_plane > 0) != (pm == 1)))
+          die("data jobs of a capped launch", p, (uint64_t)l.a.n_jobs, (uint64_t)l.a.n_data_jobs);
+        at = l.a.n_jobs;
+        looked_at++;
+      }
+      if (at != move_launches[0].a.n_data_jobs + (p.cfg.scale_dev ? 3 : 0)) die("jobs under a cap", p, (uint64_t)at, 0);
+    }
+  p.max_wgs_device = 0;
+}
+
 void geometry(int L, int H, int D, int B, int e, bool scales) {
   const int64_t chunk = (int64_t)B * H * D * e;
   if (chunk % 16 || chunk > (1 << 30) || (scales && 2ll * L * H * 4 % 16)) return;  // kv_pool_create refuses these
@@ -157,6 +191,7 @@ void geometry(int L, int H, int D, int B, int e, bool scales) {
       hbm(p, mode, 1, false);
       if (mode && p.hbm_wave) hbm(p, mode, list(p.hbm_most), true);
     }
+  if ((L == 2 || L == 3) && B <= 16) capped(p, 3);
   if (p.S < ((int64_t)1 << 34))
     for (int mode = 0; mode < 2; mode++)
       for (int64_t wgs : {(int64_t)0, (int64_t)1, (int64_t)1 << 30, INT64_MAX}) {
