@@ -153,7 +153,7 @@ void capped(kv_pool& p, int64_t cap) {
       for (const MoveLaunch& l : move_launches) {
         if (l.threads != 256 || l.grid > (uint64_t)cap) die("workgroups under a cap", p, l.grid, (uint64_t)cap);
         if (l.a.first_job != at) die("first job of a capped launch", p, (uint64_t)l.a.first_job, (uint64_t)at);
-        if (&l == &move_launches[0] && (l.a.scale_words || l.a.n_jobs != l.a.n_data_jobs || (l.a.jobs_per_plane > 0) != (pm == 1)))
+        if (&l == &move_launches[0] && (l.a.scale_words || l.a.n_jobs != l.a.n_data_jobs || (l.a.per_plane > 0) != (pm == 1)))
           die("data jobs of a capped launch", p, (uint64_t)l.a.n_jobs, (uint64_t)l.a.n_data_jobs);
         at = l.a.n_jobs;
         looked_at++;

@@ -227,6 +227,10 @@ KERNEL_MUTANTS = [
      "  auto plane_of = [&](int k) { return (int64_t)(k >> 1) * a.ls + (int64_t)((k & 1) ^ 1) * a.ks; };"),
     ("scale_jobs_launched_from_the_wrong_job", "    side.first_job = a.n_data_jobs;", "    side.first_job = a.n_data_jobs + 1;"),
     ("plane_by_plane_scatter_in_the_wrong_plane", "        k = (int)(job / a.per_plane);", "        k = (int)(job / a.per_plane) ^ 1;"),
+    ("one_wavefront_scatter_in_the_wrong_plane", "  if (PM) {\n    k = (int)(job / a.per_plane);", "  if (PM) {\n    k = (int)(job / a.per_plane) ^ 1;"),
+    ("one_wavefront_chunk_of_the_wrong_plane", "    k = (int)(rem / a.by_ppc);", "    k = (int)(rem / a.by_ppc) ^ 1;"),
+    ("scale_jobs_of_a_whole_launch_from_the_wrong_job", "    a.first_job = a.n_data_jobs;\n    a.n_jobs = a.first_job + m", "    a.first_job = a.n_data_jobs + 1;\n    a.n_jobs = a.first_job + m"),
+    ("last_lanes_of_a_block_in_the_next_one", "    v = v < a.vpb ? v : a.vpb - 1;", "    v = v < a.vpb ? v : a.vpb;"),
     ("half_the_scale_vectors", "      const int vecs = a.scale_words >> 2;", "      const int vecs = a.scale_words >> 3;"),
     ("staging_slot_of_the_wrong_block", "        dst = a.contig + (int64_t)(uint32_t)ds.b * a.S + (int64_t)k * a.chunk;",
      "        dst = a.contig + (int64_t)(uint32_t)ds.a * a.S + (int64_t)k * a.chunk;"),
