@@ -567,11 +567,11 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   hipEvent_t callers = (hipEvent_t)wait_event;
   if (callers) HIPCHK(p, hipStreamWaitEvent(st, callers, 0));
   if (n > 0) {
-    // Up to kInlineDescMax descriptors travel inside the arguments of the move itself.  More go into the fixed array
+    // Short lists travel inside the arguments of the move itself.  Longer ones go into the fixed array
     // in batches that travel as kernel arguments: nothing on the host has to outlive this call, so it never waits for
     // an earlier one.  The array keeps the previous call's descriptors: [0, n) is overwritten here, in stream order
     // behind the previous call's kernel, and nothing beyond n is read.
-    const bool inline_desc = n <= kInlineDescMax;
+    const bool hbm = hbm_kernels(p), inline_desc = n <= (hbm ? kInlineDescMax : kMoveDescMax);
     (void)hipGetLastError();
     DescPack pack;
     for (int64_t at = 0; at < n; at += kDescPack) {
@@ -582,7 +582,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     HIPCHK(p, hipGetLastError());
     (void)hipGetLastError();
     int grid;
-    if (hbm_kernels(p)) {
+    if (hbm) {
       const bool pm = inline_desc && plane_by_plane_move(p, (size_t)n);  // (a longer list would need a buffer to be sorted in)
       if (pm) std::sort(pack.d, pack.d + n, [](const Desc& x, const Desc& y) { return x.b < y.b; });
       grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, pm, st);

@@ -21,20 +21,20 @@ void record(dim3 grid, dim3 block, const Args& a);
 #include "runtime.hip.inc"
 
 struct Launch {
-  uint64_t grid, threads;
+  uint64_t grid, threads, bytes;
   HbmArgs a;
 };
 static std::vector<Launch> launches;
 template <class Args>
 void take(uint64_t grid, uint64_t threads, const Args& a) {
-  launches.push_back({grid, threads, a});
+  launches.push_back({grid, threads, sizeof(Args), a});
 }
 struct MoveLaunch {
-  uint64_t grid, threads;
+  uint64_t grid, threads, bytes;
   MoveArgs a;
 };
 static std::vector<MoveLaunch> move_launches;
-void take(uint64_t grid, uint64_t threads, const MoveArgs& a) { move_launches.push_back({grid, threads, a}); }
+void take(uint64_t grid, uint64_t threads, const MoveArgs& a) { move_launches.push_back({grid, threads, sizeof(a), a}); }
 void take(uint64_t, uint64_t, const DescPack&) {}
 template <class Args>
 void record(dim3 grid, dim3 block, const Args& a) {
@@ -163,6 +163,42 @@ void capped(kv_pool& p, int64_t cap) {
   p.max_wgs_device = 0;
 }
 
+// A list inside the kernel arguments: short ones leave the arguments (with 256 hidden bytes) below 1 KiB, and a list beyond
+// what they hold is uploaded (a short move's beyond those 1 KiB), also where a knob selects kv_move_kernel.
+void arguments() {
+  kv_pool p;
+  p.cfg.num_layers = 2;
+  p.cfg.num_kv_heads = 1;
+  p.cfg.num_blocks = 1000;
+  p.chunk = 4096;
+  p.cfg.block_stride = 4096;
+  p.cfg.kv_stride = p.cfg.layer_stride = INT64_MAX / 4;
+  p.S = p.block_bytes = 16384;
+  static uint32_t counters[64];
+  p.tickets = counters;
+  hbm_setup(&p);
+  (void)hipStreamCreateWithFlags(&p.stream[kEvict], hipStreamNonBlocking);
+  if (grow_ring(&p, 4096) != KV_OK) die("ring", p, 0, 0);
+  std::vector<Desc> list(449, Desc{0, 1});
+  for (int64_t cap : {0, 4})
+    for (int kind = 0; kind < 3; kind++)
+      for (int mode = 0; mode < (kind == 0 ? 3 : 2); mode++)
+        for (size_t n : {1, 8, 9, 60, 61, 448, 449}) {
+          p.max_wgs_device = cap;
+          launches.clear();
+          move_launches.clear();
+          Call c;
+          const size_t ring = p.ring_head;
+          if (enqueue_kernel(&p, c, mode, list.data(), n, nullptr, kind, /*sole=*/true) != KV_OK) die("launch", p, n, 0);
+          const bool uploaded = p.ring_head != ring, knob = cap && kind != 1;
+          const uint64_t bytes = knob ? move_launches.at(0).bytes : launches.at(0).bytes;
+          const bool inside = knob ? move_launches[0].a.use_inl : bytes > sizeof(HbmArgs);
+          if (inside == uploaded || inside != (n <= (knob ? 8u : mode == 2 ? 60u : 448u))) die("a list inside the arguments", p, n, inside);
+          if (bytes > (n <= 60 || knob || uploaded ? 1024u - 256u : 4096u)) die("bytes of arguments", p, bytes, n);
+          looked_at++;
+        }
+}
+
 void geometry(int L, int H, int D, int B, int e, bool scales) {
   const int64_t chunk = (int64_t)B * H * D * e;
   if (chunk % 16 || chunk > (1 << 30) || (scales && 2ll * L * H * 4 % 16)) return;  // kv_pool_create refuses these
@@ -203,6 +239,7 @@ void geometry(int L, int H, int D, int B, int e, bool scales) {
 }  // namespace
 
 int main() {
+  arguments();
   {  // the division itself, over its whole range
     kv_pool none;
     const uint64_t top = (1ull << 31) - 1;
