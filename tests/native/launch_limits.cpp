@@ -238,8 +238,22 @@ void geometry(int L, int H, int D, int B, int e, bool scales) {
 
 }  // namespace
 
+// Phases of kv_evict_and_load: small ones are for the host link, where the first and the last run alone.
+void phases() {
+  kv_pool p;
+  const int64_t MiB = 1 << 20;
+  for (int64_t larger : {1 * MiB, 32 * MiB, 256 * MiB, 320 * MiB, 4096 * MiB}) {
+    p.dev_staging = true;
+    if (phase_of(&p, larger) != 256 * MiB) die("phase in HBM", p, (uint64_t)phase_of(&p, larger), (uint64_t)larger);
+    p.dev_staging = false;
+    const int64_t host = phase_of(&p, larger);
+    if (host < 16 * MiB || host > 64 * MiB || (host > 16 * MiB && host > larger / 8)) die("phase over the link", p, (uint64_t)host, (uint64_t)larger);
+  }
+}
+
 int main() {
   arguments();
+  phases();
   {  // the division itself, over its whole range
     kv_pool none;
     const uint64_t top = (1ull << 31) - 1;
