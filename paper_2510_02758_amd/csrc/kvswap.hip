@@ -464,7 +464,13 @@ int kv_evict_and_load(kv_pool* p, int32_t n_out, const uint64_t* out_ids, const 
       // one side moves nothing: the plans are committed, enqueue them the ordinary way
       rc = swap_out_common(p, 1, po, t0, wait_event);
       if (rc) return rc;
-      if (pi.desc.empty() && !wait_event) return KV_OK;
+      p->last_plan = pi.desc;  // (swap_out_common has left the eviction's)
+      if (pi.desc.empty() && !wait_event) {
+        p->plan_stats = kv_stats{};
+        fill_plan_stats(p, &p->plan_stats, 3, 0, t1 - t0);
+        p->last_instant = true;
+        return KV_OK;
+      }
       const uint64_t dep_in = cross_stream(p, kLoad, pi.wait_out_seq);
       Call* c = nullptr;
       rc = open_call(p, kLoad, 3, dep_in, wait_event, 1, pi.desc, &c);

@@ -6,6 +6,8 @@
 // equal plain division up to the largest number the launch divides, a grid whose thread count fits 32 bits, and the
 // launches together exactly the list.  No memory is touched: descriptor pointers are only counted with.
 //
+// A check of what kv_evict_and_load reports sits beside them, on a handle whose launches are recorded.
+//
 // usage: launch_limits   (prints "launches ok" and the number of launches looked at)
 #include <hip/hip_runtime.h>
 
@@ -14,18 +16,17 @@
 #undef hipLaunchKernelGGL
 #define hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, ...) record((grid), (block), __VA_ARGS__)
 
-struct Launch;
-template <class Args>
-void record(dim3 grid, dim3 block, const Args& a);
+template <class... Args>
+void record(dim3 grid, dim3 block, const Args&... args);
 
-#include "runtime.hip.inc"
+#include "kvswap.hip"
 
 struct Launch {
   uint64_t grid, threads, bytes;
   HbmArgs a;
 };
 static std::vector<Launch> launches;
-template <class Args>
+template <class Args, class = std::enable_if_t<std::is_base_of_v<HbmArgs, Args>>>
 void take(uint64_t grid, uint64_t threads, const Args& a) {
   launches.push_back({grid, threads, sizeof(Args), a});
 }
@@ -35,10 +36,10 @@ struct MoveLaunch {
 };
 static std::vector<MoveLaunch> move_launches;
 void take(uint64_t grid, uint64_t threads, const MoveArgs& a) { move_launches.push_back({grid, threads, sizeof(a), a}); }
-void take(uint64_t, uint64_t, const DescPack&) {}
-template <class Args>
-void record(dim3 grid, dim3 block, const Args& a) {
-  take(grid.x, block.x, a);
+void take(...) {}
+template <class... Args>
+void record(dim3 grid, dim3 block, const Args&... args) {
+  if constexpr (sizeof...(args) == 1) take((uint64_t)grid.x, (uint64_t)block.x, args...);
 }
 
 namespace {
@@ -251,8 +252,42 @@ void phases() {
   }
 }
 
+// kv_evict_and_load whose eviction or load moves nothing: the plan and the statistics afterwards are still the load's.
+void evict_and_load_with_an_empty_side() {
+  kv_pool none;
+  void *pool = nullptr, *arena = nullptr;
+  kv_pool_config kc{};
+  kc.struct_size = sizeof(kc);
+  kc.num_layers = 1; kc.num_kv_heads = 1; kc.head_dim = 64; kc.block_size = 8; kc.dtype = KV_F16; kc.num_blocks = 16;
+  kc.block_stride = 1024; kc.kv_stride = 16 * 1024; kc.layer_stride = 32 * 1024;
+  (void)hipMalloc(&pool, 32 * 1024);
+  (void)hipMalloc(&arena, 16 * 2048);
+  kc.pool_dev = pool; kc.staging_host = arena; kc.staging_bytes = 16 * 2048; kc.flags = KV_STAGING_DEVICE;
+  kv_pool* p = nullptr;
+  if (kv_pool_create(&kc, &p) != KV_OK) die("kv_pool_create", none, 0, 0);
+  const uint64_t id[4] = {1, 2, 3, 4};
+  const int32_t blk[3] = {5, 6, 7}, two[2] = {0, 2}, nothing[2] = {0, 0}, tok[1] = {16}, zero[1] = {0};
+  if (kv_swap_out(p, 1, &id[0], two, blk, tok, nullptr) != KV_OK || kv_swap_out(p, 1, &id[1], nothing, blk, zero, nullptr) != KV_OK)
+    die("kv_swap_out", none, 0, 0);
+  kv_stats st;
+  // an eviction of nothing beside a load of two blocks
+  if (kv_evict_and_load(p, 1, &id[2], nothing, blk, zero, 1, &id[0], two, blk, 0, nullptr) != KV_OK) die("kv_evict_and_load", none, 0, 0);
+  st.struct_size = sizeof(st);
+  if (kv_last_plan(p, nullptr, nullptr, 0) != 2) die("plan after an empty eviction", none, (uint64_t)kv_last_plan(p, nullptr, nullptr, 0), 2);
+  if (kv_last_stats(p, &st) != KV_OK || st.op != 3 || st.blocks != 2) die("statistics after an empty eviction", none, (uint64_t)st.blocks, 2);
+  // an eviction of two blocks beside a load of nothing
+  if (kv_evict_and_load(p, 1, &id[3], two, blk, tok, 1, &id[1], nothing, blk, 0, nullptr) != KV_OK) die("kv_evict_and_load", none, 1, 0);
+  st.struct_size = sizeof(st);
+  if (kv_last_plan(p, nullptr, nullptr, 0) != 0) die("plan after an empty load", none, (uint64_t)kv_last_plan(p, nullptr, nullptr, 0), 0);
+  if (kv_last_stats(p, &st) != KV_OK || st.op != 3 || st.blocks != 0) die("statistics after an empty load", none, (uint64_t)st.blocks, 0);
+  if (kv_pool_destroy(p) != KV_OK) die("kv_pool_destroy", none, 0, 0);
+  (void)hipFree(pool);
+  (void)hipFree(arena);
+}
+
 int main() {
   arguments();
+  evict_and_load_with_an_empty_side();
   phases();
   {  // the division itself, over its whole range
     kv_pool none;
