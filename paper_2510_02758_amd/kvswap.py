@@ -128,13 +128,13 @@ _I32, _U64 = np.dtype(np.int32), np.dtype(np.uint64)
 
 
 def _i32a(a):
-    if type(a) is np.ndarray and a.dtype == _I32 and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.ndim and a.dtype == _I32 and a.flags.c_contiguous:
         return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.int32))
 
 
 def _u64a(a):
-    if type(a) is np.ndarray and a.dtype == _U64 and a.flags.c_contiguous:
+    if type(a) is np.ndarray and a.ndim and a.dtype == _U64 and a.flags.c_contiguous:
         return a
     return np.ascontiguousarray(np.asarray(a, dtype=np.uint64))
 
@@ -154,7 +154,7 @@ def _rows_ok(n, offsets, block_ids, *per_request):
     for a in per_request:
         if len(a) != n:
             return False
-    return n == 0 or offsets[n] <= len(block_ids)
+    return n == 0 or (offsets[n] if offsets.ndim == 1 else offsets.max()) <= len(block_ids)
 
 
 def kv_strerror(code):

@@ -430,6 +430,24 @@ def test_duplicate_checks_on_a_pool_of_millions_of_blocks():
     kp.close()
 
 
+def test_arrays_the_binding_takes():
+    """Scalars, lists, one number in an array without dimensions, columns, strided and byte-swapped arrays: whatever numpy
+    turns into the argument's type is taken as one row after the other."""
+    g = W.Geometry(1, 1, 64, 8, "f16", 16)
+    kp = kv.KVPool(g, flags=kv.KV_PLAN_ONLY, staging_bytes=16 * g.S)
+    for src, dst in ((3, 5), (np.int64(3), np.int32(5)), (np.array(3, np.int32), np.array(5, np.int32)), ([3], (5,))):
+        assert kp.move_blocks(src, dst) == kv.KV_OK, (src, dst)
+        assert [int(x[0]) for x in kp.last_plan()] == [3, 5]
+    ids, blocks, tokens = np.arange(8, dtype=np.uint64)[::4], np.arange(12, dtype=np.int32)[::3], np.array([16, 9], ">i4")
+    for off in ([0, 2, 4], np.array([[0], [2], [4]], np.int32), np.array([[0, 2], [4, 4], [4, 4]], np.int32)):
+        assert kp.swap_out(ids, off, blocks, tokens) == kv.KV_OK, off
+        assert kp.last_plan()[0].tolist() == [0, 3, 6, 9]
+        assert kp.swap_in(ids, off, blocks) == kv.KV_OK, off
+    assert kp.swap_out(np.array(7, np.uint64), [0, 1], np.array(2, np.int32), np.array(8, np.int32)) == kv.KV_OK
+    assert kp.swap_out([8], [0, 5], blocks, [40]) == kv.KV_EINVAL          # more than the block ids given
+    kp.close()
+
+
 def test_binding_fails_loudly_without_the_library(tmp_path):
     """No fallback path: a copy of the package without libkvswap.so must refuse to import."""
     import shutil
