@@ -75,6 +75,9 @@ typedef mockhip::Event* hipEvent_t;
 #define __shared__
 #define __restrict__
 inline void __syncthreads() { mockhip::barrier(); }
+// One lane runs at a time: plain reads and writes.
+inline unsigned atomicAdd(unsigned* p, unsigned v) { const unsigned old = *p; *p = old + v; return old; }
+inline unsigned atomicExch(unsigned* p, unsigned v) { const unsigned old = *p; *p = v; return old; }
 
 hipError_t hipGetLastError();
 hipError_t hipGetDevice(int* dev);

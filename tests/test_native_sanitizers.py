@@ -231,6 +231,10 @@ KERNEL_MUTANTS = [
     ("one_wavefront_chunk_of_the_wrong_plane", "    k = (int)(rem / a.by_ppc);", "    k = (int)(rem / a.by_ppc) ^ 1;"),
     ("scale_jobs_of_a_whole_launch_from_the_wrong_job", "    a.first_job = a.n_data_jobs;\n    a.n_jobs = a.first_job + m", "    a.first_job = a.n_data_jobs + 1;\n    a.n_jobs = a.first_job + m"),
     ("last_lanes_of_a_block_in_the_next_one", "    v = v < a.vpb ? v : a.vpb - 1;", "    v = v < a.vpb ? v : a.vpb;"),
+    ("job_counter_not_zeroed_for_the_next_launch", "    atomicExch(a.ticket, 0u);", ""),
+    ("count_of_workgroups_that_left_not_zeroed", "    atomicExch(a.ticket + 1, 0u);", ""),
+    ("counter_hands_out_a_job_less", "return gridDim.x + atomicAdd(a.ticket, 1u);", "return gridDim.x + 1 + atomicAdd(a.ticket, 1u);"),
+    ("link_job_of_the_wrong_slot", "v0 = (job - d * a.link_ppb) * 256;", "v0 = (job - d * a.link_ppb) * 255;"),
     ("half_the_scale_vectors", "      const int vecs = a.scale_words >> 2;", "      const int vecs = a.scale_words >> 3;"),
     ("staging_slot_of_the_wrong_block", "        dst = a.contig + (int64_t)(uint32_t)ds.b * a.S + (int64_t)k * a.chunk;",
      "        dst = a.contig + (int64_t)(uint32_t)ds.a * a.S + (int64_t)k * a.chunk;"),
