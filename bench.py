@@ -345,14 +345,14 @@ def headline(kv, W, BC, torch, dev, args, arena, streams):
                           "frac": r4(moved_bytes["out"] / out_k / 1e6 / 64.0), "launch_ms": r2(out_k / steps),
                           "bytes_per_launch": int(moved_bytes["out"] / steps), "measured_peak": r2(link_d2h),
                           "frac_of_measured_peak": r4(moved_bytes["out"] / out_k / 1e6 / link_d2h)},
-        "roofline_gather": {"bound": "hbm", "kernel": "kv_wave_kernel<0,false,false,false> (gather, both ends in HBM)",
+        "roofline_gather": {"bound": "hbm", "kernel": "kv_wave_kernel<0,false,false> (gather, both ends in HBM)",
                             "achieved": round(gather_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": r4(gather_gbs / HBM_PEAK_GBS), "traffic": traffic("gather"),
                             "launch_ms": r3(gather_ms), "bytes_per_launch": int(moved_bytes["gather"] / steps),
                             "measured_gathered_copy_ceiling_gbps": round(gather_ceiling, 1)},
         "roofline": {"bound": "hbm",
-                     "kernel": ("kv_wave_kernel<1,true,false,false> (scatter plane by plane, both ends in HBM)" if plane_major
-                                else "kv_wave_kernel<1,false,false,false> (scatter block by block, both ends in HBM)"),
+                     "kernel": ("kv_wave_kernel<1,true,false> (scatter plane by plane, both ends in HBM)" if plane_major
+                                else "kv_wave_kernel<1,false,false> (scatter block by block, both ends in HBM)"),
                      "achieved": round(scatter_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": r4(scatter_gbs / HBM_PEAK_GBS),
                      "traffic": traffic("scatter_plane_by_plane" if plane_major else "scatter_block_by_block"),

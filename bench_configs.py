@@ -830,8 +830,8 @@ def config8(kv, W, torch, dev, args, arena=None, streams=None):
     out = {"config": 8, "peak_gbps": HBM_PEAK_GBS, "kernels": {}}
     warm = torch.empty(8 << 30, dtype=torch.uint8, device=dev)
     kv.kv_bench_copy(warm[4 << 30:].data_ptr(), warm.data_ptr(), 4 << 30, 0, 40)     # memory clocks up
-    builds = {"fp8_scales": "kv_wave_kernel<%d,false,true,false>",
-              "one_kv_head_4KiB_chunks": "kv_wave_kernel<%d,false,false,false>", "token_level_256B_chunks": "kv_lane_kernel<%d,false,false>"}
+    builds = {"fp8_scales": "kv_wave_kernel<%d,false,true>",
+              "one_kv_head_4KiB_chunks": "kv_wave_kernel<%d,false,false>", "token_level_256B_chunks": "kv_lane_kernel<%d,false,false>"}
     for name, what, g, nblk in shapes:
         build = builds[name]
         pool = torch.empty(g.pool_bytes, dtype=torch.uint8, device=dev)

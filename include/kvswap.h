@@ -242,7 +242,8 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
                    void* wait_event);
 
 /* kv_move_blocks for callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same arguments, same result in the pool, same kernel.  The call makes no hipMalloc,
+ * that forbid hipMalloc.  Same arguments, same result in the pool, the same kernels (a list of more than 448 blocks is
+ * not sorted first, where kv_move_blocks may sort it to be faster).  The call makes no hipMalloc,
  * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: up to 448 descriptors travel inside
  * the arguments of the move kernel, longer lists inside the arguments of small fill launches (448 per launch) into a
  * fixed device array that is part of the library's code object (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB

@@ -530,8 +530,9 @@ KV_CATCH(p)
 
 // kv_move_blocks for callers that cannot allocate.  Uses only what kv_pool_create set up: no hipMalloc, hipFree,
 // hipHostMalloc, event or stream creation, and no host heap either (the descriptors travel inside kernel
-// arguments, duplicates are found with the handle's bitmap).  The kernel is the one kv_move_blocks launches; a list
-// that its arguments do not hold is read from the library's fixed device array instead of the growable ring.
+// arguments, duplicates are found with the handle's bitmap).  The kernel is the one kv_move_blocks launches, except that a
+// list its arguments do not hold stays in the caller's order (there is no buffer to sort it in), where kv_move_blocks may go
+// plane by plane; it is read from the library's fixed device array instead of the growable ring.
 int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t* dst_ids, void* wait_event) try {
   if (!p) return KV_EINVAL;
   KV_ENTER(p);
@@ -589,7 +590,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     (void)hipGetLastError();
     int grid;
     if (hbm) {
-      const bool pm = inline_desc && plane_by_plane_move(p, (size_t)n);  // (a longer list would need a buffer to be sorted in)
+      const bool pm = inline_desc && plane_by_plane_move(p, (size_t)n);
       if (pm) std::sort(pack.d, pack.d + n, [](const Desc& x, const Desc& y) { return x.b < y.b; });
       grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, pm, st);
     } else {
