@@ -43,7 +43,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 # profiles/kv_move_kernel_llama70b_waves.md, whose table holds these same numbers; tests/test_host_logic.py
 # compares the two).  KiB per block of 5 120 KiB: (read, written).
 MEASURED_KIB_PER_BLOCK = {"gather": (5120.1, 5119.8), "scatter_block_by_block": (5120.1, 5119.8),
-                          "scatter_plane_by_plane": (5140.0, 5119.8)}
+                          "scatter_plane_by_plane": (5140.1, 5119.8)}
 TRAFFIC_SOURCE = "profiles/kv_move_kernel_llama70b_waves.md"
 
 
