@@ -114,3 +114,44 @@ def test_lists_longer_than_the_kernel_arguments(gpu):
             gpu_lib._pull()
             assert np.array_equal(a.pool, b.pool), (n, flags, "move")
             gpu_lib.close()
+
+
+@pytest.mark.parametrize("n", [60, 61])
+def test_lists_at_the_end_of_the_short_argument_block(gpu, n):
+    """60 descriptors leave the arguments below 1 KiB, 61 take the long block, or an upload where they are a small move."""
+    g = W.Geometry(1, 1, 64, 8, "bf16", 200)
+    perm = np.random.default_rng(n).permutation(g.N).astype(np.int32)
+    for flags in (kv.KV_STAGING_DEVICE, kv.KV_PATH_ZEROCOPY, kv.KV_PATH_DMA):
+        a, b = (HostPool(g, 0xB0F, "layer", slots=n) for _ in range(2))
+        ora, gpu_lib = a.oracle(), GpuAdapter(b, flags, bounce_slots=n)
+        for lib in (ora, gpu_lib):
+            assert lib.swap_out([1], [0, n], perm[:n], [n * g.B]) == ko.OK
+            assert lib.swap_in([1], [0, n], perm[n:2 * n]) == ko.OK
+            assert lib.move_blocks(perm[n:2 * n], perm[2 * n:3 * n]) == ko.OK
+        assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), flags
+        assert ora.move_blocks(perm[2 * n:3 * n], perm[:n]) == ko.OK
+        gpu_lib._push()
+        assert gpu_lib.kp.move_blocks_noalloc(perm[2 * n:3 * n], perm[:n]) == kv.KV_OK
+        gpu_lib._pull()
+        assert np.array_equal(a.pool, b.pool), (flags, "move without allocation")
+        gpu_lib.close()
+
+
+@pytest.mark.parametrize("name", ["1KiB", "9KiB", "1040B", "fp8_4KiB_wide", "fp8_48B"])
+def test_workgroup_cap(gpu, name):
+    """Handles under KV_TUNE_MAX_WGS_DEVICE: lists inside the arguments and uploaded, both orders of the scatter."""
+    g = GEOMS[name]
+    rng = np.random.default_rng(5)
+    for n, order in ((8, 0), (9, 0), (g.N // 3, 2)):
+        perm = rng.permutation(g.N).astype(np.int32)
+        src, dst, mid = perm[:n], perm[n:2 * n], perm[2 * n:3 * n]
+        tune = ((kv.KV_TUNE_MAX_WGS_DEVICE, 3),) + (((kv.KV_TUNE_SCATTER_ORDER, order),) if order else ())
+        a, b = (HostPool(g, 0xB10 + n, "padded", slots=n + 1) for _ in range(2))
+        ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE, tune=tune)
+        for lib in (ora, gpu_lib):
+            assert lib.swap_out([7], [0, n], src, [n * g.B]) == ko.OK
+            assert lib.swap_in([7], [0, n], dst) == ko.OK
+            assert lib.move_blocks(dst, mid) == ko.OK
+        assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), (name, n, order)
+        assert not g.scales or np.array_equal(a.scale, b.scale), (name, n, order)
+        gpu_lib.close()
