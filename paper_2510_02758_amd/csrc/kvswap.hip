@@ -103,6 +103,54 @@ void tickets_give_back(kv_pool* p, bool drained) {
 }
 }  // namespace
 
+// ---- the words by which one stream tells the other that a launch has finished ----
+// Signal memory (the only kind that the command processor waits on), two words per handle.  Words are never freed, since a
+// stream may have waited on them: a handle hands its own back when its streams are drained, with the newest number stored
+// in it, and the next handle on that GPU goes on from there.  A process holds as many as it had handles at a time.
+namespace {
+struct DoneWord {
+  uint64_t* at;
+  uint64_t last;
+};
+std::mutex g_done_mu;
+std::vector<DoneWord> g_done_free[kMaxDevices];
+size_t g_done_taken[kMaxDevices] = {};
+constexpr int kDoneBatch = 8;  // taken at a time: 7 to 30 us each, in front of the first of four handles
+
+// Leaves the handle without words, i.e. with event waits, where the GPU has none to give.
+void done_words_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
+  std::lock_guard<std::mutex> g(g_done_mu);
+  std::vector<DoneWord>& spare = g_done_free[p->device];
+  if (spare.size() < 2) {
+    g_done_taken[p->device] += kDoneBatch;
+    spare.reserve(g_done_taken[p->device] + kDoneBatch);  // giving back does not allocate
+    for (int i = 0; i < kDoneBatch; i++) {
+      DoneWord w{};
+      if (hipExtMallocWithFlags((void**)&w.at, sizeof(uint64_t), hipMallocSignalMemory) != hipSuccess || !w.at) {
+        (void)hipGetLastError();
+        break;
+      }
+      w.last = *(volatile uint64_t*)w.at;
+      if (w.last < 1ull << 62) spare.push_back(w);
+    }
+  }
+  if (spare.size() < 2) return;
+  for (int s = 0; s < 2; s++) {
+    p->done_word[s] = spare.back().at;
+    p->done_last[s] = p->done_waited[1 - s] = spare.back().last;
+    spare.pop_back();
+  }
+}
+
+void done_words_give_back(kv_pool* p, bool drained) {
+  std::lock_guard<std::mutex> g(g_done_mu);
+  for (int s = 0; s < 2; s++) {
+    if (p->done_word[s] && drained) g_done_free[p->device].push_back({p->done_word[s], p->done_last[s]});
+    p->done_word[s] = nullptr;
+  }
+}
+}  // namespace
+
 // Everything kv_move_blocks_noalloc will need, taken once when the handle is created: the address of the
 // descriptor array on this GPU, two events and the duplicate bitmap.
 static int noalloc_setup(kv_pool* p) {
@@ -261,6 +309,7 @@ int kv_pool_create(const kv_pool_config* cfg, kv_pool** out) {
     }
     if (!rc) rc = noalloc_setup(p);
     if (!rc && !p->dev_staging) rc = tickets_setup(p);
+    if (!rc) done_words_setup(p);
     if (rc) {
       kv_pool_destroy(p);
       return rc;
@@ -284,6 +333,7 @@ int kv_pool_destroy(kv_pool* p) try {
     if (p->ring_host) (void)hipHostFree(p->ring_host);
     if (p->ring_dev) (void)hipFree(p->ring_dev);
     tickets_give_back(p, rc == KV_OK && !p->broken);
+    done_words_give_back(p, rc == KV_OK && !p->broken);
     if (p->na_fence_ev) (void)hipEventDestroy(p->na_fence_ev);
     if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
     for (int s = 0; s < 2; s++)

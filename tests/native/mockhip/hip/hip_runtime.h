@@ -21,6 +21,9 @@ typedef int hipError_t;
 enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600 };
 enum { hipStreamNonBlocking = 1 };
 enum { hipHostMallocDefault = 0 };
+enum { hipMallocSignalMemory = 2 };
+enum { hipStreamWaitValueGte = 0 };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
 enum hipMemoryType { hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2 };
 typedef void* hipDeviceptr_t;
@@ -92,6 +95,12 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned flags);
 hipError_t hipStreamDestroy(hipStream_t s);
 hipError_t hipStreamSynchronize(hipStream_t s);
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
+// A wait for a value holds its stream back until the word at `p` is at least `value`; the word is compared whenever the
+// executor looks at the stream, as the command processor does.
+hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned flags, uint64_t mask);
+hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned flags);
+hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned flags);
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);  // nothing is captured here
 hipError_t hipEventCreate(hipEvent_t* e);
 hipError_t hipEventDestroy(hipEvent_t e);
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s);

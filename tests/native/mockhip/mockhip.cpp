@@ -21,10 +21,11 @@ struct Event {
   double t = 0;            // clock value when that happened
 };
 struct Op {
-  int kind;  // 0 function, 1 record, 2 wait
+  int kind;  // 0 function, 1 record, 2 wait, 3 wait for a value
   std::function<void()> fn;
   Event* ev;
-  uint64_t gen;
+  uint64_t gen;  // generation of the event, or the value
+  const volatile uint64_t* word = nullptr;
 };
 struct Stream {
   std::deque<Op> q;
@@ -66,6 +67,7 @@ static bool injected() {
 static bool runnable(Stream* s) {
   if (s->q.empty()) return false;
   const Op& o = s->q.front();
+  if (o.kind == 3) return *o.word >= o.gen;
   return o.kind != 2 || o.ev->completed >= o.gen;
 }
 
@@ -262,6 +264,33 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   if (e->recorded == 0) return hipSuccess;  // never recorded: nothing to wait for
   S(s)->q.push_back({2, nullptr, e, e->recorded});
   progress();
+  return hipSuccess;
+}
+hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned, uint64_t) {
+  API_LOCK;
+  if (injected()) return fail_code;
+  S(s)->q.push_back({3, nullptr, nullptr, value, (const volatile uint64_t*)p});
+  progress();
+  return hipSuccess;
+}
+hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned) {
+  API_LOCK;
+  if (injected()) return fail_code;
+  push_fn(s, [=]() { *(volatile uint64_t*)p = value; });
+  return hipSuccess;
+}
+// Signal memory is never freed by the library: it is kept in a list here, for the leak checker.
+hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned) {
+  API_LOCK;
+  n_resource++;
+  static std::deque<uint64_t> words;
+  if (n != sizeof(uint64_t)) return last_error = hipErrorInvalidValue;
+  words.push_back(1);
+  *p = &words.back();
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* status) {
+  *status = hipStreamCaptureStatusNone;
   return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t* e) {

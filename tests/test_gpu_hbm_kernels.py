@@ -155,3 +155,35 @@ def test_workgroup_cap(gpu, name):
         assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), (name, n, order)
         assert not g.scales or np.array_equal(a.scale, b.scale), (name, n, order)
         gpu_lib.close()
+
+
+@pytest.mark.parametrize("arena", ["host", "device"])
+@pytest.mark.parametrize("name,n", [("16B", 1), ("16B", 600), ("9KiB", 1), ("9KiB", 6), ("9KiB", 7), ("fp8_4KiB_wide", 2), ("fp8_48B", 90),
+                                    ("1KiB", 60), ("1KiB_many", 61), ("1KiB_many", 449)])
+def test_streams_hand_over_short_transfers(gpu, name, n, arena):
+    """Short transfers tell the other stream by a number that they have finished: launches of one workgroup, of fewer jobs
+    than workgroups, of more, of ragged slots (the host arena's two kinds of job), and lists of every kind of upload.  A chain of
+    preemptions, resumptions and exchanges in which every call reads or overwrites what the one before it has moved, with
+    nothing waited for in between."""
+    g = GEOMS[name]
+    rng = np.random.default_rng(n)
+    a, b = (HostPool(g, 0xB11 + n, "layer", slots=2 * n) for _ in range(2))
+    ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE if arena == "device" else kv.KV_PATH_ZEROCOPY)
+    gpu_lib._push()
+    kp, off = gpu_lib.kp, [0, n]
+    tables = [rng.permutation(g.N)[:n].astype(np.int32) for _ in range(9)]
+    for k in range(8):
+        assert ora.swap_out([1], off, tables[k], [n * g.B]) == ko.OK
+        assert kp.swap_out([1], off, tables[k], [n * g.B]) == kv.KV_OK
+        assert ora.swap_in([1], off, tables[k + 1]) == ko.OK
+        assert kp.swap_in([1], off, tables[k + 1]) == kv.KV_OK
+    assert ora.swap_out([1], off, tables[8], [n * g.B]) == ko.OK
+    assert kp.swap_out([1], off, tables[8], [n * g.B]) == kv.KV_OK
+    for k in range(6):  # the set that is out takes the blocks of the one that goes
+        out, back = 2 - k % 2, 1 + k % 2
+        assert ora.swap_out([out], off, tables[8 - k], [n * g.B]) == ko.OK and ora.swap_in([back], off, tables[8 - k]) == ko.OK
+        assert kp.evict_and_load([out], off, tables[8 - k], [n * g.B], [back], off, tables[8 - k]) == kv.KV_OK
+    gpu_lib._pull()
+    assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
+    assert not g.scales or np.array_equal(a.scale, b.scale)
+    gpu_lib.close()

@@ -181,6 +181,8 @@ RUNTIME_MUTANTS = [
      "      HIPCHK(p, hipStreamWaitEvent(st, p->na_done_ev, 0));", ""),
     ("load_phase_forgets_the_eviction_phase_that_frees_its_blocks",
      "    if (it != reader.end()) need[i / m] = std::max(need[i / m], it->second);", "    (void)it;"),
+    ("number_of_the_launch_before_waited_for", "hipStreamWaitValue64(st, p->done_word[c.stream], v, ",
+     "hipStreamWaitValue64(st, p->done_word[c.stream], v - 1, "),
     ("write_through_that_moves_nothing_forgets_the_pending_reader",
      "        if (kvswap::Req* r = p->planner.find_mut(id)) r->in_seq = std::max(r->in_seq, fresh_dep);", "        (void)id;"),
 ]
