@@ -242,12 +242,12 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
                    void* wait_event);
 
 /* kv_move_blocks for callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses
- * that forbid hipMalloc.  Same arguments, same result in the pool, the same kernels (a list of more than 448 blocks is
- * not sorted first, where kv_move_blocks may sort it to be faster).  The call makes no hipMalloc,
- * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: up to 448 descriptors travel inside
- * the arguments of the move kernel, longer lists inside the arguments of small fill launches (448 per launch) into a
- * fixed device array that is part of the library's code object (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB
- * per GPU, held until the process ends).
+ * that forbid hipMalloc.  Same arguments, same result in the pool, the same kernels.  The call makes no hipMalloc,
+ * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: short lists travel inside
+ * the arguments of the move kernel, longer ones into a fixed device array that is part of the library's code object
+ * (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB per GPU, held until the process ends), uploaded from one of two
+ * to eight pinned buffers that kv_pool_create takes (1 MiB together at most).  While earlier calls still read all of them, and
+ * under graph capture, lists of more than 448 blocks go inside the arguments of small fill launches (448 per launch).
  *   - n > KV_NOALLOC_MAX_BLOCKS returns KV_E2BIG and does nothing; split the list.
  *   - Runs on the evict stream after everything enqueued on either stream of this handle before it; load-stream
  *     calls made while it is unfinished wait for it as a whole (it keeps no per-block marks).

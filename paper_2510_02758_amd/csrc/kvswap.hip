@@ -152,7 +152,7 @@ void done_words_give_back(kv_pool* p, bool drained) {
 }  // namespace
 
 // Everything kv_move_blocks_noalloc will need, taken once when the handle is created: the address of the
-// descriptor array on this GPU, two events and the duplicate bitmap.
+// descriptor array on this GPU, events, the duplicate bitmap, and the upload buffers.
 static int noalloc_setup(kv_pool* p) {
   hipError_t e = scratch_on_current_device(&p->na_dev, &p->device);
   if (e != hipSuccess) {
@@ -162,6 +162,14 @@ static int noalloc_setup(kv_pool* p) {
   HIPCHK(p, hipEventCreate(&p->na_fence_ev));
   HIPCHK(p, hipEventCreate(&p->na_done_ev));
   p->na_mark.assign((size_t)((p->cfg.num_blocks + 63) / 64), 0);
+  p->na_cap = (size_t)std::min<int64_t>(p->cfg.num_blocks, KV_NOALLOC_MAX_BLOCKS);
+  p->na_list.reserve(p->na_cap);
+  p->na_tmp.reserve(p->na_cap);
+  if (p->na_cap > (size_t)kMoveDescMax) {  // shorter lists travel inside the arguments
+    p->na_bufs = (int)std::min<size_t>(8, 2 * KV_NOALLOC_MAX_BLOCKS / p->na_cap);  // 1 MiB at most
+    HIPCHK(p, hipHostMalloc((void**)&p->na_up, p->na_bufs * p->na_cap * sizeof(Desc), hipHostMallocDefault));
+    for (int k = 0; k < p->na_bufs; k++) HIPCHK(p, hipEventCreate(&p->na_up_ev[k]));
+  }
   return KV_OK;
 }
 
@@ -336,6 +344,9 @@ int kv_pool_destroy(kv_pool* p) try {
     done_words_give_back(p, rc == KV_OK && !p->broken);
     if (p->na_fence_ev) (void)hipEventDestroy(p->na_fence_ev);
     if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
+    for (hipEvent_t e : p->na_up_ev)
+      if (e) (void)hipEventDestroy(e);
+    if (p->na_up) (void)hipHostFree(p->na_up);
     for (int s = 0; s < 2; s++)
       if (p->own_stream[s]) (void)hipStreamDestroy(p->stream[s]);
   }
@@ -565,7 +576,7 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
   std::vector<Desc> kd;
   if (pm) {
     kd = plan.desc;
-    sort_desc(p, &kd, &Desc::b, p->cfg.num_blocks);
+    sort_desc(&kd, &p->sort_tmp, &Desc::b, p->cfg.num_blocks);
   }
   rc = enqueue_kernel(p, *c, 2, pm ? kd.data() : plan.desc.data(), plan.desc.size(), nullptr, 0, /*sole=*/true, pm);
   if (rc) return rc;
@@ -579,10 +590,14 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
 KV_CATCH(p)
 
 // kv_move_blocks for callers that cannot allocate.  Uses only what kv_pool_create set up: no hipMalloc, hipFree,
-// hipHostMalloc, event or stream creation, and no host heap either (the descriptors travel inside kernel
-// arguments, duplicates are found with the handle's bitmap).  The kernel is the one kv_move_blocks launches, except that a
-// list its arguments do not hold stays in the caller's order (there is no buffer to sort it in), where kv_move_blocks may go
-// plane by plane; it is read from the library's fixed device array instead of the growable ring.
+// hipHostMalloc, event or stream creation, and no host heap either (duplicates are found with the handle's bitmap).  The
+// kernel is the one kv_move_blocks launches; a list its arguments do not hold is read from the library's fixed device
+// array instead of the growable ring.
+//
+// How a longer list (most_inline()) gets there.  Uploaded from one of the handle's pinned buffers that no earlier upload still
+// reads: 60 000 blocks of 16 KiB 525 us (965 inside the arguments of 134 fill launches, 3 to 8 us of host time each).
+// Inside the arguments of fill launches where all buffers are still being read (the call does not wait for them) and under graph
+// capture (a replay would read the buffer again).
 int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t* dst_ids, void* wait_event) try {
   if (!p) return KV_EINVAL;
   KV_ENTER(p);
@@ -617,39 +632,64 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   if (p->plan_only || (n == 0 && !wait_event)) return KV_OK;
 
   hipStream_t st = p->stream[kEvict];
+  const bool captured = capturing(st);
   // after everything the load stream has been given so far (it may still write blocks this move reads, or read
-  // blocks it overwrites), and after the caller's event
-  HIPCHK(p, hipEventRecord(p->na_fence_ev, p->stream[kLoad]));
-  HIPCHK(p, hipStreamWaitEvent(st, p->na_fence_ev, 0));
+  // blocks it overwrites), and after the caller's event.  A load stream that has nothing left to do needs no event (a move
+  // of two blocks 24-26 us with it, 11 without).
+  bool idle = false;
+  if (!captured && !capturing(p->stream[kLoad])) {
+    idle = hipStreamQuery(p->stream[kLoad]) == hipSuccess;
+    if (!idle) (void)hipGetLastError();
+  }
+  if (!idle) {
+    HIPCHK(p, hipEventRecord(p->na_fence_ev, p->stream[kLoad]));
+    HIPCHK(p, hipStreamWaitEvent(st, p->na_fence_ev, 0));
+  }
   hipEvent_t callers = (hipEvent_t)wait_event;
   if (callers) HIPCHK(p, hipStreamWaitEvent(st, callers, 0));
   if (n > 0) {
-    // Short lists travel inside the arguments of the move itself.  Longer ones go into the fixed array
-    // in batches that travel as kernel arguments: nothing on the host has to outlive this call, so it never waits for
-    // an earlier one.  The array keeps the previous call's descriptors: [0, n) is overwritten here, in stream order
-    // behind the previous call's kernel, and nothing beyond n is read.
-    const bool hbm = hbm_kernels(p), inline_desc = n <= (hbm ? kInlineDescMax : kMoveDescMax);
+    // Short lists travel inside the arguments of the move itself.  The array keeps the previous call's descriptors: [0, n)
+    // is overwritten here, in stream order behind the previous call's kernel, and nothing beyond n is read.
+    const bool hbm = hbm_kernels(p);
+    int up = -1;  // the buffer this call uploads from
+    if ((size_t)n > most_inline(p, 2, (size_t)n, hbm) && !captured)
+      for (int t = 0; t < p->na_bufs && up < 0; t++) {  // the one used longest ago first
+        const int k = (p->na_turn + t) % p->na_bufs;
+        if (hipEventQuery(p->na_up_ev[k]) == hipSuccess) up = k;
+      }
+    const bool inline_desc = up < 0 && n <= (hbm ? kInlineDescMax : kMoveDescMax);
     (void)hipGetLastError();
-    DescPack pack;
-    for (int64_t at = 0; at < n; at += kDescPack) {
-      const int m = (int)std::min<int64_t>(kDescPack, n - at);
-      for (int i = 0; i < m; i++) pack.d[i] = {src_ids[at + i], dst_ids[at + i]};
-      if (!inline_desc) hipLaunchKernelGGL(kv_desc_fill_kernel, dim3(1), dim3(512), 0, st, p->na_dev, at, m, pack);
+    const bool pm = hbm && plane_by_plane_move(p, (size_t)n);
+    std::vector<Desc>& list = p->na_list;
+    list.resize((size_t)n);
+    for (int64_t i = 0; i < n; i++) list[(size_t)i] = {src_ids[i], dst_ids[i]};
+    if (pm) sort_desc(&list, &p->na_tmp, &Desc::b, N);
+    if (up >= 0) {
+      Desc* to = p->na_up + (size_t)up * p->na_cap;
+      std::memcpy(to, list.data(), (size_t)n * sizeof(Desc));
+      HIPCHK(p, hipMemcpyAsync(p->na_dev, to, (size_t)n * sizeof(Desc), hipMemcpyHostToDevice, st));
+      HIPCHK(p, hipEventRecord(p->na_up_ev[up], st));
+      p->na_turn = (up + 1) % p->na_bufs;
+    } else if (!inline_desc) {
+      DescPack pack;
+      for (int64_t at = 0; at < n; at += kDescPack) {
+        const int m = (int)std::min<int64_t>(kDescPack, n - at);
+        std::memcpy(pack.d, list.data() + at, (size_t)m * sizeof(Desc));
+        hipLaunchKernelGGL(kv_desc_fill_kernel, dim3(1), dim3(512), 0, st, p->na_dev, at, m, pack);
+      }
+      HIPCHK(p, hipGetLastError());
     }
-    HIPCHK(p, hipGetLastError());
     (void)hipGetLastError();
     int grid;
     if (hbm) {
-      const bool pm = inline_desc && plane_by_plane_move(p, (size_t)n);
-      if (pm) std::sort(pack.d, pack.d + n, [](const Desc& x, const Desc& y) { return x.b < y.b; });
-      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? pack.d : nullptr, (size_t)n, nullptr, pm, st);
+      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? list.data() : nullptr, (size_t)n, nullptr, pm, st);
     } else {
       MoveArgs a;
       int u = 1;
       grid = build_move_args(p, 2, (size_t)n, nullptr, 0, false, &a, &u);
       a.desc = p->na_dev;
       a.use_inl = inline_desc ? 1 : 0;
-      if (inline_desc) std::memcpy(a.inl, pack.d, (size_t)n * sizeof(Desc));
+      if (inline_desc) std::memcpy(a.inl, list.data(), (size_t)n * sizeof(Desc));
       launch_move<2>(u, grid, 0, st, a);
     }
     HIPCHK(p, hipGetLastError());

@@ -94,6 +94,7 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t* at, const void* p);
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned flags);
 hipError_t hipStreamDestroy(hipStream_t s);
 hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipStreamQuery(hipStream_t s);
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 // A wait for a value holds its stream back until the word at `p` is at least `value`; the word is compared whenever the
 // executor looks at the stream, as the command processor does.

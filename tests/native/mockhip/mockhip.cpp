@@ -258,6 +258,11 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
   drive([&] { return st->q.empty(); });
   return hipSuccess;
 }
+hipError_t hipStreamQuery(hipStream_t s) {
+  API_LOCK;
+  if (injected()) return fail_code;
+  return S(s)->q.empty() ? hipSuccess : hipErrorNotReady;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   API_LOCK;
   if (injected()) return fail_code;
