@@ -160,7 +160,8 @@ typedef struct {
   int64_t bytes;    /* payload bytes = blocks * S */
   double plan_us;   /* host time spent validating and building descriptors */
   double enqueue_us; /* host time spent inside HIP enqueue calls */
-  float ms_total;   /* first enqueue to last completion on the stream (HIP events) */
+  float ms_total;   /* first enqueue to last completion on the stream (HIP events; a call that is a single launch and
+                       nothing else: the device's clock from the launch's first workgroup to its last) */
   float ms_kernel;  /* summed duration of the data kernels (HIP events around each launch); a call that is a
                        single launch and nothing else carries no events of its own and reports ms_total */
   int32_t scatter_order; /* large scatter with both ends in HBM: 0 block by block, 1 plane by plane; -1 otherwise */
@@ -246,7 +247,7 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
  * hipFree, hipHostMalloc, event or stream creation and no host-heap allocation: short lists travel inside
  * the arguments of the move kernel, longer ones into a fixed device array that is part of the library's code object
  * (KV_NOALLOC_MAX_BLOCKS descriptors of 8 bytes = 512 KiB per GPU, held until the process ends), uploaded from one of two
- * to eight pinned buffers that kv_pool_create takes (1 MiB together at most).  While earlier calls still read all of them, and
+ * to four pinned buffers that kv_pool_create takes (1 MiB together at most).  While earlier calls still read all of them, and
  * under graph capture, lists of more than 448 blocks go inside the arguments of small fill launches (448 per launch).
  *   - n > KV_NOALLOC_MAX_BLOCKS returns KV_E2BIG and does nothing; split the list.
  *   - Runs on the evict stream after everything enqueued on either stream of this handle before it; load-stream

@@ -61,19 +61,27 @@ namespace {
 constexpr int kTicketSlots = 1024, kTicketWords = 64;
 }
 static __device__ __align__(256) uint32_t ticket_words[kTicketSlots * kTicketWords];
+// Those of launches with both ends in HBM (kLeaveWords per stream), for the handles on the first kLeaveSlots slots: a
+// handle beyond them goes without (its calls have start events and hand over by event).
+namespace {
+constexpr int kLeaveSlots = 128;
+}
+static __device__ __align__(256) uint32_t leave_words[kLeaveSlots * 2 * kLeaveWords];
 
 namespace {
 std::mutex g_ticket_mu;
-uint32_t* kTicketsOn[kMaxDevices] = {};
+uint32_t *kTicketsOn[kMaxDevices] = {}, *kLeaveOn[kMaxDevices] = {};
 uint64_t g_ticket_taken[kMaxDevices][kTicketSlots / 64] = {};
 
 int tickets_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
   {
     std::lock_guard<std::mutex> g(g_ticket_mu);
     if (!kTicketsOn[p->device]) {
-      uint32_t* at = nullptr;
-      HIPCHK(p, hipGetSymbolAddress((void**)&at, HIP_SYMBOL(ticket_words)));
-      kTicketsOn[p->device] = at;
+      uint32_t *tickets = nullptr, *leave = nullptr;
+      HIPCHK(p, hipGetSymbolAddress((void**)&tickets, HIP_SYMBOL(ticket_words)));
+      HIPCHK(p, hipGetSymbolAddress((void**)&leave, HIP_SYMBOL(leave_words)));
+      kTicketsOn[p->device] = tickets;
+      kLeaveOn[p->device] = leave;
     }
     uint64_t* taken = g_ticket_taken[p->device];
     for (int s = 0; s < kTicketSlots; s++)
@@ -81,9 +89,11 @@ int tickets_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
         taken[s >> 6] |= 1ull << (s & 63);
         p->ticket_slot = s;
         p->tickets = kTicketsOn[p->device] + s * kTicketWords;
+        for (int k = 0; k < 2 && s < kLeaveSlots; k++) p->leave[k] = kLeaveOn[p->device] + (s * 2 + k) * kLeaveWords;
         return KV_OK;
       }
   }
+  if (p->dev_staging) return KV_OK;  // only the host arena's kernels cannot do without
   constexpr size_t bytes = kTicketWords * sizeof(uint32_t);
   HIPCHK(p, hipMalloc((void**)&p->tickets, bytes));
   std::memset(p->ring_host, 0, bytes);  // the ring is empty: its first words serve as the source
@@ -99,8 +109,9 @@ void tickets_give_back(kv_pool* p, bool drained) {
   } else if (p->tickets) {
     (void)hipFree(p->tickets);
   }
-  p->tickets = nullptr;
+  p->tickets = p->leave[0] = p->leave[1] = nullptr;
 }
+
 }  // namespace
 
 // ---- the words by which one stream tells the other that a launch has finished ----
@@ -151,8 +162,29 @@ void done_words_give_back(kv_pool* p, bool drained) {
 }
 }  // namespace
 
+// The handle's pinned memory in one piece, since each allocation costs 10 us here: records of the device's clock for the calls in
+// flight (a handle that runs out of them goes on with start events), the upload buffers of kv_move_blocks_noalloc, and the
+// descriptor ring as long as it does not have to grow.
+constexpr int kStamps = 1024;
+static int memory_setup(kv_pool* p) {
+  if (hipDeviceGetAttribute(&p->clock_khz, hipDeviceAttributeWallClockRate, p->device) != hipSuccess) p->clock_khz = 0;
+  (void)hipGetLastError();
+  const size_t stamp_words = p->clock_khz > 0 ? 2 * kStamps : 0, ring = ring_entries_for(p->cfg.num_blocks);
+  p->na_cap = (size_t)std::min<int64_t>(p->cfg.num_blocks, KV_NOALLOC_MAX_BLOCKS);
+  if (p->na_cap > (size_t)kMoveDescMax)  // shorter lists travel inside the arguments
+    p->na_bufs = (int)std::min<size_t>(4, 2 * KV_NOALLOC_MAX_BLOCKS / p->na_cap);  // 1 MiB at most
+  HIPCHK(p, hipHostMalloc((void**)&p->pinned, stamp_words * sizeof(uint64_t) + (p->na_bufs * p->na_cap + ring) * sizeof(Desc), hipHostMallocDefault));
+  p->na_up = (Desc*)(p->pinned + stamp_words);
+  p->ring_host = p->na_up + p->na_bufs * p->na_cap;
+  HIPCHK(p, hipMalloc((void**)&p->ring_dev, ring * sizeof(Desc)));
+  p->ring_cap = ring;
+  p->stamp_free.reserve(stamp_words / 2);
+  for (size_t w = stamp_words; w; w -= 2) p->stamp_free.push_back(p->pinned + w - 2);
+  return KV_OK;
+}
+
 // Everything kv_move_blocks_noalloc will need, taken once when the handle is created: the address of the
-// descriptor array on this GPU, events, the duplicate bitmap, and the upload buffers.
+// descriptor array on this GPU, events, the duplicate bitmap, and room to sort a list.
 static int noalloc_setup(kv_pool* p) {
   hipError_t e = scratch_on_current_device(&p->na_dev, &p->device);
   if (e != hipSuccess) {
@@ -162,14 +194,9 @@ static int noalloc_setup(kv_pool* p) {
   HIPCHK(p, hipEventCreate(&p->na_fence_ev));
   HIPCHK(p, hipEventCreate(&p->na_done_ev));
   p->na_mark.assign((size_t)((p->cfg.num_blocks + 63) / 64), 0);
-  p->na_cap = (size_t)std::min<int64_t>(p->cfg.num_blocks, KV_NOALLOC_MAX_BLOCKS);
   p->na_list.reserve(p->na_cap);
   p->na_tmp.reserve(p->na_cap);
-  if (p->na_cap > (size_t)kMoveDescMax) {  // shorter lists travel inside the arguments
-    p->na_bufs = (int)std::min<size_t>(8, 2 * KV_NOALLOC_MAX_BLOCKS / p->na_cap);  // 1 MiB at most
-    HIPCHK(p, hipHostMalloc((void**)&p->na_up, p->na_bufs * p->na_cap * sizeof(Desc), hipHostMallocDefault));
-    for (int k = 0; k < p->na_bufs; k++) HIPCHK(p, hipEventCreate(&p->na_up_ev[k]));
-  }
+  for (int k = 0; k < p->na_bufs; k++) HIPCHK(p, hipEventCreate(&p->na_up_ev[k]));
   return KV_OK;
 }
 
@@ -310,13 +337,14 @@ int kv_pool_create(const kv_pool_config* cfg, kv_pool** out) {
       }
     }
     hbm_setup(p);
-    if (!rc) rc = grow_ring(p, ring_entries_for(cfg->num_blocks));
+    p->device = dev;
+    if (!rc) rc = memory_setup(p);
     if (!rc) {
       p->blk_reader.assign((size_t)cfg->num_blocks, BlkMark{0, -1});
       p->blk_writer.assign((size_t)cfg->num_blocks, BlkMark{0, -1});
     }
     if (!rc) rc = noalloc_setup(p);
-    if (!rc && !p->dev_staging) rc = tickets_setup(p);
+    if (!rc) rc = tickets_setup(p);
     if (!rc) done_words_setup(p);
     if (rc) {
       kv_pool_destroy(p);
@@ -338,7 +366,7 @@ int kv_pool_destroy(kv_pool* p) try {
       if (p->stream[s] && hipStreamSynchronize(p->stream[s]) != hipSuccess) rc = KV_EHIP;
     for (auto& c : p->calls) recycle(p, c);
     for (auto ev : p->ev_free) (void)hipEventDestroy(ev);
-    if (p->ring_host) (void)hipHostFree(p->ring_host);
+    if (p->ring_host && !p->pinned_ring()) (void)hipHostFree(p->ring_host);
     if (p->ring_dev) (void)hipFree(p->ring_dev);
     tickets_give_back(p, rc == KV_OK && !p->broken);
     done_words_give_back(p, rc == KV_OK && !p->broken);
@@ -346,7 +374,7 @@ int kv_pool_destroy(kv_pool* p) try {
     if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
     for (hipEvent_t e : p->na_up_ev)
       if (e) (void)hipEventDestroy(e);
-    if (p->na_up) (void)hipHostFree(p->na_up);
+    if (p->pinned) (void)hipHostFree(p->pinned);
     for (int s = 0; s < 2; s++)
       if (p->own_stream[s]) (void)hipStreamDestroy(p->stream[s]);
   }
@@ -356,6 +384,9 @@ int kv_pool_destroy(kv_pool* p) try {
 catch (...) {
   return KV_ENOMEM;  // nothing in here allocates beyond the event free list; the handle is not touched again
 }
+
+// Whether a transfer that goes straight between pool and arena is not cut into segments.
+static bool one_launch(const kv_pool* p, const Plan& plan) { return !p->req_events && !use_dma(p, plan.desc.size()); }
 
 static int swap_out_common(kv_pool* p, int op, Plan& plan, double t0, void* wait_event) {
   const double t1 = now_us();
@@ -382,7 +413,7 @@ static int swap_out_common(kv_pool* p, int op, Plan& plan, double t0, void* wait
     return KV_OK;
   }
   Call* c = nullptr;
-  int rc = open_call(p, kEvict, op, dep, wait_event, 0, plan.desc, &c);
+  int rc = open_call(p, kEvict, op, dep, wait_event, 0, plan.desc, &c, one_launch(p, plan));
   if (rc) return rc;
   fill_plan_stats(p, &c->st, op, plan.desc.size(), t1 - t0);
   rc = enqueue_transfer(p, *c, plan, true);
@@ -451,7 +482,7 @@ int kv_swap_in(kv_pool* p, int32_t n, const uint64_t* req_ids, const int32_t* of
     return KV_OK;
   }
   Call* c = nullptr;
-  rc = open_call(p, kLoad, 3, dep, wait_event, 1, plan.desc, &c);
+  rc = open_call(p, kLoad, 3, dep, wait_event, 1, plan.desc, &c, one_launch(p, plan));
   if (rc) return rc;
   fill_plan_stats(p, &c->st, 3, plan.desc.size(), t1 - t0);
   rc = enqueue_transfer(p, *c, plan, false);
@@ -505,9 +536,10 @@ int kv_evict_and_load(kv_pool* p, int32_t n_out, const uint64_t* out_ids, const 
         const uint64_t dep_out = std::max(cross_stream(p, kEvict, po.wait_in_seq), pending_user(p, kEvict, po.fresh));
         const uint64_t dep_in = cross_stream(p, kLoad, pi.wait_out_seq);
         Call *co = nullptr, *ci = nullptr;
-        rc = open_call(p, kEvict, 1, dep_out, wait_event, 0, po.desc, &co);
+        const size_t m = phase_blocks(p, po.desc.size(), pi.desc.size());
+        rc = open_call(p, kEvict, 1, dep_out, wait_event, 0, po.desc, &co, po.desc.size() <= m);
         if (rc) return rc;
-        rc = open_call(p, kLoad, 3, dep_in, wait_event, 1, pi.desc, &ci, /*do_retire=*/false);
+        rc = open_call(p, kLoad, 3, dep_in, wait_event, 1, pi.desc, &ci, pi.desc.size() <= m, /*do_retire=*/false);
         if (rc) return rc;
         fill_plan_stats(p, &co->st, 1, po.desc.size(), t1 - t0);
         fill_plan_stats(p, &ci->st, 3, pi.desc.size(), t1 - t0);
@@ -534,7 +566,7 @@ int kv_evict_and_load(kv_pool* p, int32_t n_out, const uint64_t* out_ids, const 
       }
       const uint64_t dep_in = cross_stream(p, kLoad, pi.wait_out_seq);
       Call* c = nullptr;
-      rc = open_call(p, kLoad, 3, dep_in, wait_event, 1, pi.desc, &c);
+      rc = open_call(p, kLoad, 3, dep_in, wait_event, 1, pi.desc, &c, one_launch(p, pi));
       if (rc) return rc;
       fill_plan_stats(p, &c->st, 3, pi.desc.size(), t1 - t0);
       if ((rc = enqueue_transfer(p, *c, pi, false)) || (rc = close_call(p, *c))) return rc;
@@ -568,7 +600,7 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
     return KV_OK;
   }
   Call* c = nullptr;
-  rc = open_call(p, kEvict, 4, 0, wait_event, 2, plan.desc, &c);
+  rc = open_call(p, kEvict, 4, 0, wait_event, 2, plan.desc, &c, /*one_launch=*/true);
   if (rc) return rc;
   fill_plan_stats(p, &c->st, 4, plan.desc.size(), t1 - t0);
   c->st.path = KV_PATH_ZEROCOPY;
@@ -769,7 +801,7 @@ int kv_last_stats(kv_pool* p, kv_stats* out) try {
   if (c.end) {
     HIPCHK(p, hipEventSynchronize(c.end));
     float ms = 0.f;
-    HIPCHK(p, hipEventElapsedTime(&ms, c.start, c.end));
+    HIPCHK(p, call_ms(p, c, c.end, &ms));
     c.st.ms_total = ms;
     float ks = 0.f;
     for (auto& k : c.kev) {
@@ -849,7 +881,7 @@ int64_t kv_last_timeline(kv_pool* p, uint64_t* req_ids, float* done_ms, int64_t 
     const int sg = c.req_seg[(size_t)i].second;
     hipEvent_t ev = sg >= 0 && sg < (int)c.seg_ev.size() ? c.seg_ev[(size_t)sg] : c.end;
     float ms = 0.f;
-    HIPCHK(p, hipEventElapsedTime(&ms, c.start, ev));
+    HIPCHK(p, call_ms(p, c, ev, &ms));
     if (req_ids) req_ids[i] = c.req_seg[(size_t)i].first;
     if (done_ms) done_ms[i] = ms;
   }

@@ -85,6 +85,8 @@ inline unsigned atomicExch(unsigned* p, unsigned v) { const unsigned old = *p; *
 hipError_t hipGetLastError();
 hipError_t hipGetDevice(int* dev);
 hipError_t hipGetDeviceProperties(hipDeviceProp_t* prop, int dev);
+enum hipDeviceAttribute_t { hipDeviceAttributeWallClockRate = 1 };
+hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t what, int dev);  // a clock of 100 MHz
 hipError_t hipMalloc(void** p, size_t n);
 hipError_t hipFree(void* p);
 hipError_t hipHostMalloc(void** p, size_t n, unsigned flags);

@@ -181,6 +181,8 @@ hipError_t hipGetLastError() {
 hipError_t hipGetDevice(int* dev) { *dev = 0; return hipSuccess; }
 hipError_t hipGetDeviceProperties(hipDeviceProp_t* prop, int) { prop->multiProcessorCount = 256; return hipSuccess; }
 
+hipError_t hipDeviceGetAttribute(int* value, hipDeviceAttribute_t, int) { *value = 100000; return hipSuccess; }
+
 static hipError_t alloc_any(void** p, size_t n, int type) {
   API_LOCK;
   n_resource++;
