@@ -1,0 +1,155 @@
+// The plane-by-plane order of a launch with both ends in HBM against the block-by-block one, on the CPU: the library's host code
+// and its kernels, on the stand-in HIP runtime, over every way a pool can be laid out that the order accepts (layer-major,
+// padded, block-major, planes in descending layers' places), chunks of one KiB to several, with and without scales, lists in any order,
+// inside the arguments and uploaded, launches that finish with a number and the clock and launches that do not.  And the rule that
+// says which pools' planes collide, at the distances it was measured at.
+#include <random>
+
+#include "kvswap.hip"
+
+namespace {
+
+[[noreturn]] void die(const char* what, long a, long b) {
+  std::printf("FAILED: %s (%ld, %ld)\n", what, a, b);
+  std::exit(1);
+}
+
+long compared = 0;
+
+void compare(std::mt19937_64& rng, int L, int H, int D, int B, bool scales, int layout, size_t n) {
+  const int64_t chunk = (int64_t)B * H * D, N = 3 * (int64_t)n + 2;  // one byte per element
+  kv_pool p;
+  p.cfg.num_layers = L;
+  p.cfg.num_kv_heads = H;
+  p.cfg.num_blocks = N;
+  p.chunk = chunk;
+  p.block_bytes = 2 * L * chunk;
+  if (layout == 0) {  // layer-major
+    p.cfg.block_stride = chunk;
+    p.cfg.kv_stride = N * chunk;
+    p.cfg.layer_stride = 2 * N * chunk;
+  } else if (layout == 1) {  // the same, padded
+    p.cfg.block_stride = chunk + 48;
+    p.cfg.kv_stride = N * p.cfg.block_stride + 160;
+    p.cfg.layer_stride = 2 * p.cfg.kv_stride + 16;
+  } else if (layout == 2) {  // block-major
+    p.cfg.kv_stride = chunk;
+    p.cfg.layer_stride = 2 * chunk;
+    p.cfg.block_stride = p.block_bytes;
+  } else {  // all layers' K, then all layers' V
+    p.cfg.block_stride = chunk;
+    p.cfg.layer_stride = N * chunk;
+    p.cfg.kv_stride = L * N * chunk;
+  }
+  const int64_t pool_bytes = (L - 1) * p.cfg.layer_stride + p.cfg.kv_stride + (N - 1) * p.cfg.block_stride + chunk;
+  std::vector<char> pool((size_t)pool_bytes), scale;
+  for (char& c : pool) c = (char)rng();
+  p.cfg.pool_dev = pool.data();
+  int64_t side = 0;
+  if (scales) {
+    side = 2ll * L * H * 4;
+    scale.resize((size_t)(N * side));
+    for (char& c : scale) c = (char)rng();
+    p.cfg.scale_dev = scale.data();
+    p.cfg.scale_block_stride = H * 4;
+    p.cfg.scale_kv_stride = N * H * 4;
+    p.cfg.scale_layer_stride = 2 * N * H * 4;
+  }
+  p.S = p.block_bytes + side;
+  p.dev_staging = true;
+  hbm_setup(&p);
+  if (!p.hbm_wave) die("a chunk of whole KiB", chunk, 0);
+  hipStream_t st[2];
+  for (int s = 0; s < 2; s++) {
+    (void)hipStreamCreateWithFlags(&st[s], hipStreamNonBlocking);
+    p.stream[s] = st[s];
+  }
+  if (grow_ring(&p, 4096) != KV_OK) die("ring", 0, 0);
+  static uint32_t words[2][kLeaveWords];
+  static uint64_t done[2], stamp[2];
+
+  std::vector<int32_t> perm((size_t)N);
+  for (size_t i = 0; i < perm.size(); i++) perm[i] = (int32_t)i;
+  std::shuffle(perm.begin(), perm.end(), rng);
+  std::vector<Desc> list(n);
+  std::vector<int32_t> slot(n);
+  for (size_t i = 0; i < n; i++) slot[i] = (int32_t)i;
+  std::shuffle(slot.begin(), slot.end(), rng);
+  for (int mode = 0; mode < 3; mode++)
+    for (int finish = 0; finish < 2; finish++) {
+      for (int s = 0; s < 2; s++) {
+        p.leave[s] = finish ? words[s] : nullptr;
+        p.done_word[s] = finish ? &done[s] : nullptr;
+      }
+      std::vector<char> out[2], arena[2];
+      const std::vector<char> pool0 = pool, scale0 = scale;
+      for (int pm = 0; pm < 2; pm++) {
+        pool = pool0;
+        scale = scale0;
+        p.cfg.pool_dev = pool.data();
+        if (scales) p.cfg.scale_dev = scale.data();
+        hbm_setup(&p);
+        std::vector<char> slots((size_t)((int64_t)n * p.S));
+        for (size_t i = 0; i < slots.size(); i++) slots[i] = (char)(i * 131 >> 3);
+        for (size_t i = 0; i < n; i++) list[i] = {perm[i], mode == 2 ? perm[n + i] : slot[i]};
+        if (pm) {
+          std::vector<Desc> tmp;
+          sort_desc(&list, &tmp, mode == 2 ? &Desc::b : &Desc::a, N);
+        }
+        Call c;
+        c.stream = mode == 1 ? kLoad : kEvict;
+        c.st.op = mode == 0 ? 1 : mode == 1 ? 3 : 4;
+        c.seq = ++p.seq;
+        stamp[0] = stamp[1] = 0;
+        c.stamp = finish && mode != 2 && n <= (size_t)kInlineDescMax ? stamp : nullptr;
+        if (enqueue_kernel(&p, c, mode, list.data(), n, mode == 2 ? nullptr : slots.data(), 0, /*sole=*/true, pm == 1) != KV_OK) die("launch", n, mode);
+        (void)hipStreamSynchronize(st[c.stream]);
+        if (finish && mode != 2 && done[c.stream] != p.done_last[c.stream]) die("number of a launch", (long)done[c.stream], (long)p.done_last[c.stream]);
+        if (c.stamp && !(stamp[0] && stamp[1] > stamp[0])) die("clock of a launch", (long)stamp[0], (long)stamp[1]);
+        for (int s = 0; s < 2; s++)
+          for (uint32_t w : words[s])
+            if (w) die("a counter that is not zero after its launch", w, s);
+        out[pm] = pool;
+        out[pm].insert(out[pm].end(), scale.begin(), scale.end());
+        arena[pm] = slots;
+        p.ring_inflight.clear();
+      }
+      if (out[0] != out[1] || arena[0] != arena[1]) die("the two orders move other bytes: mode, layout", mode, layout);
+      if (mode == 0 ? arena[0][0] == 0 && n == 0 : out[0] == std::vector<char>()) die("nothing moved", mode, layout);
+      compared++;
+    }
+  (void)hipHostFree(p.ring_host);
+  (void)hipFree(p.ring_dev);
+  for (int s = 0; s < 2; s++) (void)hipStreamDestroy(st[s]);
+}
+
+bool rule(int L, int64_t chunk, int64_t N) {
+  kv_pool p;
+  p.cfg.num_layers = L;
+  p.chunk = chunk;
+  p.cfg.kv_stride = N * chunk;
+  p.cfg.layer_stride = 2 * N * chunk;
+  return planes_on_few_channels(&p);
+}
+
+}  // namespace
+
+int main() {
+  std::mt19937_64 rng(17);
+  for (int layout = 0; layout < 4; layout++)
+    for (int scales = 0; scales < 2; scales++)
+      for (size_t n : {1, 2, 63, 64, 65, 130, 449}) {
+        const int L = n > 200 ? 1 : 1 + (int)(rng() % 3), K = n > 100 ? 1 : 1 + (int)(rng() % 3);
+        compare(rng, L, 4, 64, 4 * K, scales, layout, n);
+      }
+  for (int64_t N : {508, 516, 1016, 1032, 2032, 2064})
+    if (!rule(32, 32768, N) || !rule(80, 32768, N)) die("planes that collide", N, 0);
+  for (int64_t N : {448, 500, 504, 507, 509, 512, 524, 576, 960, 1000, 1020, 1024, 1088, 2040, 2048, 4096, 38146, 40000})
+    if (rule(32, 32768, N)) die("planes that do not collide", N, 0);
+  for (int64_t N : {127, 129, 254, 258, 508, 516})
+    if (!rule(32, 131072, N)) die("planes of 128 KiB chunks that collide", N, 0);
+  for (int64_t N : {4064, 4128})
+    if (!rule(32, 4096, N)) die("planes of 4 KiB chunks that collide", N, 0);
+  std::printf("orders agree: %ld\n", compared);
+  return 0;
+}

@@ -187,3 +187,17 @@ def test_streams_hand_over_short_transfers(gpu, name, n, arena):
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     assert not g.scales or np.array_equal(a.scale, b.scale)
     gpu_lib.close()
+
+
+def test_pool_whose_planes_collide(gpu):
+    """A pool of 24 planes 4 MiB + 32 KiB apart: 110 of its 258 blocks go plane by plane out and in again."""
+    g = W.Geometry(12, 8, 128, 8, "bf16", 258)
+    n = 110
+    perm = np.random.default_rng(21).permutation(g.N).astype(np.int32)
+    a, b = (HostPool(g, 0xB12, "layer", slots=n) for _ in range(2))
+    ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE)
+    for lib in (ora, gpu_lib):
+        assert lib.swap_out([1, 2], [0, 40, n], perm[:n], [40 * g.B, (n - 40) * g.B]) == ko.OK
+        assert lib.swap_in([2, 1], [0, n - 40, n], perm[n:2 * n]) == ko.OK
+    assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
+    gpu_lib.close()

@@ -117,6 +117,19 @@ def test_limits_of_one_launch(tmp_path):
     assert r.returncode == 0 and "launches ok" in r.stdout, r.stdout + r.stderr
 
 
+def test_the_two_job_orders_move_the_same_bytes(tmp_path):
+    """Plane by plane against block by block over the layouts and lists that both accept, and the rule that picks pools for
+    the former (see tests/native/plane_orders.cpp)."""
+    if not os.path.exists(CLANGXX):
+        pytest.skip("no host clang++ for the kernel source")
+    exe = str(tmp_path / "plane_orders")
+    subprocess.check_call([CLANGXX, "-std=c++17", "-pthread", "-Wno-unused-function", "-I", MOCK, "-I", os.path.join(ROOT, "include"), "-I", CSRC] +
+                          SAN + ["-x", "c++", os.path.join(HERE, "native", "plane_orders.cpp"), os.path.join(MOCK, "mockhip.cpp"), "-o", exe])
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:" + ASAN_OPTS.replace("detect_leaks=1:", ""), UBSAN_OPTIONS="print_stacktrace=1")
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300, env=env)
+    assert r.returncode == 0 and "orders agree" in r.stdout, r.stdout + r.stderr
+
+
 @pytest.fixture(scope="module")
 def mock_driver(tmp_path_factory):
     if not os.path.exists(CLANGXX):
