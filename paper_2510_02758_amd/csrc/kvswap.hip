@@ -173,7 +173,10 @@ static int memory_setup(kv_pool* p) {
   p->na_cap = (size_t)std::min<int64_t>(p->cfg.num_blocks, KV_NOALLOC_MAX_BLOCKS);
   if (p->na_cap > (size_t)kMoveDescMax)  // shorter lists travel inside the arguments
     p->na_bufs = (int)std::min<size_t>(4, 2 * KV_NOALLOC_MAX_BLOCKS / p->na_cap);  // 1 MiB at most
-  HIPCHK(p, hipHostMalloc((void**)&p->pinned, stamp_words * sizeof(uint64_t) + (p->na_bufs * p->na_cap + ring) * sizeof(Desc), hipHostMallocDefault));
+  // (whole MiB, so that handles of unlike pools ask for the same size: the runtime hands one that was given back out again in 10
+  // us, and takes 300 to make another)
+  const size_t bytes = stamp_words * sizeof(uint64_t) + (p->na_bufs * p->na_cap + ring) * sizeof(Desc), MiB = (size_t)1 << 20;
+  HIPCHK(p, hipHostMalloc((void**)&p->pinned, (bytes + MiB - 1) / MiB * MiB, hipHostMallocDefault));
   p->na_up = (Desc*)(p->pinned + stamp_words);
   p->ring_host = p->na_up + p->na_bufs * p->na_cap;
   HIPCHK(p, hipMalloc((void**)&p->ring_dev, ring * sizeof(Desc)));
@@ -699,7 +702,8 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     if (up >= 0) {
       Desc* to = p->na_up + (size_t)up * p->na_cap;
       std::memcpy(to, list.data(), (size_t)n * sizeof(Desc));
-      HIPCHK(p, hipMemcpyAsync(p->na_dev, to, (size_t)n * sizeof(Desc), hipMemcpyHostToDevice, st));
+      upload_desc(to, p->na_dev, (size_t)n, nullptr, st);
+      HIPCHK(p, hipGetLastError());
       HIPCHK(p, hipEventRecord(p->na_up_ev[up], st));
       p->na_turn = (up + 1) % p->na_bufs;
     } else if (!inline_desc) {

@@ -158,7 +158,7 @@ def test_workgroup_cap(gpu, name):
 
 
 @pytest.mark.parametrize("arena", ["host", "device"])
-@pytest.mark.parametrize("name,n", [("16B", 1), ("16B", 600), ("9KiB", 1), ("9KiB", 6), ("9KiB", 7), ("fp8_4KiB_wide", 2), ("fp8_48B", 90),
+@pytest.mark.parametrize("name,n", [("16B", 1), ("16B", 512), ("16B", 600), ("9KiB", 1), ("9KiB", 6), ("9KiB", 7), ("fp8_4KiB_wide", 2), ("fp8_48B", 90),
                                     ("1KiB", 60), ("1KiB_many", 61), ("1KiB_many", 449)])
 def test_streams_hand_over_short_transfers(gpu, name, n, arena):
     """Short transfers tell the other stream by a number that they have finished: launches of one workgroup, of fewer jobs
