@@ -608,12 +608,11 @@ int kv_move_blocks(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t*
   fill_plan_stats(p, &c->st, 4, plan.desc.size(), t1 - t0);
   c->st.path = KV_PATH_ZEROCOPY;
   const bool pm = plane_by_plane_move(p, plan.desc.size());
-  std::vector<Desc> kd;
   if (pm) {
-    kd = plan.desc;
-    sort_desc(&kd, &p->sort_tmp, &Desc::b, p->cfg.num_blocks);
+    p->sorted.assign(plan.desc.begin(), plan.desc.end());
+    sort_desc(&p->sorted, &p->sort_tmp, &Desc::b, p->cfg.num_blocks);
   }
-  rc = enqueue_kernel(p, *c, 2, pm ? kd.data() : plan.desc.data(), plan.desc.size(), nullptr, 0, /*sole=*/true, pm);
+  rc = enqueue_kernel(p, *c, 2, pm ? p->sorted.data() : plan.desc.data(), plan.desc.size(), nullptr, 0, /*sole=*/true, pm);
   if (rc) return rc;
   mark_blocks(p, *c, 2, plan.desc.data(), plan.desc.size(), -1);
   rc = close_call(p, *c);

@@ -1,6 +1,6 @@
 // The plane-by-plane order of a launch with both ends in HBM against the block-by-block one, on the CPU: the library's host code
 // and its kernels, on the stand-in HIP runtime, over every way a pool can be laid out that the order accepts (layer-major,
-// padded, block-major, planes in descending layers' places), chunks of one KiB to several, with and without scales, lists in any order,
+// padded, block-major, planes in descending layers' places), chunks of one KiB to several and ragged ones, with and without scales, lists in any order,
 // inside the arguments and uploaded, launches that finish with a number and the clock and launches that do not.  And the rule that
 // says which pools' planes collide, at the distances it was measured at.
 #include <random>
@@ -58,7 +58,6 @@ void compare(std::mt19937_64& rng, int L, int H, int D, int B, bool scales, int 
   p.S = p.block_bytes + side;
   p.dev_staging = true;
   hbm_setup(&p);
-  if (!p.hbm_wave) die("a chunk of whole KiB", chunk, 0);
   hipStream_t st[2];
   for (int s = 0; s < 2; s++) {
     (void)hipStreamCreateWithFlags(&st[s], hipStreamNonBlocking);
@@ -141,6 +140,9 @@ int main() {
       for (size_t n : {1, 2, 63, 64, 65, 130, 449}) {
         const int L = n > 200 ? 1 : 1 + (int)(rng() % 3), K = n > 100 ? 1 : 1 + (int)(rng() % 3);
         compare(rng, L, 4, 64, 4 * K, scales, layout, n);
+        // 16 to 7200 bytes, no whole KiB: whole lines and ragged ones, below and from 4 KiB on
+        const int odd[] = {4, 36, 40, 64, 288, 520, 1152, 1800};
+        compare(rng, L + 1, 4, odd[rng() % (n > 100 ? 4 : 8)], 1, scales, layout, n);
       }
   for (int64_t N : {508, 516, 1016, 1032, 2032, 2064})
     if (!rule(32, 32768, N) || !rule(80, 32768, N)) die("planes that collide", N, 0);
