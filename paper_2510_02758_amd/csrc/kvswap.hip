@@ -9,6 +9,8 @@
 //              run of consecutive staging slots (and the mirror image for loads).
 // With KV_STAGING_DEVICE the arena is HBM and the same kernels give the
 // on-device gather/scatter.
+#include <dlfcn.h>
+
 #include "runtime.hip.inc"
 
 // Entry of a call that changes state or enqueues work: takes the handle's lock and refuses a handle on which an
@@ -115,7 +117,7 @@ void tickets_give_back(kv_pool* p, bool drained) {
 }  // namespace
 
 // ---- the words by which one stream tells the other that a launch has finished ----
-// Signal memory (the only kind that the command processor waits on), two words per handle.  Words are never freed, since a
+// Signal memory (what hipStreamWaitValue64 takes), two words per handle.  Words are never freed, since a
 // stream may have waited on them: a handle hands its own back when its streams are drained, with the newest number stored
 // in it, and the next handle on that GPU goes on from there.  A process holds as many as it had handles at a time.
 namespace {
@@ -128,8 +130,16 @@ std::vector<DoneWord> g_done_free[kMaxDevices];
 size_t g_done_taken[kMaxDevices] = {};
 constexpr int kDoneBatch = 8;  // taken at a time: 7 to 30 us each, in front of the first of four handles
 
-// Leaves the handle without words, i.e. with event waits, where the GPU has none to give.
+// The runtime waits for a number with a kernel of one wavefront that polls the word.  A profiler that collects counters lets one
+// kernel run at a time, and such a kernel would keep the one that stores the number from running: under a profiling tool (which
+// exports rocprofiler_configure, or is named in the environment) handles hand over by event.
+bool profiled() {
+  return dlsym(RTLD_DEFAULT, "rocprofiler_configure") || std::getenv("ROCP_TOOL_LIBRARIES") || std::getenv("HSA_TOOLS_LIB");
+}
+
+// Leaves the handle without words, i.e. with event waits, under a profiler and where the GPU has none to give.
 void done_words_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
+  if (profiled()) return;
   std::lock_guard<std::mutex> g(g_done_mu);
   std::vector<DoneWord>& spare = g_done_free[p->device];
   if (spare.size() < 2) {

@@ -99,7 +99,7 @@ hipError_t hipStreamSynchronize(hipStream_t s);
 hipError_t hipStreamQuery(hipStream_t s);
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 // A wait for a value holds its stream back until the word at `p` is at least `value`; the word is compared whenever the
-// executor looks at the stream, as the command processor does.
+// executor looks at the stream, as the runtime's polling kernel does.
 hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned flags, uint64_t mask);
 hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned flags);
 hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned flags);

@@ -133,7 +133,34 @@ bool rule(int L, int64_t chunk, int64_t N) {
 
 }  // namespace
 
+// Under a profiling tool, which may run one kernel at a time, a handle has no words to wait for numbers in.
+void handle_under_a_profiler() {
+  void *pool = nullptr, *arena = nullptr;
+  (void)hipMalloc(&pool, 32 * 1024);
+  (void)hipMalloc(&arena, 16 * 2048);
+  kv_pool_config kc{};
+  kc.struct_size = sizeof(kc);
+  kc.num_layers = 1; kc.num_kv_heads = 1; kc.head_dim = 64; kc.block_size = 8; kc.dtype = KV_F16; kc.num_blocks = 16;
+  kc.block_stride = 1024; kc.kv_stride = 16 * 1024; kc.layer_stride = 32 * 1024;
+  kc.pool_dev = pool; kc.staging_host = arena; kc.staging_bytes = 16 * 2048; kc.flags = KV_STAGING_DEVICE;
+  for (const char* tool : {"", "ROCP_TOOL_LIBRARIES", "HSA_TOOLS_LIB"}) {
+    if (*tool) setenv(tool, "tool.so", 1);
+    kv_pool* p = nullptr;
+    if (kv_pool_create(&kc, &p) != KV_OK) die("kv_pool_create", 0, 0);
+    if ((p->done_word[0] || p->done_word[1]) == (*tool != 0)) die("words of a handle under a profiler", *tool, 0);
+    const uint64_t id = 1;
+    const int32_t off[2] = {0, 2}, blk[2] = {5, 6}, tok = 16;
+    if (kv_swap_out(p, 1, &id, off, blk, &tok, nullptr) != KV_OK || kv_swap_in(p, 1, &id, off, blk, 0, nullptr) != KV_OK || kv_sync(p) != KV_OK)
+      die("swap of a handle under a profiler", *tool, 0);
+    if (kv_pool_destroy(p) != KV_OK) die("kv_pool_destroy", 0, 0);
+    if (*tool) unsetenv(tool);
+  }
+  (void)hipFree(pool);
+  (void)hipFree(arena);
+}
+
 int main() {
+  handle_under_a_profiler();
   std::mt19937_64 rng(17);
   for (int layout = 0; layout < 4; layout++)
     for (int scales = 0; scales < 2; scales++)
