@@ -676,12 +676,11 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   if (p->plan_only || (n == 0 && !wait_event)) return KV_OK;
 
   hipStream_t st = p->stream[kEvict];
-  const bool captured = capturing(st);
   // after everything the load stream has been given so far (it may still write blocks this move reads, or read
   // blocks it overwrites), and after the caller's event.  A load stream that has nothing left to do needs no event (a move
   // of two blocks 24-26 us with it, 11 without).
   bool idle = false;
-  if (!captured && !capturing(p->stream[kLoad])) {
+  if (!capturing(st) && !capturing(p->stream[kLoad])) {
     idle = hipStreamQuery(p->stream[kLoad]) == hipSuccess;
     if (!idle) (void)hipGetLastError();
   }
@@ -691,6 +690,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   }
   hipEvent_t callers = (hipEvent_t)wait_event;
   if (callers) HIPCHK(p, hipStreamWaitEvent(st, callers, 0));
+  const bool captured = capturing(st);  // (asked behind the two waits, either of which may have drawn the stream into a capture)
   if (n > 0) {
     // Short lists travel inside the arguments of the move itself.  The array keeps the previous call's descriptors: [0, n)
     // is overwritten here, in stream order behind the previous call's kernel, and nothing beyond n is read.

@@ -16,13 +16,15 @@
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <vector>
 
 typedef int hipError_t;
-enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600 };
+enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600, hipErrorStreamCaptureUnsupported = 900 };
 enum { hipStreamNonBlocking = 1 };
 enum { hipHostMallocDefault = 0 };
 enum { hipMallocSignalMemory = 2 };
 enum { hipStreamWaitValueGte = 0 };
+enum hipStreamCaptureMode { hipStreamCaptureModeGlobal = 0, hipStreamCaptureModeThreadLocal = 1, hipStreamCaptureModeRelaxed = 2 };
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
 enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
 enum hipMemoryType { hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2 };
@@ -43,6 +45,15 @@ void set_policy(int policy, Stream* starved);
 void enqueue(Stream* s, std::function<void()> fn);
 long executed_ops();
 long deadlocks();
+// Capture of one graph at a time.  What is enqueued on a stream that takes part is kept instead of run; a stream takes
+// part once it waits for an event recorded on one that does.  replay() enqueues the graph on a stream, in the order it was
+// captured in.  capture_errors(): calls that a real runtime refuses meanwhile: on such a stream host waits and waits for events from
+// outside or for a value, and queries of whatever stream or event by a thread whose mode is not relaxed.
+typedef std::vector<std::function<void()>> Graph;
+void begin_capture(Stream* s);
+Graph end_capture();
+void replay(Stream* s, const Graph& g);
+long capture_errors();
 // Calls so far that take or give back a resource on a real device: hipMalloc, hipHostMalloc, hipFree, hipHostFree,
 // event and stream creation and destruction.  An entry point that promises not to allocate leaves it unchanged.
 long resource_calls();
@@ -103,7 +114,8 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned flags, uint64_t mask);
 hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned flags);
 hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned flags);
-hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);  // nothing is captured here
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode);
 hipError_t hipEventCreate(hipEvent_t* e);
 hipError_t hipEventDestroy(hipEvent_t e);
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s);

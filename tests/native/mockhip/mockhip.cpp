@@ -19,6 +19,7 @@ struct Event {
   uint64_t recorded = 0;   // generation of the latest hipEventRecord
   uint64_t completed = 0;  // newest generation whose record operation has executed
   double t = 0;            // clock value when that happened
+  bool captured = false;   // the latest hipEventRecord went into a graph
 };
 struct Op {
   int kind;  // 0 function, 1 record, 2 wait, 3 wait for a value
@@ -29,6 +30,7 @@ struct Op {
 };
 struct Stream {
   std::deque<Op> q;
+  bool capturing = false;  // what is enqueued goes into `graph`
 };
 struct Alloc {
   size_t size;
@@ -44,6 +46,10 @@ static double clock_ms = 0;
 static long n_exec = 0, n_deadlock = 0;
 static hipError_t last_error = hipSuccess;
 static Stream null_stream;
+static Graph graph;
+static std::vector<Stream*> captured_streams;
+static long n_capture_errors = 0;
+static thread_local hipStreamCaptureMode thread_mode = hipStreamCaptureModeGlobal;
 // One lock around the whole stand-in: the program under test may call from several threads.  A blocking wait
 // takes it once per step of the "GPU", so that other threads get in between the steps as they would on hardware.
 static std::recursive_mutex api_mu;
@@ -135,7 +141,34 @@ void set_policy(int p, Stream* s) {
   policy = p;
   starved = s;
 }
+static void join_capture(Stream* s) {
+  if (s->capturing) return;
+  s->capturing = true;
+  captured_streams.push_back(s);
+}
+void begin_capture(Stream* s) {
+  API_LOCK;
+  graph.clear();
+  join_capture(s);
+}
+Graph end_capture() {
+  API_LOCK;
+  for (Stream* s : captured_streams) s->capturing = false;
+  captured_streams.clear();
+  return std::move(graph);
+}
+long capture_errors() { return n_capture_errors; }
+// what invalidates a capture on a real device: among other things a query while one is going on, of any stream or event
+static bool forbidden() { return !captured_streams.empty() && thread_mode != hipStreamCaptureModeRelaxed; }
+static hipError_t capture_error() {
+  n_capture_errors++;
+  return last_error = hipErrorStreamCaptureUnsupported;
+}
 static void push_fn(Stream* s, std::function<void()> fn) {
+  if (S(s)->capturing) {
+    graph.push_back(std::move(fn));
+    return;
+  }
   S(s)->q.push_back({0, std::move(fn), nullptr, 0});
   progress();
 }
@@ -143,6 +176,10 @@ void enqueue(Stream* s, std::function<void()> fn) {
   API_LOCK;
   if (injected()) return;  // a failed launch: hipGetLastError() reports it
   push_fn(s, std::move(fn));
+}
+void replay(Stream* s, const Graph& g) {
+  API_LOCK;
+  for (const auto& fn : g) push_fn(s, fn);
 }
 void fail_after(long n, int code) {
   API_LOCK;
@@ -257,18 +294,25 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
     if (injected()) return fail_code;
   }
   Stream* st = S(s);
+  if (st->capturing) return capture_error();
   drive([&] { return st->q.empty(); });
   return hipSuccess;
 }
 hipError_t hipStreamQuery(hipStream_t s) {
   API_LOCK;
   if (injected()) return fail_code;
+  if (forbidden() || S(s)->capturing) return capture_error();
   return S(s)->q.empty() ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
   API_LOCK;
   if (injected()) return fail_code;
+  if (e->captured && !captured_streams.empty()) {  // the stream joins the capture
+    join_capture(S(s));
+    return hipSuccess;
+  }
   if (e->recorded == 0) return hipSuccess;  // never recorded: nothing to wait for
+  if (S(s)->capturing) return capture_error();
   S(s)->q.push_back({2, nullptr, e, e->recorded});
   progress();
   return hipSuccess;
@@ -276,6 +320,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
 hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned, uint64_t) {
   API_LOCK;
   if (injected()) return fail_code;
+  if (S(s)->capturing) return capture_error();
   S(s)->q.push_back({3, nullptr, nullptr, value, (const volatile uint64_t*)p});
   progress();
   return hipSuccess;
@@ -296,8 +341,13 @@ hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned) {
   *p = &words.back();
   return hipSuccess;
 }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* status) {
-  *status = hipStreamCaptureStatusNone;
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+  API_LOCK;
+  *status = S(s)->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode) {
+  std::swap(*mode, thread_mode);
   return hipSuccess;
 }
 hipError_t hipEventCreate(hipEvent_t* e) {
@@ -323,6 +373,8 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
   API_LOCK;
   if (injected()) return fail_code;
+  e->captured = S(s)->capturing;
+  if (e->captured) return hipSuccess;
   e->recorded++;
   S(s)->q.push_back({1, nullptr, e, e->recorded});
   progress();
@@ -331,6 +383,7 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 hipError_t hipEventQuery(hipEvent_t e) {
   API_LOCK;
   if (injected()) return fail_code;
+  if (e->captured ? !captured_streams.empty() : e->recorded && forbidden()) return capture_error();
   return e->completed >= e->recorded ? hipSuccess : hipErrorNotReady;
 }
 hipError_t hipEventSynchronize(hipEvent_t e) {

@@ -1,0 +1,129 @@
+// Paths of the runtime that the serving histories of runtime_on_mock_hip.cpp do not take, on the stand-in HIP runtime, against
+// plain loops over the pool's bytes.  One section per argument.
+#include <random>
+
+#include "kvswap.hip"
+
+namespace {
+
+[[noreturn]] void die(const char* what, long a = 0, long b = 0) {
+  std::printf("FAILED: %s (%ld, %ld)\n", what, a, b);
+  std::exit(1);
+}
+#define OK(expr)                                        \
+  do {                                                  \
+    const int rc_ = (expr);                             \
+    if (rc_ != KV_OK) die(#expr, rc_, __LINE__);        \
+  } while (0)
+
+// A layer-major pool of N blocks of 2 x 2 chunks of 64 bytes, its arena and a handle on streams of its own.
+struct Pool {
+  static constexpr int64_t chunk = 64, planes = 4;
+  int64_t N;
+  char *pool = nullptr, *arena = nullptr;
+  hipStream_t st[2];
+  kv_pool_config kc{};
+  kv_pool* h = nullptr;
+  explicit Pool(int64_t n, int64_t slots = 16, uint32_t flags = KV_STAGING_DEVICE) : N(n) {
+    (void)hipMalloc((void**)&pool, (size_t)(N * planes * chunk));
+    if (flags & KV_STAGING_DEVICE)
+      (void)hipMalloc((void**)&arena, (size_t)(slots * planes * chunk));
+    else
+      (void)hipHostMalloc((void**)&arena, (size_t)(slots * planes * chunk), 0);
+    for (auto& s : st) (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    kc.struct_size = sizeof(kc);
+    kc.num_layers = 2; kc.num_kv_heads = 1; kc.head_dim = 32; kc.block_size = 1; kc.dtype = KV_F16; kc.num_blocks = N;
+    kc.block_stride = chunk; kc.kv_stride = N * chunk; kc.layer_stride = 2 * N * chunk;
+    kc.pool_dev = pool; kc.staging_host = arena; kc.staging_bytes = slots * planes * chunk;
+    kc.evict_stream = st[0]; kc.load_stream = st[1]; kc.flags = flags;
+    OK(kv_pool_create(&kc, &h));
+    std::mt19937_64 rng(7);
+    for (int64_t i = 0; i < N * planes * chunk; i++) pool[i] = (char)rng();
+  }
+  ~Pool() {
+    OK(kv_pool_destroy(h));
+    for (auto& s : st) (void)hipStreamDestroy(s);
+    (void)hipFree(pool);
+    (void)hipFree(arena);
+  }
+  std::vector<char> bytes() const { return std::vector<char>(pool, pool + N * planes * chunk); }
+};
+
+struct Moves {
+  std::vector<int32_t> src, dst;
+  Moves(std::mt19937_64& rng, int64_t N, size_t n) {
+    std::vector<int32_t> perm((size_t)N);
+    for (size_t i = 0; i < perm.size(); i++) perm[i] = (int32_t)i;
+    std::shuffle(perm.begin(), perm.end(), rng);
+    src.assign(perm.begin(), perm.begin() + (long)n);
+    dst.assign(perm.begin() + (long)n, perm.begin() + 2 * (long)n);
+  }
+  void apply(const Pool& p, std::vector<char>* to) const {
+    for (size_t i = 0; i < src.size(); i++)
+      for (int64_t k = 0; k < Pool::planes; k++)
+        std::memcpy(to->data() + (k * p.N + dst[i]) * Pool::chunk, to->data() + (k * p.N + src[i]) * Pool::chunk, Pool::chunk);
+  }
+  int run(const Pool& p, hipEvent_t wait = nullptr) const {
+    return kv_move_blocks_noalloc(p.h, (int64_t)src.size(), src.data(), dst.data(), wait);
+  }
+};
+
+// An allocation-free move inside a graph moves the blocks it was captured with, whatever the handle does between the
+// capture and a replay.  The evict stream joins the capture through the caller's event, or through the load stream's fence.
+void capture() {
+  std::mt19937_64 rng(1);
+  for (int through = 0; through < 2; through++)
+    for (size_t n : {7, 61, 100, 449, 1000}) {
+      Pool p(2 * (int64_t)n + 3);
+      hipStream_t origin;
+      hipEvent_t fork, join;
+      (void)hipStreamCreateWithFlags(&origin, hipStreamNonBlocking);
+      (void)hipEventCreate(&fork);
+      (void)hipEventCreate(&join);
+      const Moves first(rng, p.N, n);
+      std::vector<char> want = p.bytes();
+      mockhip::begin_capture(origin);
+      (void)hipEventRecord(fork, origin);
+      if (through == 1) (void)hipStreamWaitEvent(p.st[1], fork, 0);
+      OK(first.run(p, through == 0 ? fork : nullptr));
+      hipStreamCaptureStatus on;
+      (void)hipStreamIsCapturing(p.st[0], &on);
+      if (on != hipStreamCaptureStatusActive) die("the evict stream is not in the capture", through, (long)n);
+      (void)hipEventRecord(join, p.st[0]);
+      (void)hipStreamWaitEvent(origin, join, 0);
+      const mockhip::Graph g = mockhip::end_capture();
+      if (p.bytes() != want) die("a captured move has run", through, (long)n);
+      for (int turn = 0; turn < 6; turn++) {  // more calls than the handle has upload buffers
+        const Moves other(rng, p.N, n);
+        OK(other.run(p));
+        other.apply(p, &want);
+        OK(kv_sync(p.h));
+        if (turn % 2) {
+          mockhip::replay(origin, g);
+          first.apply(p, &want);
+          (void)hipStreamSynchronize(origin);
+        }
+        if (p.bytes() != want) die("a replay moves other blocks: through, n", through, (long)n);
+      }
+      (void)hipStreamDestroy(origin);
+      (void)hipEventDestroy(fork);
+      (void)hipEventDestroy(join);
+    }
+}
+
+}  // namespace
+
+int main(int argc, char** argv) {
+  const struct {
+    const char* name;
+    void (*run)();
+  } sections[] = {{"capture", capture}};
+  for (const auto& s : sections)
+    if (argc == 2 && !std::strcmp(argv[1], s.name)) {
+      mockhip::reset(5);
+      s.run();
+      std::printf("%s ok\n", s.name);
+      return 0;
+    }
+  die("no such section");
+}

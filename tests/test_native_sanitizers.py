@@ -131,6 +131,24 @@ def test_the_two_job_orders_move_the_same_bytes(tmp_path):
 
 
 @pytest.fixture(scope="module")
+def rare_paths(tmp_path_factory):
+    if not os.path.exists(CLANGXX):
+        pytest.skip("no host clang++ for the kernel source")
+    exe = str(tmp_path_factory.mktemp("rare") / "rare_paths")
+    subprocess.check_call([CLANGXX, "-std=c++17", "-pthread", "-Wno-unused-function", "-I", MOCK, "-I", os.path.join(ROOT, "include"), "-I", CSRC] +
+                          SAN + ["-x", "c++", os.path.join(HERE, "native", "rare_paths.cpp"), os.path.join(MOCK, "mockhip.cpp"), "-o", exe])
+    return exe
+
+
+@pytest.mark.parametrize("section", ["capture"])
+def test_paths_that_no_history_takes(rare_paths, section):
+    """See tests/native/rare_paths.cpp, which says at each section what it runs."""
+    env = dict(os.environ, ASAN_OPTIONS=ASAN_OPTS, UBSAN_OPTIONS="print_stacktrace=1")
+    r = subprocess.run([rare_paths, section], capture_output=True, text=True, timeout=300, env=env)
+    assert r.returncode == 0 and section + " ok" in r.stdout, r.stdout + r.stderr
+
+
+@pytest.fixture(scope="module")
 def mock_driver(tmp_path_factory):
     if not os.path.exists(CLANGXX):
         pytest.skip("no host clang++ for the kernel source")
