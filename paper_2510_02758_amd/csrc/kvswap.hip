@@ -681,8 +681,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   // of two blocks 24-26 us with it, 11 without).
   bool idle = false;
   if (!capturing(st) && !capturing(p->stream[kLoad])) {
-    idle = hipStreamQuery(p->stream[kLoad]) == hipSuccess;
-    if (!idle) (void)hipGetLastError();
+    idle = query_relaxed([&] { return hipStreamQuery(p->stream[kLoad]); });
   }
   if (!idle) {
     HIPCHK(p, hipEventRecord(p->na_fence_ev, p->stream[kLoad]));
@@ -699,7 +698,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     if ((size_t)n > most_inline(p, 2, (size_t)n, hbm) && !captured)
       for (int t = 0; t < p->na_bufs && up < 0; t++) {  // the one used longest ago first
         const int k = (p->na_turn + t) % p->na_bufs;
-        if (hipEventQuery(p->na_up_ev[k]) == hipSuccess) up = k;
+        if (query_relaxed([&] { return hipEventQuery(p->na_up_ev[k]); })) up = k;
       }
     const bool inline_desc = up < 0 && n <= (hbm ? kInlineDescMax : kMoveDescMax);
     (void)hipGetLastError();

@@ -105,6 +105,7 @@ void capture() {
         }
         if (p.bytes() != want) die("a replay moves other blocks: through, n", through, (long)n);
       }
+      if (mockhip::capture_errors()) die("calls that a capture does not allow", mockhip::capture_errors(), (long)n);
       (void)hipStreamDestroy(origin);
       (void)hipEventDestroy(fork);
       (void)hipEventDestroy(join);

@@ -116,3 +116,39 @@ def test_noalloc_move_is_ordered_against_swap_in(gpu):
     assert np.array_equal(pool.cpu().numpy(), ora_pool)
     assert np.array_equal(arena.numpy(), ora_stage)
     kp.close()
+
+
+@pytest.mark.parametrize("n", [40, 300, 700])
+def test_noalloc_move_inside_a_graph(gpu, n):
+    """Captured in the default mode, the evict stream joining the capture through the caller's event: the call makes no
+    query that would invalidate the capture, and every replay moves the blocks of the captured list, whatever the handle has
+    moved in between (lists of 300 and 700 blocks are then uploaded from its buffers)."""
+    import torch
+    g = W.Geometry(2, 2, 8, 2, "f16", 2000)
+    host_pool = W.fill_buffer_np(0x5EED0A02, g.pool_bytes, g.dtype)
+    rng = np.random.default_rng(n)
+    ora_pool = host_pool.copy()
+    ora = ko.Oracle(g.L, g.H, g.D, g.B, g.e, g.N, ora_pool, g.strides, np.zeros(g.S, np.uint8))
+    pool = torch.from_numpy(host_pool.copy()).to(gpu)
+    evict, load = torch.cuda.Stream(), torch.cuda.Stream()
+    kp = kv.KVPool(g, pool, torch.zeros(2 * g.S, dtype=torch.uint8).pin_memory(), evict_stream=evict, load_stream=load)
+    first = _moves(rng, g.N, n)
+    graph, fork, join = torch.cuda.CUDAGraph(), torch.cuda.Event(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        here = torch.cuda.current_stream()
+        fork.record(here)
+        assert kp.move_blocks_noalloc(*first, wait_event=fork.cuda_event) == kv.KV_OK
+        join.record(evict)
+        here.wait_event(join)
+    torch.cuda.synchronize()
+    assert np.array_equal(pool.cpu().numpy(), ora_pool), "a captured move has run"
+    for _ in range(6):
+        other = _moves(rng, g.N, n)
+        assert kp.move_blocks_noalloc(*other) == kv.KV_OK and ora.move_blocks(*other) == ko.OK
+        assert kp.sync() == kv.KV_OK
+        graph.replay()
+        assert ora.move_blocks(*first) == ko.OK
+        torch.cuda.synchronize()
+        assert np.array_equal(pool.cpu().numpy(), ora_pool)
+    kp.close()
