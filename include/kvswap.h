@@ -164,7 +164,8 @@ typedef struct {
                        nothing else: the device's clock from the launch's first workgroup to its last) */
   float ms_kernel;  /* summed duration of the data kernels (HIP events around each launch); a call that is a
                        single launch and nothing else carries no events of its own and reports ms_total */
-  int32_t scatter_order; /* large scatter with both ends in HBM: 0 block by block, 1 plane by plane; -1 otherwise */
+  int32_t scatter_order; /* scatter with both ends in HBM that is large, or goes plane by plane because its pool's planes lie on
+                            few memory channels: 0 block by block, 1 plane by plane; -1 otherwise */
   int32_t reserved;
 } kv_stats;
 

@@ -16,15 +16,15 @@ namespace {
     if (rc_ != KV_OK) die(#expr, rc_, __LINE__);        \
   } while (0)
 
-// A layer-major pool of N blocks of 2 x 2 chunks of 64 bytes, its arena and a handle on streams of its own.
+// A layer-major pool of N blocks of 2 x 2 chunks, its arena and a handle on streams of its own.
 struct Pool {
-  static constexpr int64_t chunk = 64, planes = 4;
-  int64_t N;
+  static constexpr int64_t planes = 4;
+  int64_t N, chunk;
   char *pool = nullptr, *arena = nullptr;
   hipStream_t st[2];
   kv_pool_config kc{};
   kv_pool* h = nullptr;
-  explicit Pool(int64_t n, int64_t slots = 16, uint32_t flags = KV_STAGING_DEVICE) : N(n) {
+  explicit Pool(int64_t n, int64_t slots = 16, uint32_t flags = KV_STAGING_DEVICE, int64_t chunk_bytes = 64) : N(n), chunk(chunk_bytes) {
     (void)hipMalloc((void**)&pool, (size_t)(N * planes * chunk));
     if (flags & KV_STAGING_DEVICE)
       (void)hipMalloc((void**)&arena, (size_t)(slots * planes * chunk));
@@ -32,7 +32,7 @@ struct Pool {
       (void)hipHostMalloc((void**)&arena, (size_t)(slots * planes * chunk), 0);
     for (auto& s : st) (void)hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
     kc.struct_size = sizeof(kc);
-    kc.num_layers = 2; kc.num_kv_heads = 1; kc.head_dim = 32; kc.block_size = 1; kc.dtype = KV_F16; kc.num_blocks = N;
+    kc.num_layers = 2; kc.num_kv_heads = 1; kc.head_dim = (int32_t)(chunk / 2); kc.block_size = 1; kc.dtype = KV_F16; kc.num_blocks = N;
     kc.block_stride = chunk; kc.kv_stride = N * chunk; kc.layer_stride = 2 * N * chunk;
     kc.pool_dev = pool; kc.staging_host = arena; kc.staging_bytes = slots * planes * chunk;
     kc.evict_stream = st[0]; kc.load_stream = st[1]; kc.flags = flags;
@@ -61,7 +61,7 @@ struct Moves {
   void apply(const Pool& p, std::vector<char>* to) const {
     for (size_t i = 0; i < src.size(); i++)
       for (int64_t k = 0; k < Pool::planes; k++)
-        std::memcpy(to->data() + (k * p.N + dst[i]) * Pool::chunk, to->data() + (k * p.N + src[i]) * Pool::chunk, Pool::chunk);
+        std::memcpy(to->data() + (k * p.N + dst[i]) * p.chunk, to->data() + (k * p.N + src[i]) * p.chunk, (size_t)p.chunk);
   }
   int run(const Pool& p, hipEvent_t wait = nullptr) const {
     return kv_move_blocks_noalloc(p.h, (int64_t)src.size(), src.data(), dst.data(), wait);
@@ -112,13 +112,40 @@ void capture() {
     }
 }
 
+// kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (41 MiB: such a scatter goes
+// plane by plane from 40 MiB on).
+void scatter_order() {
+  const int n = 656, N = 700;
+  Pool p(N, n, KV_STAGING_DEVICE, 16384);
+  const uint64_t id = 3;
+  const int32_t off[2] = {0, n}, tok = n;
+  std::vector<int32_t> ids(n);
+  for (int i = 0; i < n; i++) ids[(size_t)i] = i * 17 % N;
+  const std::vector<char> want = p.bytes();
+  for (bool collide : {false, true})
+    for (int knob = 0; knob < 3; knob++) {
+      p.h->planes_collide = collide;
+      OK(kv_pool_tune(p.h, KV_TUNE_SCATTER_ORDER, knob));
+      kv_stats st{};
+      st.struct_size = sizeof(st);
+      OK(kv_swap_out(p.h, 1, &id, off, ids.data(), &tok, nullptr));
+      OK(kv_last_stats(p.h, &st));
+      if (st.scatter_order != -1) die("order of a gather", st.scatter_order, knob);
+      for (int i = 0; i < n; i++) std::memset(p.pool + ids[(size_t)i] * p.chunk, 0, (size_t)p.chunk);
+      OK(kv_swap_in(p.h, 1, &id, off, ids.data(), 0, nullptr));
+      OK(kv_last_stats(p.h, &st));
+      if (st.scatter_order != (knob == 2 || (collide && knob == 0) ? 1 : -1)) die("order of a scatter, knob", st.scatter_order, knob);
+      if (p.bytes() != want) die("bytes of a swap, knob", collide, knob);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } sections[] = {{"capture", capture}};
+  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       mockhip::reset(5);

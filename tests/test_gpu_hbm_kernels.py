@@ -199,5 +199,6 @@ def test_pool_whose_planes_collide(gpu):
     for lib in (ora, gpu_lib):
         assert lib.swap_out([1, 2], [0, 40, n], perm[:n], [40 * g.B, (n - 40) * g.B]) == ko.OK
         assert lib.swap_in([2, 1], [0, n - 40, n], perm[n:2 * n]) == ko.OK
+    assert gpu_lib.kp.stats()["scatter_order"] == 1
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     gpu_lib.close()
