@@ -139,13 +139,37 @@ void scatter_order() {
     }
 }
 
+// kv_stats.ms_kernel of an exchange is its kernels alone, without what the load has waited for, also where a launch does not
+// time itself (a workgroup cap: kv_move_kernel).
+void exchange_times() {
+  for (int cap : {0, 4}) {
+    const int n = 8;
+    Pool p(40, 2 * n);
+    OK(kv_pool_tune(p.h, KV_TUNE_MAX_WGS_DEVICE, cap));
+    const uint64_t out = 1, in = 2;
+    const int32_t off[2] = {0, n}, tok = n;
+    int32_t a[n], b[n];
+    for (int i = 0; i < n; i++) a[i] = i, b[i] = 20 + i;
+    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+    OK(kv_sync(p.h));
+    mockhip::set_policy(mockhip::kLazy, nullptr);  // nothing runs before the host waits: the load waits for the eviction
+    OK(kv_evict_and_load(p.h, 1, &out, off, a, &tok, 1, &in, off, a, 0, nullptr));
+    kv_stats st{};
+    st.struct_size = sizeof(st);
+    OK(kv_last_stats(p.h, &st));
+    if (st.op != 3 || st.launches != 1 || !(st.ms_kernel > 0)) die("statistics of an exchange's load", st.op, st.launches);
+    if (cap ? st.ms_kernel >= st.ms_total : st.ms_kernel != st.ms_total) die("ms_kernel of an exchange's load, cap", cap, (long)(st.ms_kernel * 1e6));
+    mockhip::set_policy(mockhip::kRandom, nullptr);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}};
+  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       mockhip::reset(5);

@@ -140,7 +140,7 @@ def rare_paths(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("section", ["capture", "scatter_order"])
+@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times"])
 def test_paths_that_no_history_takes(rare_paths, section):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""
     env = dict(os.environ, ASAN_OPTIONS=ASAN_OPTS, UBSAN_OPTIONS="print_stacktrace=1")
