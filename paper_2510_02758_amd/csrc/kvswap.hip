@@ -9,8 +9,6 @@
 //              run of consecutive staging slots (and the mirror image for loads).
 // With KV_STAGING_DEVICE the arena is HBM and the same kernels give the
 // on-device gather/scatter.
-#include <dlfcn.h>
-
 #include "runtime.hip.inc"
 
 // Entry of a call that changes state or enqueues work: takes the handle's lock and refuses a handle on which an
@@ -130,16 +128,12 @@ std::vector<DoneWord> g_done_free[kMaxDevices];
 size_t g_done_taken[kMaxDevices] = {};
 constexpr int kDoneBatch = 8;  // taken at a time: 7 to 30 us each, in front of the first of four handles
 
-// The runtime waits for a number with a kernel of one wavefront that polls the word.  A profiler that collects counters lets one
-// kernel run at a time, and such a kernel would keep the one that stores the number from running: under a profiling tool (which
-// exports rocprofiler_configure, or is named in the environment) handles hand over by event.
-bool profiled() {
-  return dlsym(RTLD_DEFAULT, "rocprofiler_configure") || std::getenv("ROCP_TOOL_LIBRARIES") || std::getenv("HSA_TOOLS_LIB");
-}
-
-// Leaves the handle without words, i.e. with event waits, under a profiler and where the GPU has none to give.
+// Leaves the handle without words, i.e. with event waits, where a wait for a number might not end and where the GPU has no
+// words to give.
 void done_words_setup(kv_pool* p) {  // after noalloc_setup, which sets p->device
-  if (profiled()) return;
+  if (!submits_at_once()) return;
+  look_for_profiler(p);
+  if (!p->by_number) return;
   std::lock_guard<std::mutex> g(g_done_mu);
   std::vector<DoneWord>& spare = g_done_free[p->device];
   if (spare.size() < 2) {

@@ -54,6 +54,7 @@ void begin_capture(Stream* s);
 Graph end_capture();
 void replay(Stream* s, const Graph& g);
 long capture_errors();
+long value_waits();  // calls of hipStreamWaitValue64 so far
 // Calls so far that take or give back a resource on a real device: hipMalloc, hipHostMalloc, hipFree, hipHostFree,
 // event and stream creation and destruction.  An entry point that promises not to allocate leaves it unchanged.
 long resource_calls();

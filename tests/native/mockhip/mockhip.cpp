@@ -49,6 +49,7 @@ static Stream null_stream;
 static Graph graph;
 static std::vector<Stream*> captured_streams;
 static long n_capture_errors = 0;
+static long n_value_waits = 0;
 static thread_local hipStreamCaptureMode thread_mode = hipStreamCaptureModeGlobal;
 // One lock around the whole stand-in: the program under test may call from several threads.  A blocking wait
 // takes it once per step of the "GPU", so that other threads get in between the steps as they would on hardware.
@@ -158,6 +159,7 @@ Graph end_capture() {
   return std::move(graph);
 }
 long capture_errors() { return n_capture_errors; }
+long value_waits() { return n_value_waits; }
 // what invalidates a capture on a real device: among other things a query while one is going on, of any stream or event
 static bool forbidden() { return !captured_streams.empty() && thread_mode != hipStreamCaptureModeRelaxed; }
 static hipError_t capture_error() {
@@ -321,6 +323,7 @@ hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned
   API_LOCK;
   if (injected()) return fail_code;
   if (S(s)->capturing) return capture_error();
+  n_value_waits++;
   S(s)->q.push_back({3, nullptr, nullptr, value, (const volatile uint64_t*)p});
   progress();
   return hipSuccess;

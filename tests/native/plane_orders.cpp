@@ -80,6 +80,7 @@ void compare(std::mt19937_64& rng, int L, int H, int D, int B, bool scales, int 
         p.leave[s] = finish ? words[s] : nullptr;
         p.done_word[s] = finish ? &done[s] : nullptr;
       }
+      p.by_number = finish;
       std::vector<char> out[2], arena[2];
       const std::vector<char> pool0 = pool, scale0 = scale;
       for (int pm = 0; pm < 2; pm++) {

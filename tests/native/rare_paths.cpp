@@ -1,5 +1,5 @@
 // Paths of the runtime that the serving histories of runtime_on_mock_hip.cpp do not take, on the stand-in HIP runtime, against
-// plain loops over the pool's bytes.  One section per argument.
+// plain loops over the pool's bytes.  One section per run, named by the argument.
 #include <random>
 
 #include "kvswap.hip"
@@ -163,9 +163,60 @@ void exchange_times() {
   }
 }
 
+// Streams hand over by event, and not by number, where the number's wait might not end: as soon as a profiling tool has been loaded
+// (argument of the section: a library that is one), and where threads of the runtime submit the streams' work.
+void late_profiler(const char* tool) {
+  const int n = 4;
+  const uint64_t id = 3;
+  const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
+  auto swap = [&](Pool& p) {
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    const long before = mockhip::value_waits();
+    std::vector<char> want = p.bytes();
+    for (int i = 0; i < n; i++)
+      for (int64_t k = 0; k < Pool::planes; k++)
+        std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, p.pool + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
+    OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
+    OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
+    OK(kv_sync(p.h));
+    if (p.bytes() != want) die("bytes of a swap");
+    const uint64_t in = 8;  // an exchange whose load takes the evicted blocks
+    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+    OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
+    OK(kv_req_release(p.h, id));
+    OK(kv_sync(p.h));
+    for (int i = 0; i < n; i++)
+      if (std::memcmp(p.pool + a[i] * p.chunk, want.data() + b[i] * p.chunk, (size_t)p.chunk)) die("bytes of an exchange", i);
+    return mockhip::value_waits() - before;
+  };
+  {
+    setenv("AMD_DIRECT_DISPATCH", "0", 1);
+    Pool p(9);
+    if (swap(p)) die("a wait for a number where the runtime's threads submit");
+    setenv("AMD_DIRECT_DISPATCH", "1", 1);
+    Pool q(9);
+    if (!swap(q)) die("no wait for a number");
+    unsetenv("AMD_DIRECT_DISPATCH");
+  }
+  Pool p(9), q(9);
+  if (swap(p) < 2) die("no wait for a number");
+  const uint64_t id2 = 5;  // enqueued with a number, waited for after the tool has come
+  OK(kv_swap_out(q.h, 1, &id2, off, a, &tok, nullptr));
+  if (!dlopen(tool, RTLD_NOW | RTLD_GLOBAL)) die("the tool cannot be loaded");
+  const long before = mockhip::value_waits();
+  OK(kv_swap_in(q.h, 1, &id2, off, b, 0, nullptr));
+  OK(kv_sync(q.h));
+  if (swap(p) || swap(q) || mockhip::value_waits() != before) die("a wait for a number under a tool that came late");
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
+  if (argc == 3 && !std::strcmp(argv[1], "late_profiler")) {
+    late_profiler(argv[2]);
+    std::printf("late_profiler ok\n");
+    return 0;
+  }
   const struct {
     const char* name;
     void (*run)();

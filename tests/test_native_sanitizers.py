@@ -140,11 +140,16 @@ def rare_paths(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times"])
-def test_paths_that_no_history_takes(rare_paths, section):
+@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times", "late_profiler"])
+def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""
     env = dict(os.environ, ASAN_OPTIONS=ASAN_OPTS, UBSAN_OPTIONS="print_stacktrace=1")
-    r = subprocess.run([rare_paths, section], capture_output=True, text=True, timeout=300, env=env)
+    args = [section]
+    if section == "late_profiler":    # a library that exports what profiling tools export
+        (tmp_path / "tool.c").write_text("void* rocprofiler_configure(void) { return 0; }\n")
+        args.append(str(tmp_path / "tool.so"))
+        subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", args[1], str(tmp_path / "tool.c")])
+    r = subprocess.run([rare_paths] + args, capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0 and section + " ok" in r.stdout, r.stdout + r.stderr
 
 
