@@ -113,7 +113,6 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
 // A wait for a value holds its stream back until the word at `p` is at least `value`; the word is compared whenever the
 // executor looks at the stream, as the runtime's polling kernel does.
 hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned flags, uint64_t mask);
-hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned flags);
 hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned flags);
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status);
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode);

@@ -328,12 +328,6 @@ hipError_t hipStreamWaitValue64(hipStream_t s, void* p, uint64_t value, unsigned
   progress();
   return hipSuccess;
 }
-hipError_t hipStreamWriteValue64(hipStream_t s, void* p, uint64_t value, unsigned) {
-  API_LOCK;
-  if (injected()) return fail_code;
-  push_fn(s, [=]() { *(volatile uint64_t*)p = value; });
-  return hipSuccess;
-}
 // Signal memory is never freed by the library: it is kept in a list here, for the leak checker.
 hipError_t hipExtMallocWithFlags(void** p, size_t n, unsigned) {
   API_LOCK;
