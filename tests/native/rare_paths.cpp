@@ -163,50 +163,136 @@ void exchange_times() {
   }
 }
 
+// Allocation-free moves in a row while the evict stream is held back: from the upload buffers as long as one is free, then (none
+// is free before the stream runs) inside the arguments of the move or of fill launches.
+void uploads() {
+  std::mt19937_64 rng(2);
+  for (int64_t N : {2003, 66000})  // four buffers, and two
+    for (size_t n : {60, 61, 448, 449, 897, 1000}) {
+      Pool p(N);
+      std::vector<char> want = p.bytes();
+      mockhip::set_policy(mockhip::kLazy, nullptr);
+      for (int turn = 0; turn < 2; turn++) {
+        for (int k = 0; k < 7; k++) {
+          const Moves m(rng, N, n - (size_t)(k % 3));  // lists that leave the end of an earlier, longer one behind theirs
+          OK(m.run(p));
+          m.apply(p, &want);
+        }
+        OK(kv_sync(p.h));
+        if (p.bytes() != want) die("bytes of moves in a row: n, turn", (long)n, turn);
+      }
+      mockhip::set_policy(mockhip::kRandom, nullptr);
+    }
+}
+
+// One swap out and in, and one exchange, on a handle; returns the waits for a number that were made.
+long swap_and_exchange(Pool& p) {
+  const int n = 4;
+  const uint64_t id = 3, in = 8;
+  const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
+  mockhip::set_policy(mockhip::kLazy, nullptr);
+  const long before = mockhip::value_waits();
+  std::vector<char> want = p.bytes();
+  auto move = [&](const int32_t* from, const int32_t* to) {
+    const std::vector<char> was = want;
+    for (int i = 0; i < n; i++)
+      for (int64_t k = 0; k < Pool::planes; k++)
+        std::memcpy(want.data() + (k * p.N + to[i]) * p.chunk, was.data() + (k * p.N + from[i]) * p.chunk, (size_t)p.chunk);
+  };
+  kv_stats st{};
+  st.struct_size = sizeof(st);
+  OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
+  OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
+  move(a, b);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0)) die("no time of a load");
+  OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+  OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
+  move(b, a);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0) || !(st.ms_kernel > 0)) die("no time of an exchange");
+  OK(kv_req_release(p.h, id));
+  OK(kv_sync(p.h));
+  if (p.bytes() != want) die("bytes of a swap and an exchange");
+  mockhip::set_policy(mockhip::kRandom, nullptr);
+  return mockhip::value_waits() - before;
+}
+
+// Handles behind the first 128, which have no counters for launches with both ends in HBM, and behind the first 1024, whose job
+// counters of the link are an allocation of their own.
+void counters_used_up() {
+  for (int others : {0, kLeaveSlots, kTicketSlots})
+    for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
+      for (int s = 0; s < others; s++) g_ticket_taken[0][s >> 6] |= 1ull << (s & 63);  // as if that many handles were there
+      {
+        Pool p(9, 16, flags);
+        const bool device = flags & KV_STAGING_DEVICE;
+        if (p.h->ticket_slot != (others < kTicketSlots ? others : -1)) die("slot of a handle", p.h->ticket_slot, others);
+        for (int turn = 0; turn < 3; turn++) {
+          const long waits = swap_and_exchange(p);
+          if (!waits != (device && others)) die("waits for a number: others, waits", others, waits);
+        }
+      }
+      std::memset(g_ticket_taken[0], 0, sizeof(g_ticket_taken[0]));
+    }
+}
+
+// More calls in flight than there are records of the clock: the others have start events.
+void records_used_up() {
+  Pool p(9);
+  const uint64_t id = 3;
+  const int32_t off[2] = {0, 2}, tok = 2, a[2] = {1, 2}, b[2] = {5, 6};
+  const std::vector<char> before = p.bytes();
+  mockhip::set_policy(mockhip::kLazy, nullptr);
+  const int pairs = kStamps / 2 + 40;
+  for (int i = 0; i < pairs; i++) {
+    OK(kv_swap_out(p.h, 1, &id, off, i % 2 ? b : a, &tok, nullptr));
+    OK(kv_swap_in(p.h, 1, &id, off, i % 2 ? a : b, 0, nullptr));
+  }
+  if (!p.h->stamp_free.empty() || p.h->calls.back().stamp || !p.h->calls.back().start) die("records left", (long)p.h->stamp_free.size());
+  kv_stats st{};
+  st.struct_size = sizeof(st);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0)) die("no time of a call without a record");
+  OK(kv_sync(p.h));
+  std::vector<char> want = before;
+  for (int i = 0; i < 2; i++)
+    for (int64_t k = 0; k < Pool::planes; k++)
+      std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, before.data() + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
+  if (p.bytes() != want) die("bytes of calls in flight");
+  mockhip::set_policy(mockhip::kRandom, nullptr);
+  swap_and_exchange(p);
+  kv_io_stats io{};
+  io.struct_size = sizeof(io);
+  OK(kv_io_stats_get(p.h, &io));
+  if (io.total_calls[0] + io.total_calls[1] < 2 * pairs || !(io.ewma_small_us[0] > 0 && io.ewma_small_us[1] > 0)) die("telemetry", io.total_calls[0], io.total_calls[1]);
+  if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
+}
+
 // Streams hand over by event, and not by number, where the number's wait might not end: as soon as a profiling tool has been loaded
 // (argument of the section: a library that is one), and where threads of the runtime submit the streams' work.
 void late_profiler(const char* tool) {
   const int n = 4;
-  const uint64_t id = 3;
   const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
-  auto swap = [&](Pool& p) {
-    mockhip::set_policy(mockhip::kLazy, nullptr);
-    const long before = mockhip::value_waits();
-    std::vector<char> want = p.bytes();
-    for (int i = 0; i < n; i++)
-      for (int64_t k = 0; k < Pool::planes; k++)
-        std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, p.pool + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
-    OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
-    OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
-    OK(kv_sync(p.h));
-    if (p.bytes() != want) die("bytes of a swap");
-    const uint64_t in = 8;  // an exchange whose load takes the evicted blocks
-    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
-    OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
-    OK(kv_req_release(p.h, id));
-    OK(kv_sync(p.h));
-    for (int i = 0; i < n; i++)
-      if (std::memcmp(p.pool + a[i] * p.chunk, want.data() + b[i] * p.chunk, (size_t)p.chunk)) die("bytes of an exchange", i);
-    return mockhip::value_waits() - before;
-  };
   {
     setenv("AMD_DIRECT_DISPATCH", "0", 1);
     Pool p(9);
-    if (swap(p)) die("a wait for a number where the runtime's threads submit");
+    if (swap_and_exchange(p)) die("a wait for a number where the runtime's threads submit");
     setenv("AMD_DIRECT_DISPATCH", "1", 1);
     Pool q(9);
-    if (!swap(q)) die("no wait for a number");
+    if (!swap_and_exchange(q)) die("no wait for a number");
     unsetenv("AMD_DIRECT_DISPATCH");
   }
   Pool p(9), q(9);
-  if (swap(p) < 2) die("no wait for a number");
+  if (swap_and_exchange(p) < 2) die("no wait for a number");
+  mockhip::set_policy(mockhip::kLazy, nullptr);
   const uint64_t id2 = 5;  // enqueued with a number, waited for after the tool has come
   OK(kv_swap_out(q.h, 1, &id2, off, a, &tok, nullptr));
   if (!dlopen(tool, RTLD_NOW | RTLD_GLOBAL)) die("the tool cannot be loaded");
   const long before = mockhip::value_waits();
   OK(kv_swap_in(q.h, 1, &id2, off, b, 0, nullptr));
   OK(kv_sync(q.h));
-  if (swap(p) || swap(q) || mockhip::value_waits() != before) die("a wait for a number under a tool that came late");
+  if (swap_and_exchange(p) || swap_and_exchange(q) || mockhip::value_waits() != before) die("a wait for a number under a tool that came late");
 }
 
 }  // namespace
@@ -220,7 +306,8 @@ int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}};
+  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
+                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       mockhip::reset(5);

@@ -130,27 +130,74 @@ def test_the_two_job_orders_move_the_same_bytes(tmp_path):
     assert r.returncode == 0 and "orders agree" in r.stdout, r.stdout + r.stderr
 
 
-@pytest.fixture(scope="module")
-def rare_paths(tmp_path_factory):
+def _build_rare_paths(exe, csrc_dir, flags):
     if not os.path.exists(CLANGXX):
         pytest.skip("no host clang++ for the kernel source")
-    exe = str(tmp_path_factory.mktemp("rare") / "rare_paths")
-    subprocess.check_call([CLANGXX, "-std=c++17", "-pthread", "-Wno-unused-function", "-I", MOCK, "-I", os.path.join(ROOT, "include"), "-I", CSRC] +
-                          SAN + ["-x", "c++", os.path.join(HERE, "native", "rare_paths.cpp"), os.path.join(MOCK, "mockhip.cpp"), "-o", exe])
+    subprocess.check_call([CLANGXX, "-std=c++17", "-pthread", "-Wno-unused-function", "-I", MOCK, "-I", os.path.join(ROOT, "include"), "-I", csrc_dir] +
+                          flags + ["-x", "c++", os.path.join(HERE, "native", "rare_paths.cpp"), os.path.join(MOCK, "mockhip.cpp"), "-o", exe])
     return exe
 
 
-@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times", "late_profiler"])
-def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
-    """See tests/native/rare_paths.cpp, which says at each section what it runs."""
+def _run_rare_path(exe, section, tmp_path):
     env = dict(os.environ, ASAN_OPTIONS=ASAN_OPTS, UBSAN_OPTIONS="print_stacktrace=1")
     args = [section]
     if section == "late_profiler":    # a library that exports what profiling tools export
         (tmp_path / "tool.c").write_text("void* rocprofiler_configure(void) { return 0; }\n")
         args.append(str(tmp_path / "tool.so"))
         subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", args[1], str(tmp_path / "tool.c")])
-    r = subprocess.run([rare_paths] + args, capture_output=True, text=True, timeout=300, env=env)
+    return subprocess.run([exe] + args, capture_output=True, text=True, timeout=300, env=env)
+
+
+@pytest.fixture(scope="module")
+def rare_paths(tmp_path_factory):
+    return _build_rare_paths(str(tmp_path_factory.mktemp("rare") / "rare_paths"), CSRC, SAN)
+
+
+@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times", "uploads", "counters_used_up", "records_used_up",
+                                     "late_profiler"])
+def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
+    """See tests/native/rare_paths.cpp, which says at each section what it runs."""
+    r = _run_rare_path(rare_paths, section, tmp_path)
     assert r.returncode == 0 and section + " ok" in r.stdout, r.stdout + r.stderr
+
+
+# One rule taken out at a time, as for the histories below; the section named must fail.
+RARE_MUTANTS = [
+    ("capture_not_seen", "capture", "  const bool captured = capturing(st);", "  const bool captured = false;"),
+    ("upload_buffer_taken_while_it_is_read", "uploads",
+     "        if (query_relaxed([&] { return hipEventQuery(p->na_up_ev[k]); })) up = k;", "        up = k;"),
+    ("fill_launches_of_the_first_batch", "uploads", "std::memcpy(pack.d, list.data() + at,", "std::memcpy(pack.d, list.data(),"),
+    ("clock_record_not_given_back", "records_used_up", "  if (c.stamp) p->stamp_free.push_back(c.stamp);\n", ""),
+    ("tool_that_comes_late_not_seen", "late_profiler", "    if (p->done_word[0]) look_for_profiler(p);\n", ""),
+]
+
+
+@pytest.fixture(scope="module")
+def rare_mutants(tmp_path_factory):
+    """name -> executable, or the exception its build raised; several compilers at a time."""
+    from concurrent.futures import ThreadPoolExecutor
+    top = tmp_path_factory.mktemp("rare_mutants")
+
+    def build(m):
+        try:
+            d = top / m[0]
+            d.mkdir()
+            return m[0], _build_rare_paths(str(d / "mutant"), _mutated_sources(d, m[0], m[2], m[3]), ["-O1"])
+        except Exception as e:
+            return m[0], e
+    if not os.path.exists(CLANGXX):
+        pytest.skip("no host clang++ for the kernel source")
+    with ThreadPoolExecutor(max_workers=max(1, min(6, os.cpu_count() or 1))) as pool:
+        return dict(pool.map(build, RARE_MUTANTS))
+
+
+@pytest.mark.parametrize("name,section,find,repl", RARE_MUTANTS, ids=[m[0] for m in RARE_MUTANTS])
+def test_a_missing_rule_of_a_rare_path_is_noticed(rare_mutants, name, section, find, repl, tmp_path):
+    exe = rare_mutants[name]
+    if isinstance(exe, Exception):
+        raise exe
+    r = _run_rare_path(exe, section, tmp_path)
+    assert r.returncode != 0 and "FAILED" in r.stdout, r.stdout + r.stderr
 
 
 @pytest.fixture(scope="module")
