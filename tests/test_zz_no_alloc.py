@@ -152,3 +152,24 @@ def test_noalloc_move_inside_a_graph(gpu, n):
         torch.cuda.synchronize()
         assert np.array_equal(pool.cpu().numpy(), ora_pool)
     kp.close()
+
+
+@pytest.mark.parametrize("n", [60, 300, 448, 900])
+def test_noalloc_moves_in_a_row(gpu, n):
+    """More allocation-free moves than the handle has upload buffers, with nothing waited for in between."""
+    import torch
+    g = W.Geometry(2, 2, 8, 2, "f16", 2000)
+    host_pool = W.fill_buffer_np(0x5EED0A03, g.pool_bytes, g.dtype)
+    rng = np.random.default_rng(n)
+    ora_pool = host_pool.copy()
+    ora = ko.Oracle(g.L, g.H, g.D, g.B, g.e, g.N, ora_pool, g.strides, np.zeros(g.S, np.uint8))
+    pool = torch.from_numpy(host_pool.copy()).to(gpu)
+    kp = kv.KVPool(g, pool, torch.zeros(2 * g.S, dtype=torch.uint8).pin_memory())
+    lists = [_moves(rng, g.N, n - k % 3) for k in range(24)]
+    for src, dst in lists:
+        assert kp.move_blocks_noalloc(src, dst) == kv.KV_OK
+    for src, dst in lists:
+        assert ora.move_blocks(src, dst) == ko.OK
+    assert kp.sync() == kv.KV_OK
+    assert np.array_equal(pool.cpu().numpy(), ora_pool)
+    kp.close()
