@@ -109,7 +109,7 @@ enum {
 /* kv_pool_config.flags */
 enum {
   KV_PATH_AUTO = 0u,      /* zero-copy, except: with a bounce buffer, transfers of 8 MiB and more
-                             go through it and the copy engines (robust next to running compute) */
+                             go through it and hipMemcpyAsync */
   KV_PATH_DMA = 1u,       /* gather into bounce_dev, then hipMemcpyAsync (needs bounce_dev) */
   KV_PATH_ZEROCOPY = 2u,  /* kernels store to / load from the mapped host arena directly */
   KV_STAGING_DEVICE = 4u, /* staging_host is device memory: the on-device gather/scatter */
@@ -160,10 +160,12 @@ typedef struct {
   int64_t bytes;    /* payload bytes = blocks * S */
   double plan_us;   /* host time spent validating and building descriptors */
   double enqueue_us; /* host time spent inside HIP enqueue calls */
-  float ms_total;   /* first enqueue to last completion on the stream (HIP events; a call that is a single launch and
-                       nothing else: the device's clock from the launch's first workgroup to its last) */
+  float ms_total;   /* first enqueue to last completion on the stream (HIP events; a call of up to 256 MiB that is a single
+                       launch and nothing else, apart from an upload of its list: the device's clock from the first
+                       workgroup of the two to the last, with both ends in HBM the last to leave of the 4096 that are
+                       dispatched last, without what the launch itself costs and what it waited for) */
   float ms_kernel;  /* summed duration of the data kernels (HIP events around each launch); a call that is a
-                       single launch and nothing else carries no events of its own and reports ms_total */
+                       single launch and nothing else mostly carries no events of its own and then reports ms_total */
   int32_t scatter_order; /* scatter with both ends in HBM that is large, or goes plane by plane because its pool's planes lie on
                             few memory channels: 0 block by block, 1 plane by plane; -1 otherwise */
   int32_t reserved;
@@ -337,15 +339,16 @@ typedef struct {
   int64_t inflight_bytes[2]; /* their payload */
   int64_t total_calls[2];    /* finished calls accounted so far */
   int64_t total_bytes[2];
-  double ewma_gbps[2];       /* payload rate of finished calls of 4 MiB and more (0: none yet) */
-  double ewma_small_us[2];   /* stream time of finished calls below 4 MiB: the fixed cost (0: none yet) */
+  double ewma_gbps[2];       /* payload rate of finished calls of 4 MiB and more, over kv_stats.ms_total (0: none yet) */
+  double ewma_small_us[2];   /* kv_stats.ms_total of finished calls below 4 MiB: the fixed cost, of a call that is a single
+                                launch without the 4 to 8 us that the launch and its event take on the stream (0: none yet) */
 } kv_io_stats;
 int kv_io_stats_get(kv_pool* p, kv_io_stats* out);
 
 /* Blocks that a transfer enqueued now on stream `dir` (0 evict, 1 load) can move so that it
  * finishes within interval_us: floor((interval_us - fixed - inflight_bytes/rate) * rate / S),
  * never negative, with rate = ewma_gbps (32 GB/s until measured) and fixed = ewma_small_us
- * (50 us until measured).  Feed it to kv_swap_out_delta as block_budget; a result of 0 means
+ * (50 us until measured; optimistic by the few us it leaves out).  Feed it to kv_swap_out_delta as block_budget; a result of 0 means
  * "nothing fits": do not pass it on, since a budget of 0 means unlimited there. */
 int64_t kv_budget_blocks(kv_pool* p, int32_t dir, double interval_us);
 
