@@ -341,7 +341,7 @@ typedef struct {
   int64_t total_bytes[2];
   double ewma_gbps[2];       /* payload rate of finished calls of 4 MiB and more, over kv_stats.ms_total (0: none yet) */
   double ewma_small_us[2];   /* kv_stats.ms_total of finished calls below 4 MiB: the fixed cost, of a call that is a single
-                                launch without the 4 to 8 us that the launch and its event take on the stream (0: none yet) */
+                                launch without the 4 us or so that the launch itself costs on the stream (0: none yet) */
 } kv_io_stats;
 int kv_io_stats_get(kv_pool* p, kv_io_stats* out);
 
