@@ -376,7 +376,7 @@ enum {
   KV_TUNE_SCATTER_ORDER = 8,    /* scatter of 1024 blocks and more with both ends in HBM: 0 default (the handle times
                                    both job orders on its first two such calls and keeps the faster), 1 always block
                                    by block (gathers, too: where the planes of a pool lie on few memory channels they
-                                   otherwise go plane by plane from 40 MiB on), 2 plane by plane over descriptors sorted by destination block, whatever the size */
+                                   otherwise go plane by plane from 60 MiB on), 2 plane by plane over descriptors sorted by destination block, whatever the size */
   KV_TUNE_PHASE_BYTES = 9,      /* kv_evict_and_load: bytes of one phase per direction (default: host arena an eighth
                                    of the larger transfer, between 16 and 64 MiB; KV_STAGING_DEVICE 256 MiB) */
   KV_TUNE_PHASE_WGS_OUT = 10,   /* kv_evict_and_load: workgroups of an eviction phase (default 36) */

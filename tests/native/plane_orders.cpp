@@ -134,13 +134,57 @@ void compare(std::mt19937_64& rng, int L, int H, int D, int B, bool scales, int 
   for (int s = 0; s < 2; s++) (void)hipStreamDestroy(st[s]);
 }
 
-bool rule(int L, int64_t chunk, int64_t N) {
-  kv_pool p;
-  p.cfg.num_layers = L;
-  p.chunk = chunk;
-  p.cfg.kv_stride = N * chunk;
-  p.cfg.layer_stride = 2 * N * chunk;
-  return planes_on_few_channels(&p);
+// What a handle over such a pool takes its planes for.  layout: 0 layer-major, 1 block-major, 2 layer-major with a block's K and V
+// side by side.
+bool rule(int L, int64_t chunk, int64_t N, int layout = 0, kv_pool* p = nullptr) {
+  kv_pool own;
+  if (!p) p = &own;
+  p->cfg.num_layers = L;
+  p->cfg.num_kv_heads = 1;
+  p->cfg.num_blocks = N;
+  p->chunk = chunk;
+  p->S = p->block_bytes = 2 * L * chunk;
+  p->cfg.kv_stride = layout ? chunk : N * chunk;
+  p->cfg.layer_stride = layout == 1 ? 2 * chunk : 2 * N * chunk;
+  p->cfg.block_stride = layout == 0 ? chunk : layout == 1 ? 2 * L * chunk : 2 * chunk;
+  p->dev_staging = true;
+  hbm_setup(p);
+  return p->planes_collide;
+}
+
+void rules() {
+  for (int64_t N : {508, 516, 1016, 1032, 2032, 2064})
+    if (!rule(32, 32768, N) || !rule(80, 32768, N)) die("planes that collide", N, 0);
+  for (int64_t N : {448, 500, 504, 507, 509, 512, 524, 576, 960, 1000, 1020, 1024, 1088, 2040, 2048, 4096, 38146, 40000})
+    if (rule(32, 32768, N)) die("planes that do not collide", N, 0);
+  for (int64_t N : {127, 129, 254, 258, 508, 516})
+    if (!rule(32, 131072, N)) die("planes of 128 KiB chunks that collide", N, 0);
+  for (int64_t N : {4064, 4128})
+    if (!rule(32, 4096, N)) die("planes of 4 KiB chunks that collide", N, 0);
+  if (!rule(64, 32768, 127, 2)) die("planes that collide, K and V of a block side by side", 127, 0);
+  // block-major: a block is one run, whatever its chunks
+  for (int64_t chunk : {1024, 2048, 4096, 32768})
+    for (int L : {2, 16, 32, 80})
+      for (int64_t N : {508, 700, 1584, 14400})
+        if (rule(L, chunk, N, 1)) die("a block-major pool", chunk, L);
+  // planes on few channels, but of blocks so small that enough others are in flight beside them
+  const int64_t small[][3] = {{4, 1024, 13208}, {16, 1024, 27348}, {2, 4096, 7224}, {16, 3072, 2794}, {64, 3072, 7138}, {8, 65536, 2580}, {24, 32768, 1270}, {80, 8192, 344}};
+  for (auto& s : small)
+    if (rule((int)s[0], s[1], s[2])) die("small blocks", s[1], s[2]);
+  // which transfers of a pool whose planes collide: long ones, and scatters only of long chunks into a quarter of the pool
+  const struct {
+    int L, layout;
+    int64_t chunk, N;
+    size_t n;
+    bool out, in;
+  } sizes[] = {{32, 0, 32768, 508, 29, false, false}, {32, 0, 32768, 508, 30, true, false}, {32, 0, 32768, 508, 126, true, false},
+               {32, 0, 32768, 508, 127, true, true}, {32, 0, 32768, 1032, 500, true, true}, {64, 0, 8192, 508, 200, true, false},
+               {48, 0, 16384, 127, 60, true, true}, {32, 2, 32768, 1032, 256, true, false}, {32, 2, 32768, 1032, 300, false, false}};
+  for (auto& s : sizes) {
+    kv_pool p;
+    (void)rule(s.L, s.chunk, s.N, s.layout, &p);
+    if (collides(&p, true, s.n) != s.out || collides(&p, false, s.n) != s.in) die("which transfers go plane by plane", s.chunk, (long)s.n);
+  }
 }
 
 }  // namespace
@@ -173,6 +217,7 @@ void handle_under_a_profiler() {
 
 int main() {
   handle_under_a_profiler();
+  rules();
   std::mt19937_64 rng(17);
   for (int layout = 0; layout < 4; layout++)
     for (int scales = 0; scales < 2; scales++)
@@ -183,14 +228,6 @@ int main() {
         const int odd[] = {4, 36, 40, 64, 288, 520, 1152, 1800};
         compare(rng, L + 1, 4, odd[rng() % (n > 100 ? 4 : 8)], 1, scales, layout, n);
       }
-  for (int64_t N : {508, 516, 1016, 1032, 2032, 2064})
-    if (!rule(32, 32768, N) || !rule(80, 32768, N)) die("planes that collide", N, 0);
-  for (int64_t N : {448, 500, 504, 507, 509, 512, 524, 576, 960, 1000, 1020, 1024, 1088, 2040, 2048, 4096, 38146, 40000})
-    if (rule(32, 32768, N)) die("planes that do not collide", N, 0);
-  for (int64_t N : {127, 129, 254, 258, 508, 516})
-    if (!rule(32, 131072, N)) die("planes of 128 KiB chunks that collide", N, 0);
-  for (int64_t N : {4064, 4128})
-    if (!rule(32, 4096, N)) die("planes of 4 KiB chunks that collide", N, 0);
   std::printf("orders agree with the lists: %ld\n", compared);
   return 0;
 }

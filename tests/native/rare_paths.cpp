@@ -112,10 +112,10 @@ void capture() {
     }
 }
 
-// kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (41 MiB: such a scatter goes
-// plane by plane from 40 MiB on).
+// kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
+// plane by plane from 60 MiB on).
 void scatter_order() {
-  const int n = 656, N = 700;
+  const int n = 976, N = 1000;
   Pool p(N, n, KV_STAGING_DEVICE, 16384);
   const uint64_t id = 3;
   const int32_t off[2] = {0, n}, tok = n;

@@ -189,16 +189,17 @@ def test_streams_hand_over_short_transfers(gpu, name, n, arena):
     gpu_lib.close()
 
 
-def test_pool_whose_planes_collide(gpu):
-    """A pool of 24 planes 4 MiB + 32 KiB apart: 110 of its 258 blocks go plane by plane out and in again."""
-    g = W.Geometry(12, 8, 128, 8, "bf16", 258)
-    n = 110
+@pytest.mark.parametrize("layers,n,order", [(12, 110, -1), (40, 70, 1)])
+def test_pool_whose_planes_collide(gpu, layers, n, order):
+    """Pools of 24 and 80 planes 4 MiB + 32 KiB apart: 70 of 258 blocks of 1.25 MiB go plane by plane out and in again, 110 of
+    384 KiB, which are many in flight beside each other, do not."""
+    g = W.Geometry(layers, 8, 128, 8, "bf16", 258)
     perm = np.random.default_rng(21).permutation(g.N).astype(np.int32)
     a, b = (HostPool(g, 0xB12, "layer", slots=n) for _ in range(2))
     ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE)
     for lib in (ora, gpu_lib):
         assert lib.swap_out([1, 2], [0, 40, n], perm[:n], [40 * g.B, (n - 40) * g.B]) == ko.OK
         assert lib.swap_in([2, 1], [0, n - 40, n], perm[n:2 * n]) == ko.OK
-    assert gpu_lib.kp.stats()["scatter_order"] == 1
+    assert gpu_lib.kp.stats()["scatter_order"] == order
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     gpu_lib.close()
