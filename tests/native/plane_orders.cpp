@@ -134,7 +134,7 @@ void compare(std::mt19937_64& rng, int L, int H, int D, int B, bool scales, int 
   for (int s = 0; s < 2; s++) (void)hipStreamDestroy(st[s]);
 }
 
-// What a handle over such a pool takes its planes for.  layout: 0 layer-major, 1 block-major, 2 layer-major with a block's K and V
+// What a handle over such a pool does with its planes.  layout: 0 layer-major, 1 block-major, 2 layer-major with a block's K and V
 // side by side.
 bool rule(int L, int64_t chunk, int64_t N, int layout = 0, kv_pool* p = nullptr) {
   kv_pool own;
@@ -183,7 +183,22 @@ void rules() {
   for (auto& s : sizes) {
     kv_pool p;
     (void)rule(s.L, s.chunk, s.N, s.layout, &p);
+    if (plane_by_plane_move(&p, (size_t)s.N / 2) != (s.layout == 0)) die("moves of long chunks", s.chunk, s.N);
     if (collides(&p, true, s.n) != s.out || collides(&p, false, s.n) != s.in) die("which transfers go plane by plane", s.chunk, (long)s.n);
+  }
+  // moves whose lists are worth ordering
+  const struct {
+    int L;
+    int64_t chunk;
+    size_t n;
+    bool pm;
+  } moves[] = {{1, 144, 27601, false}, {1, 448, 28933, false},  {2, 768, 28606, false},  {24, 64, 38056, false}, {8, 144, 11274, false},  {24, 128, 9819, false},
+               {2, 1920, 42627, false}, {16, 384, 996, false},   {4, 1344, 50386, true},  {24, 160, 40116, true}, {48, 80, 4608, true},    {80, 16, 2866, true},
+               {32, 256, 5170, true},   {24, 224, 6552, true},   {80, 960, 6983, true},   {8, 2560, 2584, true},  {1, 1024, 300, true},    {32, 32768, 64, true}};
+  for (auto& m : moves) {
+    kv_pool p;
+    (void)rule(m.L, m.chunk, 3 * (int64_t)m.n, 0, &p);
+    if (plane_by_plane_move(&p, m.n) != m.pm) die("which moves go plane by plane", m.chunk, m.L);
   }
 }
 

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 GEOMS = {
     "1KiB": W.Geometry(3, 1, 64, 8, "bf16", 96),                       # one full wavefront per chunk
-    "1KiB_many": W.Geometry(1, 1, 64, 8, "bf16", 1800),                 # lists of 600 of 1800: sorted by digits, plane by plane
+    "1KiB_many": W.Geometry(1, 1, 64, 8, "bf16", 1800),                 # lists of 600 of 1800: sorted by digits for a scatter plane by plane
     "9KiB": W.Geometry(2, 4, 72, 16, "f16", 80),
     "1152B": W.Geometry(3, 1, 72, 8, "bf16", 96),                      # whole lines, no whole KiB; 432 vectors: lane per vector
     "2560B": W.Geometry(2, 2, 80, 8, "bf16", 96),                      # 640 vectors per block: the last job is full
@@ -51,6 +51,24 @@ def test_gather_scatter_move(gpu, name, layout):
         if g.scales:
             assert np.array_equal(a.scale, b.scale), (name, n, "scales")
         gpu_lib.close()
+
+
+@pytest.mark.parametrize("geom", [(8, 1, 64, 8, "bf16"), (12, 1, 72, 8, "bf16"), (128, 2, 8, 3, "fp8_e4m3")], ids=["1KiB", "1152B", "fp8_48B"])
+def test_moves_that_go_plane_by_plane(gpu, geom):
+    """Moves over lists that are worth ordering, by digits: chunks of whole KiB, whole lines, ragged ones with scales."""
+    g = W.Geometry(*geom, 4500, scales=geom[4] == "fp8_e4m3")
+    n = 1400
+    assert 3 * n <= g.N < 6 * n
+    perm = np.random.default_rng(22).permutation(g.N).astype(np.int32)
+    a, b = (HostPool(g, 0xB13, "layer", slots=1) for _ in range(2))
+    ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE)
+    assert ora.move_blocks(perm[:n], perm[n:2 * n]) == ko.OK and gpu_lib.move_blocks(perm[:n], perm[n:2 * n]) == kv.KV_OK
+    assert ora.move_blocks(perm[n:2 * n], perm[2 * n:3 * n]) == ko.OK
+    gpu_lib._push()
+    assert gpu_lib.kp.move_blocks_noalloc(perm[n:2 * n], perm[2 * n:3 * n]) == kv.KV_OK
+    gpu_lib._pull()
+    assert np.array_equal(a.pool, b.pool) and (not g.scales or np.array_equal(a.scale, b.scale))
+    gpu_lib.close()
 
 
 @pytest.mark.parametrize("name", ["9KiB", "1040B", "fp8_1KiB", "fp8_48B"])
