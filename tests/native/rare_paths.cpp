@@ -269,6 +269,61 @@ void records_used_up() {
   if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
 }
 
+// Calls that store a number record no end event: not behind others, and not for a program that polls; one that waits for single
+// requests gets events from then on.  What a wait, a poll and a hazard with the other stream need is there all the same.
+void no_end_events() {
+  std::mt19937_64 rng(3);
+  for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
+    Pool p(40, 16, flags);
+    std::vector<char> want = p.bytes();
+    auto moved = [&](const std::vector<int32_t>& src, const std::vector<int32_t>& dst) {
+      Moves m(rng, p.N, 1);
+      m.src = src, m.dst = dst;
+      m.apply(p, &want);
+    };
+    const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12};
+    const int32_t off[2] = {0, 3}, tok = 3;
+    const uint64_t id = 3, id2 = 4;
+    auto last = [&]() -> Call& { return p.h->calls.back(); };
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    OK(kv_move_blocks(p.h, 3, a.data(), b.data(), nullptr));
+    moved(a, b);
+    if (last().end || !last().done) die("a short move has an end event", flags);
+    OK(kv_swap_out(p.h, 1, &id, off, b.data(), &tok, nullptr));  // behind the move: the handle is busy
+    if (last().end) die("a swap-out behind a call has an end event", flags);
+    OK(kv_swap_in(p.h, 1, &id, off, a.data(), KV_KEEP_STAGING, nullptr));  // a's blocks: behind the move, which reads them
+    moved(b, a);
+    if (last().end) die("a swap-in has an end event", flags);
+    if (kv_req_poll(p.h, id) != 0) die("a request is complete before anything has run", flags);
+    OK(kv_move_blocks_noalloc(p.h, 3, a.data(), c.data(), nullptr));
+    moved(a, c);
+    if (p.h->na_recorded) die("an allocation-free move has recorded its event", flags);
+    OK(kv_swap_out(p.h, 1, &id2, off, c.data(), &tok, nullptr));
+    if (!p.h->na_recorded) die("the call behind an allocation-free move has not recorded its event", flags);
+    OK(kv_swap_in(p.h, 1, &id2, off, d.data(), 0, nullptr));
+    moved(c, d);
+    kv_stats st{};
+    st.struct_size = sizeof(st);
+    OK(kv_last_stats(p.h, &st));
+    if (!(st.ms_total > 0) || st.op != 3) die("statistics of a call without an event", flags);
+    if (p.bytes() != want) die("bytes of calls without events", flags);
+    OK(kv_sync(p.h));
+    OK(kv_swap_out(p.h, 1, &id2, off, d.data(), &tok, nullptr));
+    if (!last().end) die("a swap-out on an idle handle has no end event", flags);
+    OK(kv_swap_in(p.h, 1, &id2, off, b.data(), 0, nullptr));
+    moved(d, b);
+    if (last().end) die("a swap-in behind it has one", flags);
+    OK(kv_req_wait(p.h, id2));
+    if (kv_req_poll(p.h, id2) != 1 || p.bytes() != want) die("a request that was waited for", flags);
+    OK(kv_move_blocks(p.h, 3, b.data(), c.data(), nullptr));
+    moved(b, c);
+    if (!last().end) die("no end event for a program that waits for requests", flags);
+    OK(kv_sync(p.h));
+    if (p.bytes() != want) die("bytes", flags);
+    mockhip::set_policy(mockhip::kRandom, nullptr);
+  }
+}
+
 // Streams hand over by event, and not by number, where the number's wait might not end: as soon as a profiling tool has been loaded
 // (argument of the section: a library that is one), and where threads of the runtime submit the streams' work.
 void late_profiler(const char* tool) {
@@ -307,7 +362,8 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
-                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up}};
+                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up},
+                {"no_end_events", no_end_events}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       mockhip::reset(5);

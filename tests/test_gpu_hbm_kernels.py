@@ -221,3 +221,34 @@ def test_pool_whose_planes_collide(gpu, layers, n, order):
     assert gpu_lib.kp.stats()["scatter_order"] == order
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     gpu_lib.close()
+
+
+@pytest.mark.parametrize("arena", ["device", "host"])
+@pytest.mark.parametrize("geom,n", [((4, 4, 64, 16, "f16"), 40), ((4, 4, 64, 16, "f16"), 300), ((5, 1, 65, 8, "bf16"), 150), ((5, 1, 16, 4, "bf16"), 150),
+                                    ((2, 2, 8, 3, "fp8_e4m3"), 150)], ids=["8KiB", "8KiB_beyond_16MiB", "1040B", "128B", "fp8_48B"])
+def test_calls_in_a_row_without_end_events(gpu, geom, n, arena):
+    """Moves, allocation-free moves and transfers that depend on each other across the two streams, nothing waited for in
+    between: short launches say by a number that they have finished."""
+    g = W.Geometry(*geom, 3 * n + 5, scales=geom[4] == "fp8_e4m3")
+    perm = np.random.default_rng(n).permutation(g.N).astype(np.int32)
+    x, y, z, m = perm[:n], perm[n:2 * n], perm[2 * n:3 * n], n // 2
+    a, b = (HostPool(g, 0xB20 + n, "layer", slots=n) for _ in range(2))
+    ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE if arena == "device" else kv.KV_PATH_ZEROCOPY)
+    gpu_lib._push()
+    kp = gpu_lib.kp
+    for turn in range(6):
+        for lib, free in ((ora, ora.move_blocks), (kp, kp.move_blocks_noalloc)):
+            assert lib.move_blocks(x, y) == ko.OK
+            assert free(y, z) == ko.OK
+            assert lib.swap_out([turn], [0, m], z[:m], [m * g.B]) == ko.OK
+            assert lib.move_blocks(x[m:], z[:n - m]) == ko.OK                    # over what the swap-out reads
+            assert lib.swap_in([turn], [0, m], x[n - m:]) == ko.OK               # over what the move reads
+            assert free(x[n - m:], y[:m]) == ko.OK
+            assert lib.swap_out([100], [0, m], y[:m], [m * g.B]) == ko.OK
+            assert lib.swap_in([100], [0, m], x[:m]) == ko.OK
+        if turn == 3:
+            assert kp.req_wait(100) == kv.KV_OK and kp.req_poll(100) == 1
+    gpu_lib._pull()
+    assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
+    assert not g.scales or np.array_equal(a.scale, b.scale)
+    gpu_lib.close()
