@@ -322,20 +322,6 @@ void no_end_events() {
     if (p.bytes() != want) die("bytes", flags);
     mockhip::set_policy(mockhip::kRandom, nullptr);
   }
-  // beyond the numbers: an end event with each call, of the launch's own behind a call in flight
-  Pool p(700, 1, KV_STAGING_DEVICE, 16384);
-  std::vector<char> want = p.bytes();
-  mockhip::set_policy(mockhip::kLazy, nullptr);
-  for (size_t n : {300, 256, 257}) {
-    const Moves m(rng, p.N, n);
-    OK(kv_move_blocks(p.h, (int64_t)n, m.src.data(), m.dst.data(), nullptr));
-    m.apply(p, &want);
-    const Call& c = p.h->calls.back();
-    if (!c.end != (n == 256) || !c.done != (n != 256) || c.behind != (n != 300)) die("end of a long move", (long)n);
-  }
-  OK(kv_sync(p.h));
-  if (p.bytes() != want) die("bytes of long moves");
-  mockhip::set_policy(mockhip::kRandom, nullptr);
 }
 
 // Streams hand over by event, and not by number, where the number's wait might not end: as soon as a profiling tool has been loaded

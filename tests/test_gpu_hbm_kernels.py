@@ -228,7 +228,7 @@ def test_pool_whose_planes_collide(gpu, layers, n, order):
                                     ((2, 2, 8, 3, "fp8_e4m3"), 150)], ids=["8KiB", "8KiB_beyond_16MiB", "1040B", "128B", "fp8_48B"])
 def test_calls_in_a_row_without_end_events(gpu, geom, n, arena):
     """Moves, allocation-free moves and transfers that depend on each other across the two streams, nothing waited for in
-    between: short launches say by a number that they have finished, longer moves signal their event themselves."""
+    between: short launches say by a number that they have finished."""
     g = W.Geometry(*geom, 3 * n + 5, scales=geom[4] == "fp8_e4m3")
     perm = np.random.default_rng(n).permutation(g.N).astype(np.int32)
     x, y, z, m = perm[:n], perm[n:2 * n], perm[2 * n:3 * n], n // 2
