@@ -252,3 +252,38 @@ def test_calls_in_a_row_without_end_events(gpu, geom, n, arena):
     assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool)
     assert not g.scales or np.array_equal(a.scale, b.scale)
     gpu_lib.close()
+
+
+@pytest.mark.parametrize("geom,n", [((24, 4, 72, 16, "f16"), 701), ((20, 1, 72, 8, "bf16"), 6001), ((32, 4, 128, 8, "fp8_e4m3"), 1101)],
+                         ids=["9KiB", "1152B", "fp8_4KiB"])
+def test_lists_beyond_the_memory_side_cache(gpu, geom, n):
+    """More than 256 MiB: the gather keeps the end of its list in the cache, the scatter begins there.  Against torch's own indexing."""
+    import torch
+    g = W.Geometry(*geom, 2 * n + 1, scales=geom[4] == "fp8_e4m3")
+    assert n * g.S > 256 << 20
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    pool = torch.randint(-2**62, 2**62, (g.pool_bytes // 8,), dtype=torch.int64, device="cuda", generator=gen).view(torch.uint8)
+    scale = torch.randint(-2**62, 2**62, (g.scale_bytes // 8,), dtype=torch.int64, device="cuda", generator=gen).view(torch.uint8) if g.scales else None
+    arena = torch.zeros(n * g.S, dtype=torch.uint8, device="cuda")
+    perm = np.random.default_rng(n).permutation(g.N).astype(np.int32)
+    src, dst = (torch.as_tensor(perm[k * n:(k + 1) * n].astype(np.int64), device="cuda") for k in (0, 1))
+    planes = [t.view(2 * g.L, g.N, -1) for t in (pool, scale) if t is not None]
+    before = [p.clone() for p in planes]
+    torch.cuda.synchronize()
+    kp = kv.KVPool(g, pool, arena, scale=scale, flags=kv.KV_STAGING_DEVICE)
+    for turn in range(2):  # (the second scatter, where lists of 1024 blocks are timed both ways, goes plane by plane)
+        assert kp.swap_out([7], [0, n], perm[:n], [n * g.B]) == kv.KV_OK
+        assert kp.swap_in([7], [0, n], perm[n:2 * n]) == kv.KV_OK
+        assert kp.sync() == kv.KV_OK
+        at = 0
+        for p, b in zip(planes, before):
+            part = arena.view(n, g.S)[:, at:at + 2 * g.L * p.shape[2]].reshape(n, 2 * g.L, -1)
+            at += 2 * g.L * p.shape[2]
+            assert torch.equal(part, b[:, src].transpose(0, 1)), "gather"
+            b[:, dst] = b[:, src]
+            assert torch.equal(p, b), "scatter"
+        pool.view(torch.int64).bitwise_xor_(0x5A5A)
+        planes[0].copy_(pool.view(2 * g.L, g.N, -1))
+        before[0].copy_(planes[0])
+        torch.cuda.synchronize()
+    kp.close()
