@@ -287,3 +287,25 @@ def test_lists_beyond_the_memory_side_cache(gpu, geom, n):
         before[0].copy_(planes[0])
         torch.cuda.synchronize()
     kp.close()
+
+
+@pytest.mark.parametrize("geom,n", [((1, 4, 72, 16, "f16"), 227), ((1, 4, 72, 16, "f16"), 229), ((3, 1, 72, 8, "bf16"), 607), ((3, 1, 72, 8, "bf16"), 610),
+                                    ((1, 1, 64, 8, "bf16"), 2049), ((2, 2, 64, 8, "fp8_e4m3"), 1), ((2, 2, 64, 8, "fp8_e4m3"), 35),
+                                    ((6, 10, 16, 4, "fp8_e4m3"), 37)],
+                         ids=["9KiB_below_4MiB", "9KiB", "1152B_odd", "1152B", "1KiB", "fp8_1KiB_one", "fp8_1KiB", "fp8_640B"])
+def test_workgroups_of_four_wavefronts(gpu, geom, n):
+    """Counted launches from 4 MiB on, and all with scales, whose last workgroup has jobs for each number of its wavefronts and one or
+    two for each of them: gather, scatter and move, block by block and plane by plane."""
+    g = W.Geometry(*geom, 3 * n + 2, scales=geom[4] == "fp8_e4m3")
+    perm = np.random.default_rng(n).permutation(g.N).astype(np.int32)
+    for order in (0, 2):
+        tune = ((kv.KV_TUNE_SCATTER_ORDER, order),) if order else ()
+        a, b = (HostPool(g, 0xB30 + n, "layer", slots=n) for _ in range(2))
+        ora, gpu_lib = a.oracle(), GpuAdapter(b, kv.KV_STAGING_DEVICE, tune=tune)
+        for lib in (ora, gpu_lib):
+            assert lib.swap_out([1], [0, n], perm[:n], [n * g.B]) == ko.OK
+            assert lib.swap_in([1], [0, n], perm[n:2 * n]) == ko.OK
+            assert lib.move_blocks(perm[n:2 * n], perm[2 * n:3 * n]) == ko.OK
+        assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), order
+        assert not g.scales or np.array_equal(a.scale, b.scale), order
+        gpu_lib.close()
