@@ -309,3 +309,12 @@ def test_workgroups_of_four_wavefronts(gpu, geom, n):
         assert np.array_equal(a.staging, b.staging) and np.array_equal(a.pool, b.pool), order
         assert not g.scales or np.array_equal(a.scale, b.scale), order
         gpu_lib.close()
+
+
+@pytest.mark.parametrize("geom,n", [((24, 4, 72, 16, "f16"), 191), ((20, 1, 72, 8, "bf16"), 1901), ((20, 3, 112, 1, "bf16"), 3201)], ids=["9KiB", "1152B", "672B"])
+def test_longer_calls_in_a_row(gpu, geom, n):
+    """The same with moves of 80 MiB and transfers of 40: beyond the sizes at which moves take two jobs a wavefront, and at which only
+    calls of one launch store a number."""
+    g = W.Geometry(*geom, 1)
+    assert n * g.S > 64 << 20 and 32 << 20 < n // 2 * g.S < 48 << 20
+    test_calls_in_a_row_without_end_events(gpu, geom, n, "device")
