@@ -448,6 +448,32 @@ def test_arrays_the_binding_takes():
     kp.close()
 
 
+@pytest.mark.parametrize("form", ["read_only", "sliced", "strided", "empty"])
+def test_pointers_of_arrays(form):
+    """Arrays that cannot be written to, parts of larger ones, such that are copied first, and empty ones reach the library as they are."""
+    g = W.Geometry(2, 1, 8, 4, "f16", 32)
+    kp = kv.KVPool(g, flags=kv.KV_PLAN_ONLY, staging_bytes=16 * g.S)
+    n = 0 if form == "empty" else 2
+    want = dict(r=np.array([5, 9][:n], np.uint64), o=np.array([0, 3, 5][:n + 1], np.int32), b=np.array([7, 3, 11, 30, 1][:5 if n else 0], np.int32),
+                t=np.array([12, 8][:n], np.int32), new=np.array([2, 4, 6, 8, 10][:5 if n else 0], np.int32))
+    a = {}
+    for k, v in want.items():
+        if form == "sliced":
+            x = np.concatenate([v[:1], v, v[:1]])[1:1 + len(v)]
+        elif form == "strided":
+            x = np.repeat(v, 2)[::2]
+        else:
+            x = v.copy()
+        x.flags.writeable = form != "read_only"
+        a[k] = x
+    assert kp.swap_out(a["r"], a["o"], a["b"], a["t"]) == kv.KV_OK
+    phys, slot = kp.last_plan()
+    assert phys.tolist() == want["b"].tolist() and slot.tolist() == list(range(len(want["b"])))
+    assert kp.swap_in(a["r"], a["o"], a["new"]) == kv.KV_OK
+    assert kp.last_plan()[0].tolist() == want["new"].tolist()
+    kp.close()
+
+
 def test_binding_fails_loudly_without_the_library(tmp_path):
     """No fallback path: a copy of the package without libkvswap.so must refuse to import."""
     import shutil
