@@ -112,6 +112,103 @@ void capture() {
     }
 }
 
+// A capture that streams of a handle are drawn into through `fork`, in the relaxed mode where asked.
+struct Captured {
+  hipStream_t origin;
+  hipEvent_t fork, join;
+  hipStreamCaptureMode mode;
+  explicit Captured(bool relaxed) : mode(relaxed ? hipStreamCaptureModeRelaxed : hipStreamCaptureModeGlobal) {
+    (void)hipStreamCreateWithFlags(&origin, hipStreamNonBlocking);
+    (void)hipEventCreate(&fork);
+    (void)hipEventCreate(&join);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    mockhip::begin_capture(origin);
+    (void)hipEventRecord(fork, origin);
+  }
+  mockhip::Graph end(std::initializer_list<hipStream_t> joined) {
+    for (hipStream_t s : joined) {
+      (void)hipEventRecord(join, s);
+      (void)hipStreamWaitEvent(origin, join, 0);
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return mockhip::end_capture();
+  }
+  void replay(const mockhip::Graph& g) {
+    mockhip::replay(origin, g);
+    (void)hipStreamSynchronize(origin);
+  }
+  ~Captured() {
+    (void)hipStreamDestroy(origin);
+    (void)hipEventDestroy(fork);
+    (void)hipEventDestroy(join);
+  }
+};
+
+// Calls that keep a record go into a graph as well, and the handle goes on behind them: what is captured runs with each replay and not
+// before, and eager calls on both streams, polls, waits and telemetry work as ever.  (A swap-in that is captured asks for the swap-out in front
+// of it, which only the relaxed mode allows.)
+void captured_calls() {
+  const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12}, e{13, 14, 15};
+  const int32_t off[2] = {0, 3}, tok = 3;
+  const uint64_t id1 = 1, id2 = 2, id4 = 4, id7 = 7;
+  for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY})
+    for (int kind = 0; kind < 4; kind++) {  // a move a to d, a swap-out of a, a swap-in to d of what has been swapped out of c, both
+      Pool p(40, 16, flags);
+      std::mt19937_64 rng(4);
+      std::vector<char> want = p.bytes();
+      Moves m(rng, p.N, 1);
+      auto moved = [&](const std::vector<int32_t>& src, const std::vector<int32_t>& dst) {
+        m.src = src, m.dst = dst;
+        m.apply(p, &want);
+      };
+      if (kind >= 2) {
+        OK(kv_swap_out(p.h, 1, &id7, off, c.data(), &tok, nullptr));
+        OK(kv_swap_out(p.h, 1, &id4, off, b.data(), &tok, nullptr));
+        OK(kv_sync(p.h));
+      }
+      Captured cap(kind >= 2);
+      if (kind == 0)
+        OK(kv_move_blocks(p.h, 3, a.data(), d.data(), cap.fork));
+      else if (kind == 1)
+        OK(kv_swap_out(p.h, 1, &id1, off, a.data(), &tok, cap.fork));
+      else if (kind == 2)
+        OK(kv_swap_in(p.h, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
+      else
+        OK(kv_evict_and_load(p.h, 1, &id1, off, a.data(), &tok, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
+      const mockhip::Graph g = kind == 0 || kind == 1 ? cap.end({p.st[0]}) : kind == 2 ? cap.end({p.st[1]}) : cap.end({p.st[0], p.st[1]});
+      if (mockhip::capture_errors()) die("calls that a capture does not allow, kind", mockhip::capture_errors(), kind);
+      if (p.bytes() != want) die("a captured call has run, kind", kind, flags);
+      for (int turn = 0; turn < 3; turn++) {
+        for (int32_t blk : a)
+          for (int64_t k = 0; k < Pool::planes; k++) {
+            std::memset(p.pool + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
+            std::memset(want.data() + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
+          }
+        cap.replay(g);
+        if (kind == 0) moved(a, d);
+        if (kind >= 2) moved(c, d);
+        if (p.bytes() != want) die("bytes of a replay, kind", kind, turn);
+        if (kind == 1 || kind == 3) {
+          OK(kv_swap_in(p.h, 1, &id1, off, e.data(), KV_KEEP_STAGING, nullptr));
+          moved(a, e);
+        }
+        OK(kv_move_blocks(p.h, 3, d.data(), b.data(), nullptr));
+        moved(d, b);
+        OK(kv_swap_out(p.h, 1, &id2, off, b.data(), &tok, nullptr));
+        OK(kv_req_wait(p.h, id2));
+        if (kv_req_poll(p.h, id2) != 1) die("a request that was waited for, kind", kind, turn);
+        OK(kv_swap_in(p.h, 1, &id2, off, d.data(), 0, nullptr));
+        moved(b, d);
+        kv_stats st{};
+        st.struct_size = sizeof(st);
+        OK(kv_last_stats(p.h, &st));
+        if (st.op != 3 || !(st.ms_total > 0)) die("statistics behind a captured call, kind", kind, turn);
+        OK(kv_sync(p.h));
+        if (p.bytes() != want) die("bytes behind a captured call, kind", kind, turn);
+      }
+    }
+}
+
 // kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
 // plane by plane from 60 MiB on).
 void scatter_order() {
@@ -361,7 +458,7 @@ int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } sections[] = {{"capture", capture}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
+  } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
                 {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up},
                 {"no_end_events", no_end_events}};
   for (const auto& s : sections)

@@ -153,7 +153,7 @@ def rare_paths(tmp_path_factory):
     return _build_rare_paths(str(tmp_path_factory.mktemp("rare") / "rare_paths"), CSRC, SAN)
 
 
-@pytest.mark.parametrize("section", ["capture", "scatter_order", "exchange_times", "uploads", "counters_used_up", "records_used_up",
+@pytest.mark.parametrize("section", ["capture", "captured_calls", "scatter_order", "exchange_times", "uploads", "counters_used_up", "records_used_up",
                                      "late_profiler", "no_end_events"])
 def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""

@@ -154,6 +154,63 @@ def test_noalloc_move_inside_a_graph(gpu, n):
     kp.close()
 
 
+@pytest.mark.parametrize("arena", ["device", "host"])
+@pytest.mark.parametrize("kind,mode", [("move", "global"), ("out", "global"), ("in", "relaxed"), ("both", "relaxed")],
+                         ids=["move", "out", "in", "both"])
+def test_recorded_calls_inside_a_graph(gpu, kind, mode, arena):
+    """Calls that keep a record are captured, too, their streams joining through the caller's event: each replay moves what was captured, and
+    the handle goes on with eager calls, waits and polls."""
+    import torch
+    g = W.Geometry(2, 2, 8, 2, "f16", 200)
+    a, b, c, d, e = (np.arange(k, k + 4, dtype=np.int32) for k in (0, 10, 20, 30, 40))
+    off, tok = [0, 4], [4 * g.B]
+    pool = torch.from_numpy(W.fill_buffer_np(0x5EED0A04, g.pool_bytes, g.dtype)).to(gpu)
+    slots = torch.zeros(32 * g.S, dtype=torch.uint8, device=gpu) if arena == "device" else torch.zeros(32 * g.S, dtype=torch.uint8).pin_memory()
+    evict, load = torch.cuda.Stream(), torch.cuda.Stream()
+    kp = kv.KVPool(g, pool, slots, evict_stream=evict, load_stream=load, flags=kv.KV_STAGING_DEVICE if arena == "device" else kv.KV_PATH_ZEROCOPY)
+    blocks = pool.view(2 * g.L, g.N, -1)
+    want = blocks.clone()
+    torch.cuda.synchronize()
+    if kind in ("in", "both"):
+        assert kp.swap_out([7], off, c, tok) == kv.KV_OK and kp.swap_out([4], off, b, tok) == kv.KV_OK and kp.sync() == kv.KV_OK
+    graph, fork, j1, j2 = torch.cuda.CUDAGraph(), *(torch.cuda.Event() for _ in range(3))
+    with torch.cuda.graph(graph, capture_error_mode=mode):
+        here = torch.cuda.current_stream()
+        fork.record(here)
+        at = fork.cuda_event
+        assert {"move": lambda: kp.move_blocks(a, d, wait_event=at),
+                "out": lambda: kp.swap_out([1], off, a, tok, wait_event=at),
+                "in": lambda: kp.swap_in([7], off, d, flags=kv.KV_KEEP_STAGING, wait_event=at),
+                "both": lambda: kp.evict_and_load([1], off, a, tok, [7], off, d, in_flags=kv.KV_KEEP_STAGING, wait_event=at)}[kind]() == kv.KV_OK
+        for stream, joined, kinds in ((evict, j1, ("move", "out", "both")), (load, j2, ("in", "both"))):
+            if kind in kinds:
+                joined.record(stream)
+                here.wait_event(joined)
+    torch.cuda.synchronize()
+    assert torch.equal(blocks, want), "a captured call has run"
+    for turn in range(4):
+        blocks[:, :4] = turn + 1
+        want[:, :4] = turn + 1
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        if kind == "move":
+            want[:, 30:34] = want[:, :4]
+        if kind in ("in", "both"):
+            want[:, 30:34] = want[:, 20:24]
+        assert torch.equal(blocks, want), "replay"
+        if kind in ("out", "both"):
+            assert kp.swap_in([1], off, e, flags=kv.KV_KEEP_STAGING) == kv.KV_OK
+            want[:, 40:44] = want[:, :4]
+        assert kp.move_blocks(d, b) == kv.KV_OK and kp.swap_out([2], off, b, tok) == kv.KV_OK
+        assert kp.req_wait(2) == kv.KV_OK and kp.req_poll(2) == 1
+        assert kp.swap_in([2], off, d) == kv.KV_OK and kp.stats()["ms_total"] > 0 and kp.sync() == kv.KV_OK
+        want[:, 10:14] = want[:, 30:34]
+        torch.cuda.synchronize()
+        assert torch.equal(blocks, want), "behind a replay"
+    kp.close()
+
+
 @pytest.mark.parametrize("n", [60, 300, 448, 900])
 def test_noalloc_moves_in_a_row(gpu, n):
     """More allocation-free moves than the handle has upload buffers, with nothing waited for in between."""
