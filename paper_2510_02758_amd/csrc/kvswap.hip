@@ -379,6 +379,7 @@ int kv_pool_destroy(kv_pool* p) try {
     done_words_give_back(p, rc == KV_OK && !p->broken);
     if (p->na_fence_ev) (void)hipEventDestroy(p->na_fence_ev);
     if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
+    if (p->late_ev) (void)hipEventDestroy(p->late_ev);
     for (hipEvent_t e : p->na_up_ev)
       if (e) (void)hipEventDestroy(e);
     if (p->pinned) (void)hipHostFree(p->pinned);
@@ -863,23 +864,21 @@ KV_CATCH(p)
 int kv_req_wait(kv_pool* p, uint64_t req_id) try {
   if (!p) return KV_EINVAL;
   hipEvent_t ev;
+  uint64_t number;
+  int stream;
   {
     std::lock_guard<std::mutex> g(p->mu);
     if (p->plan_only) return KV_OK;
     Call* c = req_call(p, req_id, &ev);
     if (!c || (!ev && finished(p, *c))) return KV_OK;
-    if (!ev) {
-      // An event recorded now may fire later than the call's own would have.  A program that waits for single requests gets an end event
-      // with every call from here on.
-      p->end_events = true;
-      if (int rc = end_event(p, *c, &ev)) return rc;
-    }
+    number = c->done;
+    stream = c->stream;
   }
   // The wait runs without the handle's lock: a thread that waits for one request does not hold up the thread
   // that enqueues the next calls.  An event returns to the free list only after its work has finished; should
   // another call record it again meanwhile, this wait ends later than it had to, never earlier than the
   // request's own transfer.
-  const hipError_t e = hipEventSynchronize(ev);
+  const hipError_t e = ev ? hipEventSynchronize(ev) : wait_done(p, stream, number);
   if (e != hipSuccess) {
     std::lock_guard<std::mutex> g(p->mu);
     p->last_hip = (int)e;

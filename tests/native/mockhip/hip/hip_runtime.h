@@ -11,15 +11,19 @@
 // access the kernels make.  Launches that ask for dynamic LDS run the lanes of a workgroup as fibers, so that
 // __syncthreads() is a real barrier and data exchanged through LDS is emulated too (see run_grid below).
 #pragma once
+#include <sched.h>
+
 #include <cstddef>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <functional>
+#include <mutex>
+#include <thread>
 #include <vector>
 
 typedef int hipError_t;
-enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600, hipErrorStreamCaptureUnsupported = 900 };
+enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600, hipErrorStreamCaptureUnsupported = 900, hipErrorUnknown = 999 };
 enum { hipStreamNonBlocking = 1 };
 enum { hipHostMallocDefault = 0 };
 enum { hipMallocSignalMemory = 2 };
@@ -34,6 +38,9 @@ struct hipDeviceProp_t { int multiProcessorCount; };
 struct dim3 { unsigned x, y, z; dim3(unsigned a = 1, unsigned b = 1, unsigned c = 1) : x(a), y(b), z(c) {} };
 
 namespace mockhip {
+// A thread that polls memory for what the device will store gives way between its looks: the device goes on meanwhile, as in any
+// blocking wait.
+int yield_to_device();
 struct Stream;
 struct Event;
 struct Idx { unsigned x, y, z; };
@@ -59,7 +66,7 @@ long value_waits();  // calls of hipStreamWaitValue64 so far
 // event and stream creation and destruction.  An entry point that promises not to allocate leaves it unchanged.
 long resource_calls();
 // Calls of the CURRENT THREAD so far that block the host until device work has finished (hipStreamSynchronize,
-// hipEventSynchronize): an entry point that promises to be asynchronous leaves it unchanged.
+// hipEventSynchronize, and sched_yield, where a thread polls for what the device stores): an entry point that promises to be asynchronous leaves it unchanged.
 long host_waits();
 // Failure injection: the n-th call from now, counted over the calls that can fail on a real device (event
 // creation, record, wait, query and synchronisation, stream synchronisation, copies, kernel launches), returns
@@ -78,6 +85,7 @@ bool fibers_available();  // false in a ThreadSanitizer build: launches with LDS
 typedef mockhip::Stream* hipStream_t;
 typedef mockhip::Event* hipEvent_t;
 
+#define sched_yield() mockhip::yield_to_device()
 #define threadIdx mockhip::threadIdx_
 #define blockIdx mockhip::blockIdx_
 #define gridDim mockhip::gridDim_

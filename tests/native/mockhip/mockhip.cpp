@@ -2,6 +2,7 @@
 #include <atomic>
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstdio>
 #include <deque>
 #include <map>
@@ -201,6 +202,24 @@ static std::atomic<long> n_resource{0};
 long resource_calls() { return n_resource.load(); }
 static thread_local long n_host_waits = 0;
 long host_waits() { return n_host_waits; }
+
+// Twenty seconds of polling with nothing left to run: what the thread looks for never comes.
+int yield_to_device() {
+  n_host_waits++;
+  API_LOCK;
+  static auto last = std::chrono::steady_clock::now();
+  static long seen = -1;
+  const auto now = std::chrono::steady_clock::now();
+  if (step() || seen != n_exec) {
+    seen = n_exec;
+    last = now;
+  } else if (now - last > std::chrono::seconds(20)) {
+    n_deadlock++;
+    std::fprintf(stderr, "mockhip: DEADLOCK: a wait can never be satisfied\n");
+    std::abort();
+  }
+  return 0;
+}
 
 long deadlocks() {
   API_LOCK;

@@ -366,8 +366,86 @@ void records_used_up() {
   if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
 }
 
-// Calls that store a number record no end event: not behind others, and not for a program that polls; one that waits for single
-// requests gets events from then on.  What a wait, a poll and a hazard with the other stream need is there all the same.
+// A wait for one call that finishes by number ends with that call, whatever its stream has been given since: here the rest of the stream is
+// held back until the wait has returned.  The same for the statistics, and for a full ring of descriptors, which waits for the list that
+// is in the way; and while the stream is being captured.
+void waits_for_numbers() {
+  std::mt19937_64 rng(5);
+  const int n = 61;  // beyond what travels inside the arguments
+  for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY})
+    for (int what = 0; what < 5; what++) {
+      const bool host = flags & KV_PATH_ZEROCOPY;
+      const int m = what == 3 && host ? kInlineDescMax + 1 : n;  // (over the link such a list has to be longer)
+      Pool p(6 * m, 2 * m, flags);
+      std::vector<char> want = p.bytes();
+      std::vector<int32_t> blk[6];
+      for (int i = 0; i < 6; i++)
+        for (int k = 0; k < m; k++) blk[i].push_back(i * m + k);
+      auto moved = [&](int from, int to) {
+        Moves mv(rng, p.N, 1);
+        mv.src = blk[from], mv.dst = blk[to];
+        mv.apply(p, &want);
+      };
+      const int32_t off[2] = {0, m}, tok = m;
+      const uint64_t id = 3;
+      uint64_t gate = 0;
+      auto hold = [&](int s) { (void)hipStreamWaitValue64(p.st[s], &gate, 1, hipStreamWaitValueGte, ~0ull); };
+      mockhip::set_policy(mockhip::kLazy, nullptr);
+      OK(kv_move_blocks(p.h, m, blk[0].data(), blk[1].data(), nullptr));
+      moved(0, 1);
+      const long waited = mockhip::host_waits();
+      if (what == 3) {
+        if (p.h->ring_head < (size_t)m) die("the list has not been uploaded", flags);
+        p.h->ring_cap = 2 * (size_t)m;
+        OK(kv_move_blocks(p.h, m, blk[1].data(), blk[2].data(), nullptr));
+        moved(1, 2);
+        hold(0);
+        if (mockhip::host_waits() != waited) die("a wait with room in the ring", flags);
+        OK(kv_move_blocks(p.h, m, blk[2].data(), blk[3].data(), nullptr));  // where the first list is, behind what is held back
+        moved(2, 3);
+      } else {
+        OK(kv_swap_out(p.h, 1, &id, off, blk[1].data(), &tok, nullptr));
+        if (p.h->calls.back().end || !p.h->calls.back().done) die("a swap-out behind a call has an end event", flags);
+        hold(0);
+        kv_stats st{};
+        st.struct_size = sizeof(st);
+        uint64_t ids[1];
+        float ms[1];
+        if (what == 0) {
+          OK(kv_req_wait(p.h, id));
+        } else if (what == 1) {
+          OK(kv_last_stats(p.h, &st));
+          if (st.op != 1 || !(st.ms_total > 0)) die("statistics", flags);
+        } else if (what == 2) {
+          if (kv_last_timeline(p.h, ids, ms, 1) != 1 || ids[0] != id || !(ms[0] > 0)) die("timeline", flags);
+        } else {
+          Captured cap(true);
+          (void)hipStreamWaitEvent(p.st[0], cap.fork, 0);
+          if (kv_req_poll(p.h, id) != 0) die("a request is complete before anything has run", flags);
+          OK(kv_req_wait(p.h, id));
+          OK(kv_last_stats(p.h, &st));
+          (void)cap.end({p.st[0]});
+          if (mockhip::capture_errors()) die("calls that a capture does not allow", mockhip::capture_errors(), flags);
+        }
+        if (kv_req_poll(p.h, id) != 1 || p.bytes() != want) die("a request that was waited for", what, flags);
+      }
+      if (mockhip::host_waits() == waited) die("no wait", what, flags);
+      kv_io_stats io{};
+      io.struct_size = sizeof(io);
+      OK(kv_io_stats_get(p.h, &io));
+      if (io.inflight_calls[0]) die("a finished call is in flight", what, flags);
+      gate = 1;
+      OK(kv_move_blocks(p.h, m, blk[3].data(), blk[4].data(), nullptr));
+      moved(3, 4);
+      if (p.h->calls.back().end) die("an end event behind a wait", what, flags);
+      OK(kv_sync(p.h));
+      if (p.bytes() != want) die("bytes", what, flags);
+      mockhip::set_policy(mockhip::kRandom, nullptr);
+    }
+}
+
+// Calls that store a number record no end event: not behind others, and not for a program that polls or waits for single
+// requests.  What a wait, a poll and a hazard with the other stream need is there all the same.
 void no_end_events() {
   std::mt19937_64 rng(3);
   for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
@@ -414,7 +492,7 @@ void no_end_events() {
     if (kv_req_poll(p.h, id2) != 1 || p.bytes() != want) die("a request that was waited for", flags);
     OK(kv_move_blocks(p.h, 3, b.data(), c.data(), nullptr));
     moved(b, c);
-    if (!last().end) die("no end event for a program that waits for requests", flags);
+    if (last().end) die("an end event for a program that waits for requests", flags);
     OK(kv_sync(p.h));
     if (p.bytes() != want) die("bytes", flags);
     mockhip::set_policy(mockhip::kRandom, nullptr);
@@ -447,12 +525,55 @@ void late_profiler(const char* tool) {
   if (swap_and_exchange(p) || swap_and_exchange(q) || mockhip::value_waits() != before) die("a wait for a number under a tool that came late");
 }
 
+// A call without an end event that the other stream has to wait for after a tool has come: by an event recorded then, or, where the
+// event would be a graph's, on the host.
+void late_events(const char* tool) {
+  const int n = 4;
+  const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {5, 6, 7, 8}, c[n] = {9, 10, 11, 12};
+  const uint64_t id = 5;
+  Pool p(16), q(16);
+  std::vector<char> want[2];
+  uint64_t gate = 0;  // holds p's move back until it is p's turn
+  for (Pool* r : {&p, &q}) {
+    std::vector<char>& w = want[r == &q];
+    w = r->bytes();
+    std::mt19937_64 rng(6);
+    Moves m(rng, r->N, 1);
+    OK(kv_swap_out(r->h, 1, &id, off, a, &tok, nullptr));
+    OK(kv_sync(r->h));
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    if (r == &p) (void)hipStreamWaitValue64(r->st[0], &gate, 1, hipStreamWaitValueGte, ~0ull);
+    OK(kv_move_blocks(r->h, n, b, c, nullptr));
+    if (r->h->calls.back().end) die("a short move has an end event");
+    m.src.assign(a, a + n), m.dst.assign(c, c + n);  // the swap-in into c comes last
+    m.apply(*r, &w);
+  }
+  if (!dlopen(tool, RTLD_NOW | RTLD_GLOBAL)) die("the tool cannot be loaded");
+  for (Pool* r : {&q, &p}) {
+    const long values = mockhip::value_waits(), waits = mockhip::host_waits();
+    {
+      Captured cap(true);
+      if (r == &q) (void)hipStreamWaitEvent(r->st[0], cap.fork, 0);
+      OK(kv_swap_in(r->h, 1, &id, off, c, 0, nullptr));
+      (void)cap.end({cap.origin});
+    }
+    if (mockhip::value_waits() != values) die("a wait for a number under a tool that came late");
+    if ((mockhip::host_waits() != waits) != (r == &q)) die("waits on the host", r == &q);
+    gate = r == &p;
+    mockhip::set_policy(mockhip::kStarve0, r->st[0]);  // the load goes first where nothing holds it back
+    OK(kv_sync(r->h));
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    if (r->bytes() != want[r == &q]) die("a load has not waited for a move", r == &q);
+  }
+  if (mockhip::capture_errors()) die("calls that a capture does not allow", mockhip::capture_errors());
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
-  if (argc == 3 && !std::strcmp(argv[1], "late_profiler")) {
-    late_profiler(argv[2]);
-    std::printf("late_profiler ok\n");
+  if (argc == 3) {
+    !std::strcmp(argv[1], "late_profiler") ? late_profiler(argv[2]) : late_events(argv[2]);
+    std::printf("%s ok\n", argv[1]);
     return 0;
   }
   const struct {
@@ -460,7 +581,7 @@ int main(int argc, char** argv) {
     void (*run)();
   } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
                 {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up},
-                {"no_end_events", no_end_events}};
+                {"no_end_events", no_end_events}, {"waits_for_numbers", waits_for_numbers}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {
       mockhip::reset(5);

@@ -141,7 +141,7 @@ def _build_rare_paths(exe, csrc_dir, flags):
 def _run_rare_path(exe, section, tmp_path):
     env = dict(os.environ, ASAN_OPTIONS=ASAN_OPTS, UBSAN_OPTIONS="print_stacktrace=1")
     args = [section]
-    if section == "late_profiler":    # a library that exports what profiling tools export
+    if section in ("late_profiler", "late_events"):    # a library that exports what profiling tools export
         (tmp_path / "tool.c").write_text("void* rocprofiler_configure(void) { return 0; }\n")
         args.append(str(tmp_path / "tool.so"))
         subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", args[1], str(tmp_path / "tool.c")])
@@ -154,7 +154,7 @@ def rare_paths(tmp_path_factory):
 
 
 @pytest.mark.parametrize("section", ["capture", "captured_calls", "scatter_order", "exchange_times", "uploads", "counters_used_up", "records_used_up",
-                                     "late_profiler", "no_end_events"])
+                                     "late_profiler", "late_events", "no_end_events", "waits_for_numbers"])
 def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""
     r = _run_rare_path(rare_paths, section, tmp_path)
@@ -264,8 +264,8 @@ RUNTIME_MUTANTS = [
      "      HIPCHK(p, hipStreamWaitEvent(st, p->na_done_ev, 0));", ""),
     ("load_phase_forgets_the_eviction_phase_that_frees_its_blocks",
      "    if (it != reader.end()) need[i / m] = std::max(need[i / m], it->second);", "    (void)it;"),
-    ("number_of_the_launch_before_waited_for", "hipStreamWaitValue64(st, p->done_word[c.stream], v, ",
-     "hipStreamWaitValue64(st, p->done_word[c.stream], v - 1, "),
+    ("number_of_the_launch_before_waited_for", "hipStreamWaitValue64(st, p->done_word[other], v, ",
+     "hipStreamWaitValue64(st, p->done_word[other], v - 1, "),
     ("write_through_that_moves_nothing_forgets_the_pending_reader",
      "        if (kvswap::Req* r = p->planner.find_mut(id)) r->in_seq = std::max(r->in_seq, fresh_dep);", "        (void)id;"),
 ]
