@@ -199,7 +199,7 @@ static int noalloc_setup(kv_pool* p) {
     return KV_EHIP;
   }
   HIPCHK(p, hipEventCreate(&p->na_fence_ev));
-  HIPCHK(p, hipEventCreate(&p->na_done_ev));
+  for (hipEvent_t& e : p->na_done_ev) HIPCHK(p, hipEventCreate(&e));
   p->na_mark.assign((size_t)((p->cfg.num_blocks + 63) / 64), 0);
   p->na_list.reserve(p->na_cap);
   p->na_tmp.reserve(p->na_cap);
@@ -378,7 +378,8 @@ int kv_pool_destroy(kv_pool* p) try {
     tickets_give_back(p, rc == KV_OK && !p->broken);
     done_words_give_back(p, rc == KV_OK && !p->broken);
     if (p->na_fence_ev) (void)hipEventDestroy(p->na_fence_ev);
-    if (p->na_done_ev) (void)hipEventDestroy(p->na_done_ev);
+    for (hipEvent_t e : p->na_done_ev)
+      if (e) (void)hipEventDestroy(e);
     if (p->late_ev) (void)hipEventDestroy(p->late_ev);
     for (hipEvent_t e : p->na_up_ev)
       if (e) (void)hipEventDestroy(e);
@@ -637,6 +638,13 @@ KV_CATCH(p)
 // reads: 60 000 blocks of 16 KiB 525 us (965 inside the arguments of 134 fill launches, 3 to 8 us of host time each).
 // Inside the arguments of fill launches where all buffers are still being read (the call does not wait for them) and under graph
 // capture (a replay would read the buffer again).
+//
+// What later calls of the load stream wait for: the number that the kernel stores, up to kNoallocNumber, else an event behind it.  Us queued / each
+// waited for, with neither, with the event, with the number: 8 blocks of 32 KiB 5.7 / 16.5, 10.3 / 14.5, 5.7 / 16.4; 300 of 16 KiB 13.0 / 23, 16.3 / 23.7, 13.4 /
+// 24.1; of 2 MiB: 16 11.2 / 23.5, 14.3 / 23.5, 12.9 / 25.4; 24 15.9 / 28.2, 18.9 / 28.3, 18.1 / 30.4; 32 21.1 / 33.4, 24.1 / 33.5, 24.0 / 36.6; 46 31.1 / 43.4,
+// 34.1 / 43.6, 36.4 / 49.8; 64 43.0 / 55.7, 46.2 / 55.8 (no number); 700 of 23 KiB 17.4 / 32.6, 21.4 / 32.4, 18.1 / 33.7.  (An event recorded by the first call
+// that needs it cannot be had once a capture has begun on the stream.)
+constexpr int64_t kNoallocNumber = 32ll << 20;
 int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const int32_t* dst_ids, void* wait_event) try {
   if (!p) return KV_EINVAL;
   KV_ENTER(p);
@@ -685,6 +693,7 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
   hipEvent_t callers = (hipEvent_t)wait_event;
   if (callers) HIPCHK(p, hipStreamWaitEvent(st, callers, 0));
   const bool captured = capturing(st);  // (asked behind the two waits, either of which may have drawn the stream into a capture)
+  Finish f;
   if (n > 0) {
     // Short lists travel inside the arguments of the move itself.  The array keeps the previous call's descriptors: [0, n)
     // is overwritten here, in stream order behind the previous call's kernel, and nothing beyond n is read.
@@ -721,7 +730,14 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     (void)hipGetLastError();
     int grid;
     if (hbm) {
-      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? list.data() : nullptr, (size_t)n, nullptr, pm, st);
+      // Later calls of the load stream wait for its number (a replay would store it again: none under capture) or, where counting its workgroups
+      // costs more, for an event behind it.
+      if (!captured && n * p->S <= kNoallocNumber && plan_launch(p, kEvict, 2, (size_t)n, 0, true).number) {
+        f.done = ++p->done_last[kEvict];
+        f.word = p->done_word[kEvict];
+        f.leave = p->leave[kEvict];
+      }
+      grid = launch_hbm(p, 2, p->na_dev, inline_desc ? list.data() : nullptr, (size_t)n, nullptr, pm, st, f);
     } else {
       MoveArgs a;
       int u = 1;
@@ -735,11 +751,13 @@ int kv_move_blocks_noalloc(kv_pool* p, int64_t n, const int32_t* src_ids, const 
     p->plan_stats.launches = 1;
     p->plan_stats.grid = grid;
   }
-  // (recorded by the next call that comes behind it, see open_call(): 64 blocks of 2 MiB queued 45.0 us with its event, 41.9 without, 8 of
-  // 32 KiB 10.3 and 6.4)
-  if (captured) HIPCHK(p, hipEventRecord(p->na_done_ev, st));
-  p->na_recorded = captured;
-  p->na_pending = true;
+  if (f.done) {
+    p->na_done = f.done;
+    p->na_pending[0] = false;
+  } else {
+    HIPCHK(p, hipEventRecord(p->na_done_ev[captured], st));
+    p->na_pending[captured] = true;
+  }
   p->plan_stats.enqueue_us = now_us() - t0 - p->plan_stats.plan_us;
   return KV_OK;
 }
@@ -751,7 +769,6 @@ int kv_sync(kv_pool* p) try {
   if (p->plan_only) return KV_OK;
   for (int s = 0; s < 2; s++) HIPCHK(p, hipStreamSynchronize(p->stream[s]));
   retire(p);
-  if (!p->na_recorded) p->na_pending = false;
   return KV_OK;
 }
 KV_CATCH(p)

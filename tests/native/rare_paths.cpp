@@ -145,225 +145,277 @@ struct Captured {
 };
 
 // Calls that keep a record go into a graph as well, and the handle goes on behind them: what is captured runs with each replay and not
-// before, and eager calls on both streams, polls, waits and telemetry work as ever.  (A swap-in that is captured asks for the swap-out in front
+// before, and eager calls on both streams, polls, waits and telemetry work as ever.  `front`: in front of it nothing, an allocation-free move
+// that stores a number, one with an event; the program itself has waited for that move, and the handle has not looked.  (A swap-in that is captured asks for the swap-out in front
 // of it, which only the relaxed mode allows.)
 void captured_calls() {
   const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12}, e{13, 14, 15};
   const int32_t off[2] = {0, 3}, tok = 3;
   const uint64_t id1 = 1, id2 = 2, id4 = 4, id7 = 7;
+  const std::vector<int32_t> f{20, 21, 22}, h{23, 24, 25};
   for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY})
-    for (int kind = 0; kind < 4; kind++) {  // a move a to d, a swap-out of a, a swap-in to d of what has been swapped out of c, both
-      Pool p(40, 16, flags);
-      std::mt19937_64 rng(4);
-      std::vector<char> want = p.bytes();
-      Moves m(rng, p.N, 1);
-      auto moved = [&](const std::vector<int32_t>& src, const std::vector<int32_t>& dst) {
-        m.src = src, m.dst = dst;
-        m.apply(p, &want);
-      };
-      if (kind >= 2) {
-        OK(kv_swap_out(p.h, 1, &id7, off, c.data(), &tok, nullptr));
-        OK(kv_swap_out(p.h, 1, &id4, off, b.data(), &tok, nullptr));
-        OK(kv_sync(p.h));
-      }
-      Captured cap(kind >= 2);
-      if (kind == 0)
-        OK(kv_move_blocks(p.h, 3, a.data(), d.data(), cap.fork));
-      else if (kind == 1)
-        OK(kv_swap_out(p.h, 1, &id1, off, a.data(), &tok, cap.fork));
-      else if (kind == 2)
-        OK(kv_swap_in(p.h, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
-      else
-        OK(kv_evict_and_load(p.h, 1, &id1, off, a.data(), &tok, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
-      const mockhip::Graph g = kind == 0 || kind == 1 ? cap.end({p.st[0]}) : kind == 2 ? cap.end({p.st[1]}) : cap.end({p.st[0], p.st[1]});
-      if (mockhip::capture_errors()) die("calls that a capture does not allow, kind", mockhip::capture_errors(), kind);
-      if (p.bytes() != want) die("a captured call has run, kind", kind, flags);
-      for (int turn = 0; turn < 3; turn++) {
-        for (int32_t blk : a)
-          for (int64_t k = 0; k < Pool::planes; k++) {
-            std::memset(p.pool + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
-            std::memset(want.data() + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
-          }
-        cap.replay(g);
-        if (kind == 0) moved(a, d);
-        if (kind >= 2) moved(c, d);
-        if (p.bytes() != want) die("bytes of a replay, kind", kind, turn);
-        if (kind == 1 || kind == 3) {
-          OK(kv_swap_in(p.h, 1, &id1, off, e.data(), KV_KEEP_STAGING, nullptr));
-          moved(a, e);
+    for (int front = 0; front < 3; front++)
+      for (int kind = 0; kind < 4; kind++) {  // a move a to d, a swap-out of a, a swap-in to d of what has been swapped out of c, both
+        Pool p(40, 16, flags);
+        std::mt19937_64 rng(4);
+        std::vector<char> want = p.bytes();
+        Moves m(rng, p.N, 1);
+        auto moved = [&](const std::vector<int32_t>& src, const std::vector<int32_t>& dst) {
+          m.src = src, m.dst = dst;
+          m.apply(p, &want);
+        };
+        if (kind >= 2) {
+          OK(kv_swap_out(p.h, 1, &id7, off, c.data(), &tok, nullptr));
+          OK(kv_swap_out(p.h, 1, &id4, off, b.data(), &tok, nullptr));
+          OK(kv_sync(p.h));
         }
-        OK(kv_move_blocks(p.h, 3, d.data(), b.data(), nullptr));
-        moved(d, b);
-        OK(kv_swap_out(p.h, 1, &id2, off, b.data(), &tok, nullptr));
-        OK(kv_req_wait(p.h, id2));
-        if (kv_req_poll(p.h, id2) != 1) die("a request that was waited for, kind", kind, turn);
-        OK(kv_swap_in(p.h, 1, &id2, off, d.data(), 0, nullptr));
-        moved(b, d);
+        if (front) {
+          p.h->by_number = front == 1;
+          OK(kv_move_blocks_noalloc(p.h, 3, f.data(), h.data(), nullptr));
+          p.h->by_number = true;
+          moved(f, h);
+          if (!p.h->na_done == (front == 1)) die("number of an allocation-free move", front, kind);
+          (void)hipStreamSynchronize(p.st[0]);
+        }
+        Captured cap(kind >= 2);
+        if (front) (void)hipStreamWaitEvent(p.st[0], cap.fork, 0);  // (it is in the capture before the call)
+        if (kind == 0)
+          OK(kv_move_blocks(p.h, 3, a.data(), d.data(), cap.fork));
+        else if (kind == 1)
+          OK(kv_swap_out(p.h, 1, &id1, off, a.data(), &tok, cap.fork));
+        else if (kind == 2)
+          OK(kv_swap_in(p.h, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
+        else
+          OK(kv_evict_and_load(p.h, 1, &id1, off, a.data(), &tok, 1, &id7, off, d.data(), KV_KEEP_STAGING, cap.fork));
+        const mockhip::Graph g = kind == 0 || kind == 1 ? cap.end({p.st[0]}) : kind == 2 && !front ? cap.end({p.st[1]}) : cap.end({p.st[0], p.st[1]});
+        if (mockhip::capture_errors()) die("calls that a capture does not allow, kind", mockhip::capture_errors(), kind);
+        if (p.bytes() != want) die("a captured call has run, kind", kind, flags);
+        for (int turn = 0; turn < 3; turn++) {
+          for (int32_t blk : a)
+            for (int64_t k = 0; k < Pool::planes; k++) {
+              std::memset(p.pool + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
+              std::memset(want.data() + (k * p.N + blk) * p.chunk, turn, (size_t)p.chunk);
+            }
+          cap.replay(g);
+          if (kind == 0) moved(a, d);
+          if (kind >= 2) moved(c, d);
+          if (p.bytes() != want) die("bytes of a replay, kind", kind, turn);
+          if (kind == 1 || kind == 3) {
+            OK(kv_swap_in(p.h, 1, &id1, off, e.data(), KV_KEEP_STAGING, nullptr));
+            moved(a, e);
+          }
+          OK(kv_move_blocks(p.h, 3, d.data(), b.data(), nullptr));
+          moved(d, b);
+          OK(kv_swap_out(p.h, 1, &id2, off, b.data(), &tok, nullptr));
+          OK(kv_req_wait(p.h, id2));
+          if (kv_req_poll(p.h, id2) != 1) die("a request that was waited for, kind", kind, turn);
+          OK(kv_swap_in(p.h, 1, &id2, off, d.data(), 0, nullptr));
+          moved(b, d);
+          kv_stats st{};
+          st.struct_size = sizeof(st);
+          OK(kv_last_stats(p.h, &st));
+          if (st.op != 3 || !(st.ms_total > 0)) die("statistics behind a captured call, kind", kind, turn);
+          OK(kv_sync(p.h));
+          if (p.bytes() != want) die("bytes behind a captured call, kind", kind, turn);
+        }
+      }
+}
+
+  // kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
+  // plane by plane from 60 MiB on).
+  void scatter_order() {
+    const int n = 976, N = 1000;
+    Pool p(N, n, KV_STAGING_DEVICE, 16384);
+    const uint64_t id = 3;
+    const int32_t off[2] = {0, n}, tok = n;
+    std::vector<int32_t> ids(n);
+    for (int i = 0; i < n; i++) ids[(size_t)i] = i * 17 % N;
+    const std::vector<char> want = p.bytes();
+    for (bool collide : {false, true})
+      for (int knob = 0; knob < 3; knob++) {
+        p.h->planes_collide = collide;
+        OK(kv_pool_tune(p.h, KV_TUNE_SCATTER_ORDER, knob));
         kv_stats st{};
         st.struct_size = sizeof(st);
+        OK(kv_swap_out(p.h, 1, &id, off, ids.data(), &tok, nullptr));
         OK(kv_last_stats(p.h, &st));
-        if (st.op != 3 || !(st.ms_total > 0)) die("statistics behind a captured call, kind", kind, turn);
-        OK(kv_sync(p.h));
-        if (p.bytes() != want) die("bytes behind a captured call, kind", kind, turn);
+        if (st.scatter_order != -1) die("order of a gather", st.scatter_order, knob);
+        for (int i = 0; i < n; i++) std::memset(p.pool + ids[(size_t)i] * p.chunk, 0, (size_t)p.chunk);
+        OK(kv_swap_in(p.h, 1, &id, off, ids.data(), 0, nullptr));
+        OK(kv_last_stats(p.h, &st));
+        if (st.scatter_order != (knob == 2 || (collide && knob == 0) ? 1 : -1)) die("order of a scatter, knob", st.scatter_order, knob);
+        if (p.bytes() != want) die("bytes of a swap, knob", collide, knob);
       }
-    }
 }
 
-// kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
-// plane by plane from 60 MiB on).
-void scatter_order() {
-  const int n = 976, N = 1000;
-  Pool p(N, n, KV_STAGING_DEVICE, 16384);
-  const uint64_t id = 3;
-  const int32_t off[2] = {0, n}, tok = n;
-  std::vector<int32_t> ids(n);
-  for (int i = 0; i < n; i++) ids[(size_t)i] = i * 17 % N;
-  const std::vector<char> want = p.bytes();
-  for (bool collide : {false, true})
-    for (int knob = 0; knob < 3; knob++) {
-      p.h->planes_collide = collide;
-      OK(kv_pool_tune(p.h, KV_TUNE_SCATTER_ORDER, knob));
+  // kv_stats.ms_kernel of an exchange is its kernels alone, without what the load has waited for, also where a launch does not
+  // time itself (a workgroup cap: kv_move_kernel).
+  void exchange_times() {
+    for (int cap : {0, 4}) {
+      const int n = 8;
+      Pool p(40, 2 * n);
+      OK(kv_pool_tune(p.h, KV_TUNE_MAX_WGS_DEVICE, cap));
+      const uint64_t out = 1, in = 2;
+      const int32_t off[2] = {0, n}, tok = n;
+      int32_t a[n], b[n];
+      for (int i = 0; i < n; i++) a[i] = i, b[i] = 20 + i;
+      OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+      OK(kv_sync(p.h));
+      mockhip::set_policy(mockhip::kLazy, nullptr);  // nothing runs before the host waits: the load waits for the eviction
+      OK(kv_evict_and_load(p.h, 1, &out, off, a, &tok, 1, &in, off, a, 0, nullptr));
       kv_stats st{};
       st.struct_size = sizeof(st);
-      OK(kv_swap_out(p.h, 1, &id, off, ids.data(), &tok, nullptr));
       OK(kv_last_stats(p.h, &st));
-      if (st.scatter_order != -1) die("order of a gather", st.scatter_order, knob);
-      for (int i = 0; i < n; i++) std::memset(p.pool + ids[(size_t)i] * p.chunk, 0, (size_t)p.chunk);
-      OK(kv_swap_in(p.h, 1, &id, off, ids.data(), 0, nullptr));
-      OK(kv_last_stats(p.h, &st));
-      if (st.scatter_order != (knob == 2 || (collide && knob == 0) ? 1 : -1)) die("order of a scatter, knob", st.scatter_order, knob);
-      if (p.bytes() != want) die("bytes of a swap, knob", collide, knob);
-    }
-}
-
-// kv_stats.ms_kernel of an exchange is its kernels alone, without what the load has waited for, also where a launch does not
-// time itself (a workgroup cap: kv_move_kernel).
-void exchange_times() {
-  for (int cap : {0, 4}) {
-    const int n = 8;
-    Pool p(40, 2 * n);
-    OK(kv_pool_tune(p.h, KV_TUNE_MAX_WGS_DEVICE, cap));
-    const uint64_t out = 1, in = 2;
-    const int32_t off[2] = {0, n}, tok = n;
-    int32_t a[n], b[n];
-    for (int i = 0; i < n; i++) a[i] = i, b[i] = 20 + i;
-    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
-    OK(kv_sync(p.h));
-    mockhip::set_policy(mockhip::kLazy, nullptr);  // nothing runs before the host waits: the load waits for the eviction
-    OK(kv_evict_and_load(p.h, 1, &out, off, a, &tok, 1, &in, off, a, 0, nullptr));
-    kv_stats st{};
-    st.struct_size = sizeof(st);
-    OK(kv_last_stats(p.h, &st));
-    if (st.op != 3 || st.launches != 1 || !(st.ms_kernel > 0)) die("statistics of an exchange's load", st.op, st.launches);
-    if (cap ? st.ms_kernel >= st.ms_total : st.ms_kernel != st.ms_total) die("ms_kernel of an exchange's load, cap", cap, (long)(st.ms_kernel * 1e6));
-    mockhip::set_policy(mockhip::kRandom, nullptr);
-  }
-}
-
-// Allocation-free moves in a row while the evict stream is held back: from the upload buffers as long as one is free, then (none
-// is free before the stream runs) inside the arguments of the move or of fill launches.
-void uploads() {
-  std::mt19937_64 rng(2);
-  for (int64_t N : {2003, 66000})  // four buffers, and two
-    for (size_t n : {60, 61, 448, 449, 897, 1000}) {
-      Pool p(N);
-      std::vector<char> want = p.bytes();
-      mockhip::set_policy(mockhip::kLazy, nullptr);
-      for (int turn = 0; turn < 2; turn++) {
-        for (int k = 0; k < 7; k++) {
-          const Moves m(rng, N, n - (size_t)(k % 3));  // lists that leave the end of an earlier, longer one behind theirs
-          OK(m.run(p));
-          m.apply(p, &want);
-        }
-        OK(kv_sync(p.h));
-        if (p.bytes() != want) die("bytes of moves in a row: n, turn", (long)n, turn);
-      }
+      if (st.op != 3 || st.launches != 1 || !(st.ms_kernel > 0)) die("statistics of an exchange's load", st.op, st.launches);
+      if (cap ? st.ms_kernel >= st.ms_total : st.ms_kernel != st.ms_total) die("ms_kernel of an exchange's load, cap", cap, (long)(st.ms_kernel * 1e6));
       mockhip::set_policy(mockhip::kRandom, nullptr);
     }
 }
 
-// One swap out and in, and one exchange, on a handle; returns the waits for a number that were made.
-long swap_and_exchange(Pool& p) {
-  const int n = 4;
-  const uint64_t id = 3, in = 8;
-  const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
-  mockhip::set_policy(mockhip::kLazy, nullptr);
-  const long before = mockhip::value_waits();
-  std::vector<char> want = p.bytes();
-  auto move = [&](const int32_t* from, const int32_t* to) {
-    const std::vector<char> was = want;
-    for (int i = 0; i < n; i++)
-      for (int64_t k = 0; k < Pool::planes; k++)
-        std::memcpy(want.data() + (k * p.N + to[i]) * p.chunk, was.data() + (k * p.N + from[i]) * p.chunk, (size_t)p.chunk);
-  };
-  kv_stats st{};
-  st.struct_size = sizeof(st);
-  OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
-  OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
-  move(a, b);
-  OK(kv_last_stats(p.h, &st));
-  if (!(st.ms_total > 0)) die("no time of a load");
-  OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
-  OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
-  move(b, a);
-  OK(kv_last_stats(p.h, &st));
-  if (!(st.ms_total > 0) || !(st.ms_kernel > 0)) die("no time of an exchange");
-  OK(kv_req_release(p.h, id));
-  OK(kv_sync(p.h));
-  if (p.bytes() != want) die("bytes of a swap and an exchange");
-  mockhip::set_policy(mockhip::kRandom, nullptr);
-  return mockhip::value_waits() - before;
-}
-
-// Handles behind the first 128, which have no counters for launches with both ends in HBM, and behind the first 1024, whose job
-// counters of the link are an allocation of their own.
-void counters_used_up() {
-  for (int others : {0, kLeaveSlots, kTicketSlots})
-    for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
-      for (int s = 0; s < others; s++) g_ticket_taken[0][s >> 6] |= 1ull << (s & 63);  // as if that many handles were there
-      {
-        Pool p(9, 16, flags);
-        const bool device = flags & KV_STAGING_DEVICE;
-        if (p.h->ticket_slot != (others < kTicketSlots ? others : -1)) die("slot of a handle", p.h->ticket_slot, others);
-        for (int turn = 0; turn < 3; turn++) {
-          const long waits = swap_and_exchange(p);
-          if (!waits != (device && others)) die("waits for a number: others, waits", others, waits);
+  // Allocation-free moves in a row while the evict stream is held back: from the upload buffers as long as one is free, then (none
+  // is free before the stream runs) inside the arguments of the move or of fill launches.
+  void uploads() {
+    std::mt19937_64 rng(2);
+    for (int64_t N : {2003, 66000})  // four buffers, and two
+      for (size_t n : {60, 61, 448, 449, 897, 1000}) {
+        Pool p(N);
+        std::vector<char> want = p.bytes();
+        mockhip::set_policy(mockhip::kLazy, nullptr);
+        for (int turn = 0; turn < 2; turn++) {
+          for (int k = 0; k < 7; k++) {
+            const Moves m(rng, N, n - (size_t)(k % 3));  // lists that leave the end of an earlier, longer one behind theirs
+            OK(m.run(p));
+            m.apply(p, &want);
+          }
+          OK(kv_sync(p.h));
+          if (p.bytes() != want) die("bytes of moves in a row: n, turn", (long)n, turn);
         }
+        mockhip::set_policy(mockhip::kRandom, nullptr);
       }
-      std::memset(g_ticket_taken[0], 0, sizeof(g_ticket_taken[0]));
-    }
 }
 
-// More calls in flight than there are records of the clock: the others have start events.
-void records_used_up() {
-  Pool p(9);
+  // One swap out and in, and one exchange, on a handle; returns the waits for a number that were made.
+  long swap_and_exchange(Pool& p) {
+    const int n = 4;
+    const uint64_t id = 3, in = 8;
+    const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    const long before = mockhip::value_waits();
+    std::vector<char> want = p.bytes();
+    auto move = [&](const int32_t* from, const int32_t* to) {
+      const std::vector<char> was = want;
+      for (int i = 0; i < n; i++)
+        for (int64_t k = 0; k < Pool::planes; k++)
+          std::memcpy(want.data() + (k * p.N + to[i]) * p.chunk, was.data() + (k * p.N + from[i]) * p.chunk, (size_t)p.chunk);
+    };
+    kv_stats st{};
+    st.struct_size = sizeof(st);
+    OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
+    OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
+    move(a, b);
+    OK(kv_last_stats(p.h, &st));
+    if (!(st.ms_total > 0)) die("no time of a load");
+    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+    OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
+    move(b, a);
+    OK(kv_last_stats(p.h, &st));
+    if (!(st.ms_total > 0) || !(st.ms_kernel > 0)) die("no time of an exchange");
+    OK(kv_req_release(p.h, id));
+    OK(kv_sync(p.h));
+    if (p.bytes() != want) die("bytes of a swap and an exchange");
+    mockhip::set_policy(mockhip::kRandom, nullptr);
+    return mockhip::value_waits() - before;
+}
+
+  // Handles behind the first 128, which have no counters for launches with both ends in HBM, and behind the first 1024, whose job
+  // counters of the link are an allocation of their own.
+  void counters_used_up() {
+    for (int others : {0, kLeaveSlots, kTicketSlots})
+      for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
+        for (int s = 0; s < others; s++) g_ticket_taken[0][s >> 6] |= 1ull << (s & 63);  // as if that many handles were there
+        {
+          Pool p(9, 16, flags);
+          const bool device = flags & KV_STAGING_DEVICE;
+          if (p.h->ticket_slot != (others < kTicketSlots ? others : -1)) die("slot of a handle", p.h->ticket_slot, others);
+          for (int turn = 0; turn < 3; turn++) {
+            const long waits = swap_and_exchange(p);
+            if (!waits != (device && others)) die("waits for a number: others, waits", others, waits);
+          }
+        }
+        std::memset(g_ticket_taken[0], 0, sizeof(g_ticket_taken[0]));
+      }
+}
+
+  // More calls in flight than there are records of the clock: the others have start events.
+  void records_used_up() {
+    Pool p(9);
+    const uint64_t id = 3;
+    const int32_t off[2] = {0, 2}, tok = 2, a[2] = {1, 2}, b[2] = {5, 6};
+    const std::vector<char> before = p.bytes();
+    mockhip::set_policy(mockhip::kLazy, nullptr);
+    const int pairs = kStamps / 2 + 40;
+    for (int i = 0; i < pairs; i++) {
+      OK(kv_swap_out(p.h, 1, &id, off, i % 2 ? b : a, &tok, nullptr));
+      OK(kv_swap_in(p.h, 1, &id, off, i % 2 ? a : b, 0, nullptr));
+    }
+    if (!p.h->stamp_free.empty() || p.h->calls.back().stamp || !p.h->calls.back().start) die("records left", (long)p.h->stamp_free.size());
+    kv_stats st{};
+    st.struct_size = sizeof(st);
+    OK(kv_last_stats(p.h, &st));
+    if (!(st.ms_total > 0)) die("no time of a call without a record");
+    OK(kv_sync(p.h));
+    std::vector<char> want = before;
+    for (int i = 0; i < 2; i++)
+      for (int64_t k = 0; k < Pool::planes; k++)
+        std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, before.data() + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
+    if (p.bytes() != want) die("bytes of calls in flight");
+    mockhip::set_policy(mockhip::kRandom, nullptr);
+    swap_and_exchange(p);
+    kv_io_stats io{};
+    io.struct_size = sizeof(io);
+    OK(kv_io_stats_get(p.h, &io));
+    if (io.total_calls[0] + io.total_calls[1] < 2 * pairs || !(io.ewma_small_us[0] > 0 && io.ewma_small_us[1] > 0)) die("telemetry", io.total_calls[0], io.total_calls[1]);
+    if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
+}
+
+// An allocation-free move that is still under way when its stream is drawn into a capture: calls of the load stream come behind it all the
+// same, by its number or by the event recorded behind it, during the capture as well as after one that another such move has gone into.
+void capture_behind_a_move() {
+  const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12}, e{13, 14, 15};
+  const int32_t off[2] = {0, 3}, tok = 3;
   const uint64_t id = 3;
-  const int32_t off[2] = {0, 2}, tok = 2, a[2] = {1, 2}, b[2] = {5, 6};
-  const std::vector<char> before = p.bytes();
-  mockhip::set_policy(mockhip::kLazy, nullptr);
-  const int pairs = kStamps / 2 + 40;
-  for (int i = 0; i < pairs; i++) {
-    OK(kv_swap_out(p.h, 1, &id, off, i % 2 ? b : a, &tok, nullptr));
-    OK(kv_swap_in(p.h, 1, &id, off, i % 2 ? a : b, 0, nullptr));
-  }
-  if (!p.h->stamp_free.empty() || p.h->calls.back().stamp || !p.h->calls.back().start) die("records left", (long)p.h->stamp_free.size());
-  kv_stats st{};
-  st.struct_size = sizeof(st);
-  OK(kv_last_stats(p.h, &st));
-  if (!(st.ms_total > 0)) die("no time of a call without a record");
-  OK(kv_sync(p.h));
-  std::vector<char> want = before;
-  for (int i = 0; i < 2; i++)
-    for (int64_t k = 0; k < Pool::planes; k++)
-      std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, before.data() + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
-  if (p.bytes() != want) die("bytes of calls in flight");
-  mockhip::set_policy(mockhip::kRandom, nullptr);
-  swap_and_exchange(p);
-  kv_io_stats io{};
-  io.struct_size = sizeof(io);
-  OK(kv_io_stats_get(p.h, &io));
-  if (io.total_calls[0] + io.total_calls[1] < 2 * pairs || !(io.ewma_small_us[0] > 0 && io.ewma_small_us[1] > 0)) die("telemetry", io.total_calls[0], io.total_calls[1]);
-  if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
+  for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY})
+    for (int how = 0; how < 4; how++) {
+      const bool number = how % 2 == 0, behind = how >= 2;
+      Pool p(40, 16, flags);
+      std::mt19937_64 rng(8);
+      std::vector<char> want = p.bytes();
+      Moves m(rng, p.N, 1);
+      OK(kv_swap_out(p.h, 1, &id, off, c.data(), &tok, nullptr));
+      OK(kv_sync(p.h));
+      mockhip::set_policy(mockhip::kLazy, nullptr);
+      p.h->by_number = number;
+      OK(kv_move_blocks_noalloc(p.h, 3, a.data(), b.data(), nullptr));
+      m.src = a, m.dst = b;
+      m.apply(p, &want);
+      const long values = mockhip::value_waits();
+      {
+        Captured cap(true);
+        if (behind) OK(kv_move_blocks_noalloc(p.h, 3, d.data(), e.data(), cap.fork));
+        (void)hipStreamWaitEvent(p.st[0], cap.fork, 0);
+        if (!behind) OK(kv_swap_in(p.h, 1, &id, off, a.data(), 0, nullptr));  // into what the move reads
+        (void)cap.end({p.st[0]});
+        if (behind) OK(kv_swap_in(p.h, 1, &id, off, a.data(), 0, nullptr));
+      }
+      m.src = c, m.dst = a;
+      m.apply(p, &want);
+      if ((mockhip::value_waits() != values) != number) die("waits for a number", flags, how);
+      mockhip::set_policy(mockhip::kStarve0, p.st[0]);  // the load goes first where nothing holds it back
+      OK(kv_sync(p.h));
+      if (p.bytes() != want) die("a load has not waited for a move", flags, how);
+      if (mockhip::capture_errors()) die("calls that a capture does not allow", mockhip::capture_errors(), how);
+      mockhip::set_policy(mockhip::kRandom, nullptr);
+    }
 }
 
 // A wait for one call that finishes by number ends with that call, whatever its stream has been given since: here the rest of the stream is
@@ -472,9 +524,8 @@ void no_end_events() {
     if (kv_req_poll(p.h, id) != 0) die("a request is complete before anything has run", flags);
     OK(kv_move_blocks_noalloc(p.h, 3, a.data(), c.data(), nullptr));
     moved(a, c);
-    if (p.h->na_recorded) die("an allocation-free move has recorded its event", flags);
+    if (!p.h->na_done) die("an allocation-free move has no number", flags);
     OK(kv_swap_out(p.h, 1, &id2, off, c.data(), &tok, nullptr));
-    if (!p.h->na_recorded) die("the call behind an allocation-free move has not recorded its event", flags);
     OK(kv_swap_in(p.h, 1, &id2, off, d.data(), 0, nullptr));
     moved(c, d);
     kv_stats st{};
@@ -579,7 +630,7 @@ int main(int argc, char** argv) {
   const struct {
     const char* name;
     void (*run)();
-  } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
+  } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"capture_behind_a_move", capture_behind_a_move}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
                 {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up},
                 {"no_end_events", no_end_events}, {"waits_for_numbers", waits_for_numbers}};
   for (const auto& s : sections)

@@ -154,6 +154,49 @@ def test_noalloc_move_inside_a_graph(gpu, n):
     kp.close()
 
 
+@pytest.mark.parametrize("mib", [1, 40], ids=["by_number", "by_event"])
+@pytest.mark.parametrize("arena", ["device", "host"])
+def test_noalloc_moves_across_the_streams(gpu, arena, mib):
+    """Allocation-free moves, those that store a number and longer ones with an event, between transfers of the other stream that need what
+    they move, and with another move captured in between, nothing waited for."""
+    import torch
+    g = W.Geometry(8, 4, 128, 16, "bf16", 18 * mib)         # 256 KiB blocks
+    n = 4 * mib
+    a, b, c, d = (np.arange(k * n, (k + 1) * n, dtype=np.int32) for k in range(4))
+    off, tok = [0, n], [n * g.B]
+    pool = torch.randint(-2**62, 2**62, (g.pool_bytes // 8,), dtype=torch.int64, device=gpu, generator=torch.Generator(device=gpu).manual_seed(mib)).view(torch.uint8)
+    size = 2 * n * g.S
+    slots = torch.zeros(size, dtype=torch.uint8, device=gpu) if arena == "device" else torch.zeros(size, dtype=torch.uint8).pin_memory()
+    blocks = pool.view(2 * g.L, g.N, -1)
+    want = blocks.clone()
+    evict, load = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    kp = kv.KVPool(g, pool, slots, evict_stream=evict, load_stream=load, flags=kv.KV_STAGING_DEVICE if arena == "device" else kv.KV_PATH_ZEROCOPY)
+
+    def moved(src, dst):
+        want[:, torch.as_tensor(dst.astype(np.int64))] = want[:, torch.as_tensor(src.astype(np.int64))]
+    for turn in range(4):
+        assert kp.swap_out([turn], off, a, tok) == kv.KV_OK
+        assert kp.move_blocks_noalloc(b, c) == kv.KV_OK
+        assert kp.swap_in([turn], off, b) == kv.KV_OK          # over what the move reads
+        assert kp.move_blocks_noalloc(b, d) == kv.KV_OK        # what the load writes
+        if turn == 2:
+            graph, fork, join = torch.cuda.CUDAGraph(), torch.cuda.Event(), torch.cuda.Event()
+            with torch.cuda.graph(graph, capture_error_mode="relaxed"):
+                here = torch.cuda.current_stream()
+                fork.record(here)
+                assert kp.move_blocks_noalloc(a, b, wait_event=fork.cuda_event) == kv.KV_OK
+                join.record(evict)
+                here.wait_event(join)
+        assert kp.swap_out([100], off, c, tok) == kv.KV_OK
+        assert kp.swap_in([100], off, a) == kv.KV_OK
+        for src, dst in ((b, c), (a, b), (b, d), (c, a)):
+            moved(src, dst)
+    assert kp.sync() == kv.KV_OK
+    assert torch.equal(blocks, want)
+    kp.close()
+
+
 @pytest.mark.parametrize("arena", ["device", "host"])
 @pytest.mark.parametrize("kind,mode", [("move", "global"), ("out", "global"), ("in", "relaxed"), ("both", "relaxed")],
                          ids=["move", "out", "in", "both"])
