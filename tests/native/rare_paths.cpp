@@ -146,15 +146,15 @@ struct Captured {
 
 // Calls that keep a record go into a graph as well, and the handle goes on behind them: what is captured runs with each replay and not
 // before, and eager calls on both streams, polls, waits and telemetry work as ever.  `front`: in front of it nothing, an allocation-free move
-// that stores a number, one with an event; the program itself has waited for that move, and the handle has not looked.  (A swap-in that is captured asks for the swap-out in front
+// that stores a number, one with an event, a swap-out; the program itself has waited for that, and the handle has not looked.  (A swap-in that is captured asks for the swap-out in front
 // of it, which only the relaxed mode allows.)
 void captured_calls() {
   const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12}, e{13, 14, 15};
   const int32_t off[2] = {0, 3}, tok = 3;
-  const uint64_t id1 = 1, id2 = 2, id4 = 4, id7 = 7;
+  const uint64_t id1 = 1, id2 = 2, id4 = 4, id7 = 7, id8 = 8;
   const std::vector<int32_t> f{20, 21, 22}, h{23, 24, 25};
   for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY})
-    for (int front = 0; front < 3; front++)
+    for (int front = 0; front < 4; front++)
       for (int kind = 0; kind < 4; kind++) {  // a move a to d, a swap-out of a, a swap-in to d of what has been swapped out of c, both
         Pool p(40, 16, flags);
         std::mt19937_64 rng(4);
@@ -169,7 +169,10 @@ void captured_calls() {
           OK(kv_swap_out(p.h, 1, &id4, off, b.data(), &tok, nullptr));
           OK(kv_sync(p.h));
         }
-        if (front) {
+        if (front == 3) {
+          OK(kv_swap_out(p.h, 1, &id8, off, f.data(), &tok, nullptr));
+          (void)hipStreamSynchronize(p.st[0]);
+        } else if (front) {
           p.h->by_number = front == 1;
           OK(kv_move_blocks_noalloc(p.h, 3, f.data(), h.data(), nullptr));
           p.h->by_number = true;
