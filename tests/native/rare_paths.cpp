@@ -146,8 +146,8 @@ struct Captured {
 
 // Calls that keep a record go into a graph as well, and the handle goes on behind them: what is captured runs with each replay and not
 // before, and eager calls on both streams, polls, waits and telemetry work as ever.  `front`: in front of it nothing, an allocation-free move
-// that stores a number, one with an event, a swap-out; the program itself has waited for that, and the handle has not looked.  (A swap-in that is captured asks for the swap-out in front
-// of it, which only the relaxed mode allows.)
+// that stores a number, one with an event, a swap-out; the program itself has waited for that, and the handle has not looked.
+// (A swap-in that is captured asks for the swap-out in front of it, which only the relaxed mode allows.)
 void captured_calls() {
   const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9}, d{10, 11, 12}, e{13, 14, 15};
   const int32_t off[2] = {0, 3}, tok = 3;
@@ -224,161 +224,192 @@ void captured_calls() {
       }
 }
 
-  // kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
-  // plane by plane from 60 MiB on).
-  void scatter_order() {
-    const int n = 976, N = 1000;
-    Pool p(N, n, KV_STAGING_DEVICE, 16384);
-    const uint64_t id = 3;
-    const int32_t off[2] = {0, n}, tok = n;
-    std::vector<int32_t> ids(n);
-    for (int i = 0; i < n; i++) ids[(size_t)i] = i * 17 % N;
-    const std::vector<char> want = p.bytes();
-    for (bool collide : {false, true})
-      for (int knob = 0; knob < 3; knob++) {
-        p.h->planes_collide = collide;
-        OK(kv_pool_tune(p.h, KV_TUNE_SCATTER_ORDER, knob));
-        kv_stats st{};
-        st.struct_size = sizeof(st);
-        OK(kv_swap_out(p.h, 1, &id, off, ids.data(), &tok, nullptr));
-        OK(kv_last_stats(p.h, &st));
-        if (st.scatter_order != -1) die("order of a gather", st.scatter_order, knob);
-        for (int i = 0; i < n; i++) std::memset(p.pool + ids[(size_t)i] * p.chunk, 0, (size_t)p.chunk);
-        OK(kv_swap_in(p.h, 1, &id, off, ids.data(), 0, nullptr));
-        OK(kv_last_stats(p.h, &st));
-        if (st.scatter_order != (knob == 2 || (collide && knob == 0) ? 1 : -1)) die("order of a scatter, knob", st.scatter_order, knob);
-        if (p.bytes() != want) die("bytes of a swap, knob", collide, knob);
-      }
-}
-
-  // kv_stats.ms_kernel of an exchange is its kernels alone, without what the load has waited for, also where a launch does not
-  // time itself (a workgroup cap: kv_move_kernel).
-  void exchange_times() {
-    for (int cap : {0, 4}) {
-      const int n = 8;
-      Pool p(40, 2 * n);
-      OK(kv_pool_tune(p.h, KV_TUNE_MAX_WGS_DEVICE, cap));
-      const uint64_t out = 1, in = 2;
-      const int32_t off[2] = {0, n}, tok = n;
-      int32_t a[n], b[n];
-      for (int i = 0; i < n; i++) a[i] = i, b[i] = 20 + i;
-      OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
-      OK(kv_sync(p.h));
-      mockhip::set_policy(mockhip::kLazy, nullptr);  // nothing runs before the host waits: the load waits for the eviction
-      OK(kv_evict_and_load(p.h, 1, &out, off, a, &tok, 1, &in, off, a, 0, nullptr));
+// kv_stats.scatter_order says how a scatter went, also where a pool whose planes collide decides it (61 MiB: such a scatter goes
+// plane by plane from 60 MiB on).
+void scatter_order() {
+  const int n = 976, N = 1000;
+  Pool p(N, n, KV_STAGING_DEVICE, 16384);
+  const uint64_t id = 3;
+  const int32_t off[2] = {0, n}, tok = n;
+  std::vector<int32_t> ids(n);
+  for (int i = 0; i < n; i++) ids[(size_t)i] = i * 17 % N;
+  const std::vector<char> want = p.bytes();
+  for (bool collide : {false, true})
+    for (int knob = 0; knob < 3; knob++) {
+      p.h->planes_collide = collide;
+      OK(kv_pool_tune(p.h, KV_TUNE_SCATTER_ORDER, knob));
       kv_stats st{};
       st.struct_size = sizeof(st);
+      OK(kv_swap_out(p.h, 1, &id, off, ids.data(), &tok, nullptr));
       OK(kv_last_stats(p.h, &st));
-      if (st.op != 3 || st.launches != 1 || !(st.ms_kernel > 0)) die("statistics of an exchange's load", st.op, st.launches);
-      if (cap ? st.ms_kernel >= st.ms_total : st.ms_kernel != st.ms_total) die("ms_kernel of an exchange's load, cap", cap, (long)(st.ms_kernel * 1e6));
+      if (st.scatter_order != -1) die("order of a gather", st.scatter_order, knob);
+      for (int i = 0; i < n; i++) std::memset(p.pool + ids[(size_t)i] * p.chunk, 0, (size_t)p.chunk);
+      OK(kv_swap_in(p.h, 1, &id, off, ids.data(), 0, nullptr));
+      OK(kv_last_stats(p.h, &st));
+      if (st.scatter_order != (knob == 2 || (collide && knob == 0) ? 1 : -1)) die("order of a scatter, knob", st.scatter_order, knob);
+      if (p.bytes() != want) die("bytes of a swap, knob", collide, knob);
+    }
+}
+
+// kv_stats.ms_kernel of an exchange is its kernels alone, without what the load has waited for, also where a launch does not
+// time itself (a workgroup cap: kv_move_kernel).
+void exchange_times() {
+  for (int cap : {0, 4}) {
+    const int n = 8;
+    Pool p(40, 2 * n);
+    OK(kv_pool_tune(p.h, KV_TUNE_MAX_WGS_DEVICE, cap));
+    const uint64_t out = 1, in = 2;
+    const int32_t off[2] = {0, n}, tok = n;
+    int32_t a[n], b[n];
+    for (int i = 0; i < n; i++) a[i] = i, b[i] = 20 + i;
+    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+    OK(kv_sync(p.h));
+    mockhip::set_policy(mockhip::kLazy, nullptr);  // nothing runs before the host waits: the load waits for the eviction
+    OK(kv_evict_and_load(p.h, 1, &out, off, a, &tok, 1, &in, off, a, 0, nullptr));
+    kv_stats st{};
+    st.struct_size = sizeof(st);
+    OK(kv_last_stats(p.h, &st));
+    if (st.op != 3 || st.launches != 1 || !(st.ms_kernel > 0)) die("statistics of an exchange's load", st.op, st.launches);
+    if (cap ? st.ms_kernel >= st.ms_total : st.ms_kernel != st.ms_total) die("ms_kernel of an exchange's load, cap", cap, (long)(st.ms_kernel * 1e6));
+    mockhip::set_policy(mockhip::kRandom, nullptr);
+  }
+}
+
+// Allocation-free moves in a row while the evict stream is held back: from the upload buffers as long as one is free, then (none
+// is free before the stream runs) inside the arguments of the move or of fill launches.
+void uploads() {
+  std::mt19937_64 rng(2);
+  for (int64_t N : {2003, 66000})  // four buffers, and two
+    for (size_t n : {60, 61, 448, 449, 897, 1000}) {
+      Pool p(N);
+      std::vector<char> want = p.bytes();
+      mockhip::set_policy(mockhip::kLazy, nullptr);
+      for (int turn = 0; turn < 2; turn++) {
+        for (int k = 0; k < 7; k++) {
+          const Moves m(rng, N, n - (size_t)(k % 3));  // lists that leave the end of an earlier, longer one behind theirs
+          OK(m.run(p));
+          m.apply(p, &want);
+        }
+        OK(kv_sync(p.h));
+        if (p.bytes() != want) die("bytes of moves in a row: n, turn", (long)n, turn);
+      }
       mockhip::set_policy(mockhip::kRandom, nullptr);
     }
 }
 
-  // Allocation-free moves in a row while the evict stream is held back: from the upload buffers as long as one is free, then (none
-  // is free before the stream runs) inside the arguments of the move or of fill launches.
-  void uploads() {
-    std::mt19937_64 rng(2);
-    for (int64_t N : {2003, 66000})  // four buffers, and two
-      for (size_t n : {60, 61, 448, 449, 897, 1000}) {
-        Pool p(N);
-        std::vector<char> want = p.bytes();
-        mockhip::set_policy(mockhip::kLazy, nullptr);
-        for (int turn = 0; turn < 2; turn++) {
-          for (int k = 0; k < 7; k++) {
-            const Moves m(rng, N, n - (size_t)(k % 3));  // lists that leave the end of an earlier, longer one behind theirs
-            OK(m.run(p));
-            m.apply(p, &want);
-          }
-          OK(kv_sync(p.h));
-          if (p.bytes() != want) die("bytes of moves in a row: n, turn", (long)n, turn);
-        }
-        mockhip::set_policy(mockhip::kRandom, nullptr);
-      }
-}
-
-  // One swap out and in, and one exchange, on a handle; returns the waits for a number that were made.
-  long swap_and_exchange(Pool& p) {
-    const int n = 4;
-    const uint64_t id = 3, in = 8;
-    const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
-    mockhip::set_policy(mockhip::kLazy, nullptr);
-    const long before = mockhip::value_waits();
-    std::vector<char> want = p.bytes();
-    auto move = [&](const int32_t* from, const int32_t* to) {
-      const std::vector<char> was = want;
-      for (int i = 0; i < n; i++)
-        for (int64_t k = 0; k < Pool::planes; k++)
-          std::memcpy(want.data() + (k * p.N + to[i]) * p.chunk, was.data() + (k * p.N + from[i]) * p.chunk, (size_t)p.chunk);
-    };
-    kv_stats st{};
-    st.struct_size = sizeof(st);
-    OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
-    OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
-    move(a, b);
-    OK(kv_last_stats(p.h, &st));
-    if (!(st.ms_total > 0)) die("no time of a load");
-    OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
-    OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
-    move(b, a);
-    OK(kv_last_stats(p.h, &st));
-    if (!(st.ms_total > 0) || !(st.ms_kernel > 0)) die("no time of an exchange");
-    OK(kv_req_release(p.h, id));
-    OK(kv_sync(p.h));
-    if (p.bytes() != want) die("bytes of a swap and an exchange");
-    mockhip::set_policy(mockhip::kRandom, nullptr);
-    return mockhip::value_waits() - before;
-}
-
-  // Handles behind the first 128, which have no counters for launches with both ends in HBM, and behind the first 1024, whose job
-  // counters of the link are an allocation of their own.
-  void counters_used_up() {
-    for (int others : {0, kLeaveSlots, kTicketSlots})
-      for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
-        for (int s = 0; s < others; s++) g_ticket_taken[0][s >> 6] |= 1ull << (s & 63);  // as if that many handles were there
-        {
-          Pool p(9, 16, flags);
-          const bool device = flags & KV_STAGING_DEVICE;
-          if (p.h->ticket_slot != (others < kTicketSlots ? others : -1)) die("slot of a handle", p.h->ticket_slot, others);
-          for (int turn = 0; turn < 3; turn++) {
-            const long waits = swap_and_exchange(p);
-            if (!waits != (device && others)) die("waits for a number: others, waits", others, waits);
-          }
-        }
-        std::memset(g_ticket_taken[0], 0, sizeof(g_ticket_taken[0]));
-      }
-}
-
-  // More calls in flight than there are records of the clock: the others have start events.
-  void records_used_up() {
-    Pool p(9);
-    const uint64_t id = 3;
-    const int32_t off[2] = {0, 2}, tok = 2, a[2] = {1, 2}, b[2] = {5, 6};
-    const std::vector<char> before = p.bytes();
-    mockhip::set_policy(mockhip::kLazy, nullptr);
-    const int pairs = kStamps / 2 + 40;
-    for (int i = 0; i < pairs; i++) {
-      OK(kv_swap_out(p.h, 1, &id, off, i % 2 ? b : a, &tok, nullptr));
-      OK(kv_swap_in(p.h, 1, &id, off, i % 2 ? a : b, 0, nullptr));
-    }
-    if (!p.h->stamp_free.empty() || p.h->calls.back().stamp || !p.h->calls.back().start) die("records left", (long)p.h->stamp_free.size());
-    kv_stats st{};
-    st.struct_size = sizeof(st);
-    OK(kv_last_stats(p.h, &st));
-    if (!(st.ms_total > 0)) die("no time of a call without a record");
-    OK(kv_sync(p.h));
-    std::vector<char> want = before;
-    for (int i = 0; i < 2; i++)
+// One swap out and in, and one exchange, on a handle; returns the waits for a number that were made.
+long swap_and_exchange(Pool& p) {
+  const int n = 4;
+  const uint64_t id = 3, in = 8;
+  const int32_t off[2] = {0, n}, tok = n, a[n] = {1, 2, 3, 4}, b[n] = {4, 5, 6, 7};
+  mockhip::set_policy(mockhip::kLazy, nullptr);
+  const long before = mockhip::value_waits();
+  std::vector<char> want = p.bytes();
+  auto move = [&](const int32_t* from, const int32_t* to) {
+    const std::vector<char> was = want;
+    for (int i = 0; i < n; i++)
       for (int64_t k = 0; k < Pool::planes; k++)
-        std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, before.data() + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
-    if (p.bytes() != want) die("bytes of calls in flight");
-    mockhip::set_policy(mockhip::kRandom, nullptr);
-    swap_and_exchange(p);
-    kv_io_stats io{};
-    io.struct_size = sizeof(io);
-    OK(kv_io_stats_get(p.h, &io));
-    if (io.total_calls[0] + io.total_calls[1] < 2 * pairs || !(io.ewma_small_us[0] > 0 && io.ewma_small_us[1] > 0)) die("telemetry", io.total_calls[0], io.total_calls[1]);
-    if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
+        std::memcpy(want.data() + (k * p.N + to[i]) * p.chunk, was.data() + (k * p.N + from[i]) * p.chunk, (size_t)p.chunk);
+  };
+  kv_stats st{};
+  st.struct_size = sizeof(st);
+  OK(kv_swap_out(p.h, 1, &id, off, a, &tok, nullptr));
+  OK(kv_swap_in(p.h, 1, &id, off, b, 0, nullptr));
+  move(a, b);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0)) die("no time of a load");
+  OK(kv_swap_out(p.h, 1, &in, off, b, &tok, nullptr));
+  OK(kv_evict_and_load(p.h, 1, &id, off, a, &tok, 1, &in, off, a, 0, nullptr));
+  move(b, a);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0) || !(st.ms_kernel > 0)) die("no time of an exchange");
+  OK(kv_req_release(p.h, id));
+  OK(kv_sync(p.h));
+  if (p.bytes() != want) die("bytes of a swap and an exchange");
+  mockhip::set_policy(mockhip::kRandom, nullptr);
+  return mockhip::value_waits() - before;
+}
+
+// Handles behind the first 128, which have no counters for launches with both ends in HBM, and behind the first 1024, whose job
+// counters of the link are an allocation of their own.
+void counters_used_up() {
+  for (int others : {0, kLeaveSlots, kTicketSlots})
+    for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
+      for (int s = 0; s < others; s++) g_ticket_taken[0][s >> 6] |= 1ull << (s & 63);  // as if that many handles were there
+      {
+        Pool p(9, 16, flags);
+        const bool device = flags & KV_STAGING_DEVICE;
+        if (p.h->ticket_slot != (others < kTicketSlots ? others : -1)) die("slot of a handle", p.h->ticket_slot, others);
+        for (int turn = 0; turn < 3; turn++) {
+          const long waits = swap_and_exchange(p);
+          if (!waits != (device && others)) die("waits for a number: others, waits", others, waits);
+        }
+      }
+      std::memset(g_ticket_taken[0], 0, sizeof(g_ticket_taken[0]));
+    }
+}
+
+// More calls in flight than there are records of the clock: the others have start events.
+void records_used_up() {
+  Pool p(9);
+  const uint64_t id = 3;
+  const int32_t off[2] = {0, 2}, tok = 2, a[2] = {1, 2}, b[2] = {5, 6};
+  const std::vector<char> before = p.bytes();
+  mockhip::set_policy(mockhip::kLazy, nullptr);
+  const int pairs = kStamps / 2 + 40;
+  for (int i = 0; i < pairs; i++) {
+    OK(kv_swap_out(p.h, 1, &id, off, i % 2 ? b : a, &tok, nullptr));
+    OK(kv_swap_in(p.h, 1, &id, off, i % 2 ? a : b, 0, nullptr));
+  }
+  if (!p.h->stamp_free.empty() || p.h->calls.back().stamp || !p.h->calls.back().start) die("records left", (long)p.h->stamp_free.size());
+  kv_stats st{};
+  st.struct_size = sizeof(st);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0)) die("no time of a call without a record");
+  OK(kv_sync(p.h));
+  std::vector<char> want = before;
+  for (int i = 0; i < 2; i++)
+    for (int64_t k = 0; k < Pool::planes; k++)
+      std::memcpy(want.data() + (k * p.N + b[i]) * p.chunk, before.data() + (k * p.N + a[i]) * p.chunk, (size_t)p.chunk);
+  if (p.bytes() != want) die("bytes of calls in flight");
+  mockhip::set_policy(mockhip::kRandom, nullptr);
+  swap_and_exchange(p);
+  kv_io_stats io{};
+  io.struct_size = sizeof(io);
+  OK(kv_io_stats_get(p.h, &io));
+  if (io.total_calls[0] + io.total_calls[1] < 2 * pairs || !(io.ewma_small_us[0] > 0 && io.ewma_small_us[1] > 0)) die("telemetry", io.total_calls[0], io.total_calls[1]);
+  if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
+}
+
+// The clock at the end of a call may arrive behind the call's number: its record is not handed to another call before, and what is reported
+// is what has arrived.
+void late_clock() {
+  Pool p(40);
+  const int32_t a[2] = {1, 2}, b[2] = {5, 6}, c[2] = {9, 10};
+  mockhip::set_policy(mockhip::kLazy, nullptr);
+  OK(kv_move_blocks(p.h, 2, a, b, nullptr));
+  (void)hipStreamSynchronize(p.st[0]);
+  uint64_t* record = p.h->calls.back().stamp;
+  const uint64_t end = __atomic_exchange_n(record + 1, 0, __ATOMIC_ACQ_REL);  // as if it were still on its way
+  if (!end || p.h->calls.back().end) die("a move that times itself");
+  std::atomic<bool> arrived{false};
+  std::thread device([&] {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+    while (std::chrono::steady_clock::now() < until) {}
+    arrived = true;
+    __atomic_store_n(record + 1, end, __ATOMIC_RELEASE);
+  });
+  OK(kv_move_blocks(p.h, 2, b, c, nullptr));
+  OK(kv_move_blocks(p.h, 2, c, a, nullptr));  // the first one's call goes
+  if (p.h->calls.back().stamp == record && !arrived) die("a record that the device still stores to");
+  device.join();
+  if (!p.h->call_by_seq.count(3) || p.h->call_by_seq.count(1)) die("the calls of the handle");
+  OK(kv_sync(p.h));
+  kv_stats st{};
+  st.struct_size = sizeof(st);
+  OK(kv_last_stats(p.h, &st));
+  if (!(st.ms_total > 0 && st.ms_total < 1000)) die("time of a move");
+  mockhip::set_policy(mockhip::kRandom, nullptr);
 }
 
 // An allocation-free move that is still under way when its stream is drawn into a capture: calls of the load stream come behind it all the
@@ -634,7 +665,7 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"capture_behind_a_move", capture_behind_a_move}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
-                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up},
+                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up}, {"late_clock", late_clock},
                 {"no_end_events", no_end_events}, {"waits_for_numbers", waits_for_numbers}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {

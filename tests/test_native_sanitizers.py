@@ -153,8 +153,9 @@ def rare_paths(tmp_path_factory):
     return _build_rare_paths(str(tmp_path_factory.mktemp("rare") / "rare_paths"), CSRC, SAN)
 
 
-@pytest.mark.parametrize("section", ["capture", "captured_calls", "capture_behind_a_move", "scatter_order", "exchange_times", "uploads", "counters_used_up", "records_used_up",
-                                     "late_profiler", "late_events", "no_end_events", "waits_for_numbers"])
+@pytest.mark.parametrize("section", ["capture", "captured_calls", "capture_behind_a_move", "scatter_order", "exchange_times", "uploads",
+                                     "counters_used_up", "records_used_up", "late_clock", "late_profiler", "late_events", "no_end_events",
+                                     "waits_for_numbers"])
 def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""
     r = _run_rare_path(rare_paths, section, tmp_path)
@@ -167,7 +168,7 @@ RARE_MUTANTS = [
     ("upload_buffer_taken_while_it_is_read", "uploads",
      "        if (query_relaxed([&] { return hipEventQuery(p->na_up_ev[k]); })) up = k;", "        up = k;"),
     ("fill_launches_of_the_first_batch", "uploads", "std::memcpy(pack.d, list.data() + at,", "std::memcpy(pack.d, list.data(),"),
-    ("clock_record_not_given_back", "records_used_up", "  if (c.stamp) p->stamp_free.push_back(c.stamp);\n", ""),
+    ("clock_record_not_given_back", "records_used_up", "  if (c.stamp && (!c.done || end_clock(c))) p->stamp_free.push_back(c.stamp);\n", ""),
     ("load_does_not_wait_for_the_event_of_a_move", "capture_behind_a_move", "        HIPCHK(p, hipStreamWaitEvent(st, p->na_done_ev[k], 0));", ""),
     ("tool_that_comes_late_not_seen", "late_profiler", "    if (p->done_word[0]) look_for_profiler(p);\n", ""),
 ]
