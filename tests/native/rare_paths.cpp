@@ -381,6 +381,50 @@ void records_used_up() {
   if (!p.h->calls.back().stamp || p.h->stamp_free.size() + p.h->calls.size() < (size_t)kStamps) die("records not given back", (long)p.h->stamp_free.size());
 }
 
+// A load drawn into a capture by what it waits for, a captured move of the blocks that it writes: it goes into the graph behind that, with
+// nothing of the handle's that a replay would store to.
+void drawn_into_a_capture() {
+  const std::vector<int32_t> a{1, 2, 3}, b{4, 5, 6}, c{7, 8, 9};
+  const int32_t off[2] = {0, 3}, tok = 3;
+  const uint64_t id = 3;
+  for (uint32_t flags : {(uint32_t)KV_STAGING_DEVICE, (uint32_t)KV_PATH_ZEROCOPY}) {
+    Pool p(40, 16, flags);
+    std::vector<char> want = p.bytes();
+    std::mt19937_64 rng(8);
+    Moves m(rng, p.N, 1);
+    auto moved = [&](const std::vector<int32_t>& src, const std::vector<int32_t>& dst) {
+      m.src = src, m.dst = dst;
+      m.apply(p, &want);
+    };
+    OK(kv_swap_out(p.h, 1, &id, off, c.data(), &tok, nullptr));
+    OK(kv_sync(p.h));
+    const size_t records = p.h->stamp_free.size() + 1;  // (the newest call keeps its own)
+    Captured cap(true);
+    OK(kv_move_blocks(p.h, 3, a.data(), b.data(), cap.fork));
+    OK(kv_swap_in(p.h, 1, &id, off, a.data(), KV_KEEP_STAGING, nullptr));
+    hipStreamCaptureStatus on;
+    (void)hipStreamIsCapturing(p.st[1], &on);
+    if (on != hipStreamCaptureStatusActive) die("the load stream is not in the capture", flags);
+    if (p.h->calls.back().stamp || p.h->calls.back().done || !p.h->calls.back().start) die("a captured load has a clock record or a number", flags);
+    const mockhip::Graph g = cap.end({p.st[0], p.st[1]});
+    for (int turn = 0; turn < 3; turn++) {
+      OK(kv_move_blocks(p.h, 3, b.data(), c.data(), nullptr));
+      moved(b, c);
+      OK(kv_sync(p.h));
+      const uint64_t *record = p.h->calls.back().stamp, was[2] = {record[0], record[1]};
+      std::vector<char> slots(p.arena, p.arena + 3 * Pool::planes * p.chunk);
+      cap.replay(g);
+      moved(a, b);
+      for (int i = 0; i < 3; i++)
+        for (int64_t k = 0; k < Pool::planes; k++)
+          std::memcpy(want.data() + (k * p.N + a[(size_t)i]) * p.chunk, slots.data() + (i * Pool::planes + k) * p.chunk, (size_t)p.chunk);
+      if (p.bytes() != want) die("bytes of a replay, turn", turn, flags);
+      if (record[0] != was[0] || record[1] != was[1]) die("a replay has stored to a record, turn", turn, flags);
+    }
+    if (p.h->stamp_free.size() + 1 != records) die("records", (long)p.h->stamp_free.size(), (long)records);
+  }
+}
+
 // The clock at the end of a call may arrive behind the call's number: its record is not handed to another call before, and what is reported
 // is what has arrived.
 void late_clock() {
@@ -665,7 +709,7 @@ int main(int argc, char** argv) {
     const char* name;
     void (*run)();
   } sections[] = {{"capture", capture}, {"captured_calls", captured_calls}, {"capture_behind_a_move", capture_behind_a_move}, {"scatter_order", scatter_order}, {"exchange_times", exchange_times}, {"uploads", uploads},
-                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up}, {"late_clock", late_clock},
+                {"counters_used_up", counters_used_up}, {"records_used_up", records_used_up}, {"late_clock", late_clock}, {"drawn_into_a_capture", drawn_into_a_capture},
                 {"no_end_events", no_end_events}, {"waits_for_numbers", waits_for_numbers}};
   for (const auto& s : sections)
     if (argc == 2 && !std::strcmp(argv[1], s.name)) {

@@ -155,7 +155,7 @@ def rare_paths(tmp_path_factory):
 
 @pytest.mark.parametrize("section", ["capture", "captured_calls", "capture_behind_a_move", "scatter_order", "exchange_times", "uploads",
                                      "counters_used_up", "records_used_up", "late_clock", "late_profiler", "late_events", "no_end_events",
-                                     "waits_for_numbers"])
+                                     "drawn_into_a_capture", "waits_for_numbers"])
 def test_paths_that_no_history_takes(rare_paths, section, tmp_path):
     """See tests/native/rare_paths.cpp, which says at each section what it runs."""
     r = _run_rare_path(rare_paths, section, tmp_path)
