@@ -69,6 +69,10 @@
  *     and kv_sync / kv_req_wait.
  *   - wait_event (nullable) is a hipEvent_t; the call's stream waits for it
  *     before touching the pool (ordering after the caller's compute stream).
+ *   - A call whose stream is being captured into a HIP graph (it joins through wait_event, or the caller
+ *     captures a stream that it gave) runs with each replay; the handle's own state changes once, when the
+ *     call is made.  Calls may ask for earlier ones that are in flight, which only a capture in the relaxed mode
+ *     allows, and up to 60 blocks travel inside the graph: kv_move_blocks_noalloc takes any list in any mode.
  *   - Argument arrays are HOST pointers, read during the call, free on return.
  *   - pool_dev, scale_dev, bounce_dev are DEVICE pointers; staging_host is a
  *     pinned, device-mapped HOST pointer (hipHostMalloc / torch pin_memory),
@@ -320,7 +324,8 @@ int64_t kv_last_plan(kv_pool* p, int32_t* phys, int64_t* slot, int64_t cap);
  * kv_req_poll: 1 when no transfer of this request is in flight (or none was ever enqueued), 0 while
  * its last enqueued segment is unfinished.  kv_req_wait blocks until then; it does not hold the
  * handle's lock while it blocks, so another thread may go on enqueuing calls meanwhile (kv_sync does
- * hold it: it is the call that stops everything).  Without KV_REQ_EVENTS both answer for the whole
+ * hold it: it is the call that stops everything).  It waits for that call only, not for what the
+ * stream has been given since.  Without KV_REQ_EVENTS both answer for the whole
  * call the request was part of. */
 int kv_req_poll(kv_pool* p, uint64_t req_id);
 int kv_req_wait(kv_pool* p, uint64_t req_id);
