@@ -254,6 +254,76 @@ def test_calls_in_a_row_without_end_events(gpu, geom, n, arena):
     gpu_lib.close()
 
 
+@pytest.mark.parametrize("arena", ["device", "host"])
+def test_a_wait_ends_with_its_call(gpu, arena):
+    """kv_req_wait and kv_last_stats of a call that finishes by number, with 60 ms of other work behind it on the same stream."""
+    import torch
+    g = W.Geometry(4, 4, 64, 16, "f16", 60)
+    a, b = HostPool(g, 0xB40, "layer", slots=40), HostPool(g, 0xB40, "layer", slots=40)
+    pool = torch.from_numpy(b.pool).to(gpu)
+    slots = torch.zeros(40 * g.S, dtype=torch.uint8, device=gpu) if arena == "device" else torch.zeros(40 * g.S, dtype=torch.uint8).pin_memory()
+    evict, load = torch.cuda.Stream(), torch.cuda.Stream()
+    big = torch.zeros(2 << 30, dtype=torch.uint8, device=gpu)
+    torch.cuda.synchronize()
+    kp = kv.KVPool(g, pool, slots, evict_stream=evict, load_stream=load, flags=kv.KV_STAGING_DEVICE if arena == "device" else kv.KV_PATH_ZEROCOPY)
+    ids = np.arange(60, dtype=np.int32)
+    x, y, z = ids[:20], ids[20:40], ids[40:]
+    off, tok = [0, 20], [20 * g.B]
+    behind = torch.cuda.Event()
+    for turn in range(4):
+        assert kp.move_blocks(x, y) == kv.KV_OK and kp.swap_out([turn], off, y, tok) == kv.KV_OK
+        with torch.cuda.stream(evict):
+            for _ in range(80):
+                big[:1 << 30].copy_(big[1 << 30:])
+            behind.record()
+        if turn % 2:
+            assert kp.req_wait(turn) == kv.KV_OK
+        else:
+            st = kp.stats()
+            assert st["op"] == 1 and 0 < st["ms_total"] < 20
+        assert not behind.query(), "the wait has waited for what is behind its call"
+        assert kp.req_poll(turn) == 1 and kp.io_stats()["inflight_calls"] == [0, 0]
+        assert kp.swap_in([turn], off, z) == kv.KV_OK and kp.req_wait(turn) == kv.KV_OK
+        assert kp.sync() == kv.KV_OK
+        want = a.pool.reshape(2 * g.L, g.N, -1)
+        want[:, y] = want[:, x]
+        want[:, z] = want[:, x]
+        assert np.array_equal(pool.cpu().numpy(), a.pool.reshape(-1).view(np.uint8))
+        pool.view(2 * g.L, g.N, -1)[:, :20] += 1
+        a.pool.reshape(2 * g.L, g.N, -1).view(np.uint8)[:, :20] += 1
+        torch.cuda.synchronize()
+    kp.close()
+
+
+@pytest.mark.parametrize("geom,n", [((4, 4, 64, 16, "f16"), 27), ((1, 1, 72, 1, "bf16"), 57), ((2, 4, 64, 16, "fp8_e4m3"), 40), ((32, 8, 128, 16, "bf16"), 12)],
+                         ids=["8KiB", "144B", "fp8", "24MiB"])
+def test_the_host_reads_what_a_wait_says_is_there(gpu, geom, n):
+    """The host arena is complete when a wait or a poll by number says so, over each build of the link kernel's gather."""
+    import torch
+    g = W.Geometry(*geom, 2 * n, scales=geom[4] == "fp8_e4m3")
+    pool = torch.zeros(g.pool_bytes, dtype=torch.uint8, device=gpu)
+    scale = torch.zeros(g.scale_bytes, dtype=torch.uint8, device=gpu) if g.scales else None
+    slots = torch.zeros(n * g.S, dtype=torch.uint8).pin_memory()
+    kp = kv.KVPool(g, pool, slots, scale=scale)
+    ids, off, tok = np.arange(2 * n, dtype=np.int32), [0, n], [n * g.B]
+    seen = slots.numpy()
+    for turn in range(1, 60 if n * g.S > 1 << 20 else 250):
+        for t in (pool, scale):
+            if t is not None:
+                t.fill_(turn)
+        torch.cuda.synchronize()
+        assert kp.move_blocks(ids[:1], ids[-1:]) == kv.KV_OK      # (the swap-out behind a call in flight has no end event)
+        assert kp.swap_out([turn], off, ids[:n], tok) == kv.KV_OK
+        if turn % 2:
+            assert kp.req_wait(turn) == kv.KV_OK
+        else:
+            while not kp.req_poll(turn):
+                pass
+        assert (seen == turn).all(), turn
+        assert kp.swap_in([turn], off, ids[n:]) == kv.KV_OK and kp.sync() == kv.KV_OK
+    kp.close()
+
+
 @pytest.mark.parametrize("geom,n", [((24, 4, 72, 16, "f16"), 701), ((20, 1, 72, 8, "bf16"), 6001), ((32, 4, 128, 8, "fp8_e4m3"), 1101)],
                          ids=["9KiB", "1152B", "fp8_4KiB"])
 def test_lists_beyond_the_memory_side_cache(gpu, geom, n):
