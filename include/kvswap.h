@@ -72,7 +72,8 @@
  *   - A call whose stream is being captured into a HIP graph (it joins through wait_event, or the caller
  *     captures a stream that it gave) runs with each replay; the handle's own state changes once, when the
  *     call is made.  Calls may ask for earlier ones that are in flight, which only a capture in the relaxed mode
- *     allows, and up to 60 blocks travel inside the graph: kv_move_blocks_noalloc takes any list in any mode.
+ *     allows.  A list of up to 60 blocks is part of the graph; a longer one may be read from memory that later
+ *     calls of the handle overwrite.  kv_move_blocks_noalloc may be captured in any mode, with any list.
  *   - Argument arrays are HOST pointers, read during the call, free on return.
  *   - pool_dev, scale_dev, bounce_dev are DEVICE pointers; staging_host is a
  *     pinned, device-mapped HOST pointer (hipHostMalloc / torch pin_memory),
